@@ -807,8 +807,7 @@ beagle_status beagle_generation(beagle_ctx* ctx, const beagle_programs* parents,
   a.child_consts = child_consts;
   a.child_const_count = child_const_count;
   a.slots = nullptr;
-  hipLaunchKernelGGL(bgl::k_generation, dim3((n + 63) / 64), dim3(64), 0, reinterpret_cast<hipStream_t>(stream),
-                     a);
+  bgl::launch_generation(a, reinterpret_cast<hipStream_t>(stream));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "generation launch");
   clear_error();
@@ -908,7 +907,7 @@ beagle_status beagle_generation_microcosm(beagle_ctx* ctx, const beagle_programs
     a.child_consts = child_consts;
     a.child_const_count = child_const_count;
     a.slots = m.slots;
-    hipLaunchKernelGGL(bgl::k_generation, dim3((n_children + 63) / 64), dim3(64), 0, s, a);
+    bgl::launch_generation(a, s);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "generation launch");
   }

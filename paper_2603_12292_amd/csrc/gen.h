@@ -52,6 +52,7 @@ struct GenStepArgs {
   // that a child need not read two header entries of a random parent; NULL:
   // always read them
   const int64_t* slots;
+  int32_t per_wave;  // children per wave (set by launch_generation)
 };
 
 struct InitArgs {
@@ -89,7 +90,7 @@ struct MicroArgs {
   int64_t* slots;
 };
 
-__global__ void k_generation(GenStepArgs a);
+void launch_generation(GenStepArgs a, hipStream_t s);
 __global__ void k_micro_threshold(MicroArgs a);
 __global__ void k_micro_count(MicroArgs a);
 __global__ void k_micro_scan(MicroArgs a);

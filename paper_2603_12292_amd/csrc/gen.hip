@@ -2,7 +2,7 @@
 // tournament selection, subtree crossover and point mutation on postfix
 // programs, driven by the Philox4x32-10 counter-based generator.
 //
-// One thread per child.  Child c's random words come from Philox with key =
+// Child c's random words come from Philox with key =
 // seed and counter (c, generation, block, tag); word j of the child's stream
 // is word j % 4 of block j / 4, so every draw has a fixed position whatever
 // operator the child ends up using, and children are independent of the
@@ -43,6 +43,7 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
   return o;
 }
 
+// word j of the stream of (seed, index, gen, tag)
 struct Stream {
   uint32_t k0, k1, index, gen, tag;
   int blk = -1;
@@ -55,7 +56,10 @@ struct Stream {
       words = philox4x32_10(index, gen, uint32_t(b), tag, k0, k1);
       blk = b;
     }
-    return words.v[j & 3];
+    // (selected, not indexed: an indexed array would be moved to LDS, 40 KB
+    // of it per 64 threads, and cost the kernel its occupancy)
+    const uint32_t lo = (j & 1) ? words.v[1] : words.v[0], hi = (j & 1) ? words.v[3] : words.v[2];
+    return (j & 2) ? hi : lo;
   }
 };
 
@@ -71,59 +75,22 @@ __device__ __noinline__ float const_value(uint32_t u, float lo, float hi) {
   return float(double(lo) + prod);
 }
 
-// Zeroes elements [from, to) of a child slot: element stores up to the first
-// 16-byte boundary, then 16-byte stores, then the tail (one thread writes a
-// whole slot, so element-wide stores would each touch another cache line
-// across the wave).
+// Zeroes elements [from, to) of a child slot with `lanes` threads (this one
+// number l): element stores up to the first 16-byte boundary, then 16-byte
+// stores, then the tail.
 template <class T>
-__device__ __forceinline__ void zero_fill(T* base, int from, int to) {
+__device__ __forceinline__ void zero_fill(T* base, int from, int to, int l, int lanes) {
   constexpr int PER = 16 / int(sizeof(T));
-  int i = from;
-  while (i < to && (reinterpret_cast<uintptr_t>(base + i) & 15u) != 0) base[i++] = T(0);
-  for (; i + PER <= to; i += PER) *reinterpret_cast<uint4*>(base + i) = make_uint4(0u, 0u, 0u, 0u);
-  for (; i < to; ++i) base[i] = T(0);
+  const int off = int((reinterpret_cast<uintptr_t>(base + from) & 15u) / sizeof(T));
+  const int head = off == 0 ? from : from + (PER - off) < to ? from + (PER - off) : to;
+  for (int i = from + l; i < head; i += lanes) base[i] = T(0);
+  const int vecs = (to - head) / PER;
+  for (int v = l; v < vecs; v += lanes) *reinterpret_cast<uint4*>(base + head + v * PER) = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = head + vecs * PER + l; i < to; i += lanes) base[i] = T(0);
 }
 
 // opcode of unary index u (0..4: SIN..SQRT, 5..11: SQUARE..TANH)
 __device__ __forceinline__ uint32_t unary_opcode(uint32_t u) { return u < 5u ? OP_SIN + u : OP_SQUARE + (u - 5u); }
-
-__device__ __forceinline__ int subtree_start(const uint16_t* tok, int i) {
-  int need = 1;
-  for (int j = i; j >= 0; --j) {
-    need += arity(tok[j] & 0xFFu) - 1;
-    if (need == 0) return j;
-  }
-  return 0;  // malformed parent: clamp (documented: parents must be valid)
-}
-
-// Appends parent tokens [from, to) to the child, renumbering constants.
-struct ChildWriter {
-  uint16_t* tok;
-  float* cst;
-  int len = 0;
-  int ncst = 0;
-  int max_consts;
-  __device__ ChildWriter(uint16_t* t, float* c, int mc) : tok(t), cst(c), max_consts(mc) {}
-  __device__ void put(uint32_t t, float cval) {
-    if ((t & 0xFFu) == OP_CONST) {
-      if (ncst < max_consts) {
-        tok[len++] = uint16_t(OP_CONST | (uint32_t(ncst) << 8));
-        cst[ncst++] = cval;
-      } else {
-        tok[len++] = uint16_t(OP_VAR);
-      }
-    } else {
-      tok[len++] = uint16_t(t);
-    }
-  }
-  __device__ void copy(const uint16_t* ptok, const float* pcst, int pcc, int from, int to) {
-    for (int i = from; i < to; ++i) {
-      const uint32_t t = ptok[i];
-      const uint32_t a = t >> 8;
-      put(t, ((t & 0xFFu) == OP_CONST && int(a) < pcc) ? pcst[a] : 0.0f);
-    }
-  }
-};
 
 __device__ __forceinline__ bool better(double fa, int ia, double fb, int ib) {
   // lower fitness wins; NaN loses to everything; ties -> lower index
@@ -133,113 +100,247 @@ __device__ __forceinline__ bool better(double fa, int ia, double fb, int ib) {
   return ia < ib;
 }
 
+// The winner of entrants first_draw .. first_draw + t - 1; four draws and
+// their fitness loads are made before the first comparison.
 __device__ __forceinline__ int tournament(Stream& s, int first_draw, int t, const double* fit, uint32_t N) {
-  int best = int(below(s.draw(first_draw), N));
-  double fb = fit[best];
-  for (int k = 1; k < t; ++k) {
-    const int e = int(below(s.draw(first_draw + k), N));
-    const double fe = fit[e];
-    if (better(fe, e, fb, best)) {
-      best = e;
-      fb = fe;
+  int best = 0x7FFFFFFF;
+  double fb = __longlong_as_double(0x7FF8000000000000LL);  // loses to every entrant
+  for (int k = 0; k < t; k += 4) {
+    int e[4];
+    double f[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      // (a repeated last entrant changes nothing)
+      e[u] = int(below(s.draw(first_draw + (k + u < t ? k + u : t - 1)), N));
+      f[u] = fit[e[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (better(f[u], e[u], fb, best)) {
+        best = e[u];
+        fb = f[u];
+      }
     }
   }
   return best;
 }
 
-__global__ void k_generation(GenStepArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.n) return;
-  const int t = a.tournament;
-  Stream s(a.seed, uint32_t(c), a.generation, a.tag);
-  const double choice = unit01(s.draw(0));
-  const uint32_t N = uint32_t(a.n_parents);
-  int ia, ib;
-  if (a.surv) {
-    const int S = *a.n_surv;
-    const uint32_t ua = below(s.draw(1), uint32_t(S > 0 ? S : N));
-    const uint32_t ub = below(s.draw(1 + t), uint32_t(S > 0 ? S : N));
-    ia = S > 0 ? a.surv[ua] : int(ua);
-    ib = S > 0 ? a.surv[ub] : int(ub);
-  } else {
-    ia = tournament(s, 1, t, a.fitness, N);
-    ib = tournament(s, 1 + t, t, a.fitness, N);
-  }
-  // (a regular layout gives the offsets without reading them)
-  const bool reg = a.slots && a.slots[0] != 0;
-  const int64_t oa = reg ? a.slots[1] + int64_t(ia) * a.slots[2] : a.tok_offset[ia];
-  const int64_t ob = reg ? a.slots[1] + int64_t(ib) * a.slots[2] : a.tok_offset[ib];
-  const int64_t coa = reg ? a.slots[3] + int64_t(ia) * a.slots[4] : a.const_offset[ia];
-  const int64_t cob = reg ? a.slots[3] + int64_t(ib) * a.slots[4] : a.const_offset[ib];
-  const int LA = a.tok_len[ia], LB = a.tok_len[ib];
-  const int ca = a.const_count[ia], cb = a.const_count[ib];
-  // a parent outside its arrays, empty or longer than a child slot gives an
-  // empty child (parents are meant to be valid programs)
-  auto usable = [&](int64_t o, int L, int64_t co, int cc) {
-    return L > 0 && L <= a.max_len && o >= 0 && o + L <= a.n_tokens && cc >= 0 &&
-           (cc == 0 || (co >= 0 && co + cc <= a.n_consts));
-  };
-  const bool okA = usable(oa, LA, coa, ca), okB = usable(ob, LB, cob, cb);
-  const uint16_t* A = a.tokens + (okA ? oa : 0);
-  const uint16_t* B = a.tokens + (okB ? ob : 0);
-  const float* Ac = a.consts + (okA && ca > 0 ? coa : 0);
-  const float* Bc = a.consts + (okB && cb > 0 ? cob : 0);
-  const int xa = int(below(s.draw(2 * t + 1), uint32_t(okA ? LA : 0)));
-  const int xb = int(below(s.draw(2 * t + 2), uint32_t(okB ? LB : 0)));
-  const int mpos = int(below(s.draw(2 * t + 3), uint32_t(okA ? LA : 0)));
-  const uint32_t msym = s.draw(2 * t + 4);
-  const uint32_t mconst = s.draw(2 * t + 5);
-  uint16_t* out = a.child_tokens + int64_t(c) * a.max_len;
-  float* outc = a.child_consts + int64_t(c) * a.max_consts;
-  ChildWriter w(out, outc, a.max_consts);
-  const bool cross = choice < double(a.t_cross);
-  if (!okA || (cross && !okB)) {
-    // empty child
-  } else if (cross) {
-    const int sa = subtree_start(A, xa);
-    const int sb = subtree_start(B, xb);
-    const int len = LA - (xa - sa + 1) + (xb - sb + 1);
-    if (len > a.max_len) {
-      w.copy(A, Ac, ca, 0, LA);
-    } else {
-      w.copy(A, Ac, ca, 0, sa);
-      w.copy(B, Bc, cb, sb, xb + 1);
-      w.copy(A, Ac, ca, xa + 1, LA);
+// Children in two phases.  First every lane (of the first `per_wave`) draws
+// one child's random words and parents and reads the parents' headers; then
+// the wave writes its children, GEN_GROUP lanes each, eight at a time: a
+// group walks the child's token positions GEN_GROUP at a time, so that
+// parents are read and children written in runs of lanes, and the constants
+// are numbered by ballots.  Bound by the reads of random parents (a token
+// slot, a constant row and two header entries, a memory line each) and the
+// child writes.  One thread per child walked its tokens one by one, each
+// lane in another line, behind 40 KB of LDS per wave: 572 us for 10^6
+// children of slots of 64 tokens (microcosm selection), 128 us for 16 384 of
+// 128 tokens (tournaments of four and crossover).
+constexpr int GEN_GROUP = 8;
+constexpr int GEN_GROUPS = 64 / GEN_GROUP;
+
+// The start of the subtree that ends at position i of tok, found by every
+// group for itself: GEN_GROUP positions a step backwards from i, the open
+// operand count by prefix sums over the group's lanes (0 for a malformed
+// parent; parents must be valid).  Groups with `on` false leave at once; every
+// lane of the wave takes part.
+__device__ __forceinline__ int subtree_start(const uint16_t* tok, int i, bool on, int gl, int gb) {
+  int need = 1, start = 0;
+  bool open = on;
+  for (int j0 = i; __builtin_amdgcn_ballot_w64(open) != 0; j0 -= GEN_GROUP) {
+    const int j = j0 - gl;
+    int v = open && j >= 0 ? arity(tok[j] & 0xFFu) - 1 : 0;
+#pragma unroll
+    for (int d = 1; d < GEN_GROUP; d <<= 1) {
+      const int w = __builtin_amdgcn_ds_bpermute((gb + (gl >= d ? gl - d : gl)) << 2, v);
+      v += gl >= d ? w : 0;
     }
-  } else if (choice < double(a.t_mut)) {
-    const uint32_t old = A[mpos] & 0xFFu;
-    const int ar = arity(old);
-    uint32_t repl;
-    float rval = 0.0f;
-    if (ar == 2) {
-      repl = below(msym, 4);  // ADD, SUB, MUL, DIV
-    } else if (ar == 1) {
-      repl = unary_opcode(below(msym, uint32_t(a.n_unary)));
+    const uint32_t closed = uint32_t(__builtin_amdgcn_ballot_w64(open && j >= 0 && need + v == 0) >> gb) &
+                            ((1u << GEN_GROUP) - 1u);
+    const int last = __builtin_amdgcn_ds_bpermute((gb + GEN_GROUP - 1) << 2, v);
+    if (open && closed != 0) {
+      start = j0 - (__ffs(closed) - 1);
+      open = false;
+    }
+    need += last;
+    if (j0 - GEN_GROUP < 0) open = false;
+  }
+  return start;
+}
+
+__global__ void __launch_bounds__(256) k_generation(GenStepArgs a) {
+  const int lane = int(threadIdx.x & 63u);
+  const int64_t c0 = (int64_t(blockIdx.x) * 4 + int64_t(threadIdx.x >> 6)) * a.per_wave;
+  if (c0 >= a.n) return;
+  const int here = int(a.n - c0 < a.per_wave ? a.n - c0 : a.per_wave);
+  // ---- phase 1: lane j draws child c0 + j
+  const int t = a.tournament;
+  const uint32_t N = uint32_t(a.n_parents);
+  int kind = 0;  // 0 empty, 1 copy of A, 2 mutant of A, 3 crossover
+  int LA = 0, LB = 0, ca = 0, cb = 0, xa = 0, xb = 0, mpos = 0;
+  int64_t oa = 0, ob = 0, coa = 0, cob = 0;
+  uint32_t msym = 0, mconst = 0;
+  if (lane < here) {
+    Stream s(a.seed, uint32_t(c0 + lane), a.generation, a.tag);
+    const double choice = unit01(s.draw(0));
+    int ia, ib;
+    if (a.surv) {
+      const int S = *a.n_surv;
+      const uint32_t ua = below(s.draw(1), uint32_t(S > 0 ? S : N));
+      const uint32_t ub = below(s.draw(1 + t), uint32_t(S > 0 ? S : N));
+      ia = S > 0 ? a.surv[ua] : int(ua);
+      ib = S > 0 ? a.surv[ub] : int(ub);
     } else {
-      const uint32_t sym = below(msym, uint32_t(a.D + 1));
-      if (int(sym) < a.D) {
-        repl = OP_VAR | (sym << 8);
-      } else {
-        int others = 0;
-        for (int i = 0; i < LA; ++i) others += (i != mpos && (A[i] & 0xFFu) == OP_CONST) ? 1 : 0;
-        if (others < a.max_consts) {
-          repl = OP_CONST;
-          rval = const_value(mconst, a.const_lo, a.const_hi);
-        } else {
-          repl = OP_VAR;
-        }
+      ia = tournament(s, 1, t, a.fitness, N);
+      ib = tournament(s, 1 + t, t, a.fitness, N);
+    }
+    const bool cross = choice < double(a.t_cross);
+    // a parent outside its arrays, empty or longer than a child slot gives an
+    // empty child (parents are meant to be valid programs)
+    auto usable = [&](int64_t o, int L, int64_t co, int cc) {
+      return L > 0 && L <= a.max_len && o >= 0 && o + L <= a.n_tokens && cc >= 0 &&
+             (cc == 0 || (co >= 0 && co + cc <= a.n_consts));
+    };
+    // (a regular layout gives the offsets without reading them)
+    const bool reg = a.slots && a.slots[0] != 0;
+    oa = reg ? a.slots[1] + int64_t(ia) * a.slots[2] : a.tok_offset[ia];
+    coa = reg ? a.slots[3] + int64_t(ia) * a.slots[4] : a.const_offset[ia];
+    LA = a.tok_len[ia];
+    ca = a.const_count[ia];
+    bool okB = false;
+    if (cross) {  // (only crossover reads parent B)
+      ob = reg ? a.slots[1] + int64_t(ib) * a.slots[2] : a.tok_offset[ib];
+      cob = reg ? a.slots[3] + int64_t(ib) * a.slots[4] : a.const_offset[ib];
+      LB = a.tok_len[ib];
+      cb = a.const_count[ib];
+      okB = usable(ob, LB, cob, cb);
+    }
+    const bool okA = usable(oa, LA, coa, ca);
+    kind = !okA || (cross && !okB) ? 0 : cross ? 3 : choice < double(a.t_mut) ? 2 : 1;
+    xa = int(below(s.draw(2 * t + 1), uint32_t(okA ? LA : 0)));
+    xb = int(below(s.draw(2 * t + 2), uint32_t(okB ? LB : 0)));
+    mpos = int(below(s.draw(2 * t + 3), uint32_t(okA ? LA : 0)));
+    msym = s.draw(2 * t + 4);
+    mconst = s.draw(2 * t + 5);
+    if (kind == 0) LA = LB = ca = cb = 0, oa = ob = coa = cob = 0;
+  }
+  // ---- phase 2: the wave's groups write the children
+  const int gl = lane & (GEN_GROUP - 1), gb = lane & ~(GEN_GROUP - 1);
+  auto of = [](int v, int src) { return __builtin_amdgcn_ds_bpermute(src << 2, v); };
+  auto of64 = [&](int64_t v, int src) {
+    const uint32_t lo = uint32_t(of(int(uint32_t(uint64_t(v))), src));
+    const uint32_t hi = uint32_t(of(int(uint32_t(uint64_t(v) >> 32)), src));
+    return int64_t((uint64_t(hi) << 32) | lo);
+  };
+  for (int j0 = 0; j0 < here; j0 += GEN_GROUPS) {
+    const int j = j0 + (lane / GEN_GROUP);
+    const bool live = j < here;
+    const int sj = live ? j : 0;
+    // (every lane takes part in the reads across lanes)
+    int k = of(kind, sj);
+    if (!live) k = 0;
+    const int la = of(LA, sj), pa = of(ca, sj), pb = of(cb, sj), ma = of(mpos, sj);
+    const int ya = of(xa, sj), yb = of(xb, sj);
+    const uint16_t* A = a.tokens + of64(oa, sj);
+    const uint16_t* B = a.tokens + of64(ob, sj);
+    const float* Ac = a.consts + of64(coa, sj);
+    const float* Bc = a.consts + of64(cob, sj);
+    const uint32_t ms = uint32_t(of(int(msym), sj)), mc = uint32_t(of(int(mconst), sj));
+    // crossover: A[0, sa) B[sb, yb] A[ya + 1, la)
+    int sa = 0x7FFFFFFF, nb = 0, sb = 0, len = k == 0 ? 0 : la;
+    if (__builtin_amdgcn_ballot_w64(k == 3) != 0) {
+      const int s0 = subtree_start(A, ya, k == 3, gl, gb);
+      const int s1 = subtree_start(B, yb, k == 3, gl, gb);
+      const int l = la - (ya - s0 + 1) + (yb - s1 + 1);
+      if (k == 3 && l <= a.max_len) {  // (a longer child: a copy of A)
+        sa = s0;
+        sb = s1;
+        nb = yb - s1 + 1;
+        len = l;
       }
     }
-    w.copy(A, Ac, ca, 0, mpos);
-    w.put(repl, rval);
-    w.copy(A, Ac, ca, mpos + 1, LA);
-  } else {
-    w.copy(A, Ac, ca, 0, LA);
+    // mutation: the new symbol of position ma
+    uint32_t repl = 0;
+    float rval = 0.0f;
+    bool need_count = false;
+    if (k == 2) {
+      const uint32_t old = A[ma] & 0xFFu;
+      const int ar = arity(old);
+      if (ar == 2) {
+        repl = below(ms, 4);  // ADD, SUB, MUL, DIV
+      } else if (ar == 1) {
+        repl = unary_opcode(below(ms, uint32_t(a.n_unary)));
+      } else {
+        const uint32_t sym = below(ms, uint32_t(a.D + 1));
+        need_count = int(sym) >= a.D;
+        repl = need_count ? uint32_t(OP_CONST) : OP_VAR | (sym << 8);
+      }
+    }
+    if (__builtin_amdgcn_ballot_w64(need_count) != 0) {
+      // a new constant only if the parent's others leave it a slot
+      int others = 0;
+      for (int i0 = 0; __builtin_amdgcn_ballot_w64(need_count && i0 < la) != 0; i0 += GEN_GROUP) {
+        const int i = i0 + gl;
+        const bool cst = need_count && i < la && i != ma && (A[i] & 0xFFu) == OP_CONST;
+        others += __popc(uint32_t(__builtin_amdgcn_ballot_w64(cst) >> gb) & ((1u << GEN_GROUP) - 1u));
+      }
+      if (need_count) {
+        if (others < a.max_consts)
+          rval = const_value(mc, a.const_lo, a.const_hi);
+        else
+          repl = OP_VAR;
+      }
+    }
+    const int64_t c = c0 + j;
+    uint16_t* out = a.child_tokens + (live ? c : 0) * a.max_len;
+    float* outc = a.child_consts + (live ? c : 0) * a.max_consts;
+    int ncst = 0;
+    for (int i0 = 0; __builtin_amdgcn_ballot_w64(i0 < len) != 0; i0 += GEN_GROUP) {
+      const int i = i0 + gl;
+      const bool on = i < len;
+      const bool inb = i >= sa && i < sa + nb;
+      uint32_t tk = 0;
+      if (on) tk = inb ? B[sb + i - sa] : A[i < sa ? i : ya + 1 + (i - sa - nb)];
+      const bool mut = k == 2 && i == ma;
+      if (mut) tk = repl;
+      const bool cst = on && (tk & 0xFFu) == OP_CONST;
+      const uint32_t m = uint32_t(__builtin_amdgcn_ballot_w64(cst) >> gb) & ((1u << GEN_GROUP) - 1u);
+      if (cst) {
+        const int slot = ncst + __popc(m & ((1u << gl) - 1u));
+        const int arg = int(tk >> 8);
+        float v = rval;
+        if (!mut) v = arg < (inb ? pb : pa) ? (inb ? Bc : Ac)[arg] : 0.0f;
+        if (slot < a.max_consts) {
+          tk = OP_CONST | (uint32_t(slot) << 8);
+          outc[slot] = v;
+        } else {
+          tk = OP_VAR;
+        }
+      }
+      if (on) out[i] = uint16_t(tk);
+      ncst += __popc(m);
+    }
+    ncst = ncst < a.max_consts ? ncst : a.max_consts;
+    if (live) {
+      zero_fill(out, len, a.max_len, gl, GEN_GROUP);
+      zero_fill(outc, ncst, a.max_consts, gl, GEN_GROUP);
+      if (gl == 0) {
+        a.child_len[c] = len;
+        a.child_const_count[c] = ncst;
+      }
+    }
   }
-  zero_fill(out, w.len, a.max_len);
-  zero_fill(outc, w.ncst, a.max_consts);
-  a.child_len[c] = w.len;
-  a.child_const_count[c] = w.ncst;
+}
+
+// Children per wave: 64, fewer (not below the GEN_GROUPS that the second
+// phase writes at a time) where that would leave under 8192 waves, eight per
+// SIMD: the phases are chains of dependent reads, which only other waves hide.
+void launch_generation(GenStepArgs a, hipStream_t s) {
+  int per = 64;
+  while (per > GEN_GROUPS && int64_t(a.n) < int64_t(8192) * per) per >>= 1;
+  a.per_wave = per;
+  const int64_t waves = (int64_t(a.n) + per - 1) / per;
+  hipLaunchKernelGGL(k_generation, dim3(uint32_t((waves + 3) / 4)), dim3(256), 0, s, a);
 }
 
 // ---- microcosm selection ----------------------------------------------------
@@ -410,8 +511,8 @@ __global__ void k_init_population(InitArgs a) {
     if (sp == 0) break;
     level = fr[sp - 1].level + 1;
   }
-  zero_fill(out, len, a.max_len);
-  zero_fill(outc, ncst, a.max_consts);
+  zero_fill(out, len, a.max_len, 0, 1);
+  zero_fill(outc, ncst, a.max_consts, 0, 1);
   a.len[c] = len;
   a.const_count[c] = ncst;
 }
