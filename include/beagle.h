@@ -250,8 +250,9 @@ beagle_status beagle_ctx_set_decoder(beagle_ctx* ctx, int decoder);
 typedef enum { BEAGLE_TUNE_AUTO = 0, BEAGLE_TUNE_WIDE = 1, BEAGLE_TUNE_NARROW = 2 } beagle_tuning;
 
 /* How many fitness cases each lane carries through the interpreter for the
- * common programs (stack of at most 4 values): 8 (BEAGLE_TUNE_WIDE, used
- * only where D <= 8) or 4 (BEAGLE_TUNE_NARROW).  BEAGLE_TUNE_AUTO, the
+ * common programs (stack of at most 4 values): 8 (BEAGLE_TUNE_WIDE; case
+ * sets split into chunks of less than 512 cases take 4 all the same) or 4
+ * (BEAGLE_TUNE_NARROW).  BEAGLE_TUNE_AUTO, the
  * default, times both the first time an evaluation meets a problem-shape
  * bucket (fitness kind, D, log2 M, log2 of the mean program length) -- that
  * call synchronises the device -- and keeps the faster in the context.  When
@@ -281,10 +282,7 @@ beagle_status beagle_ctx_tile_width(beagle_ctx* ctx, int kind, int32_t D, int64_
  * meets a problem table (every pointer and size above, the tile widths and
  * the workspace) and replays that graph while the table is unchanged; the
  * table itself is copied to the device before every launch.  Results are
- * bit-identical to beagle_eval on each problem alone, except on problems
- * that beagle_eval gives to its resident-inputs kernel (at least 4096
- * programs on a case set whose inputs fit 64 KB in one chunk): there the
- * partial sums are added in another order (same accuracy).  Problems with no
+ * bit-identical to beagle_eval on each problem alone.  Problems with no
  * programs are skipped.  The workspace must hold every problem at once
  * (BEAGLE_E_NOMEM beyond the context cap: no slicing here).  Correlation
  * fitness needs M >= 2 in every problem.  n_problems <= 65535. */

@@ -84,8 +84,8 @@ beagle_status check_data(const beagle_dataset* d, int kind) {
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
-// Case chunking of the evaluation grid: about 32K cases per chunk, more
-// chunks when the population alone gives too few workgroups to fill the GPU.
+// Case chunking: at most max_chunk_cases cases per chunk, more chunks when
+// the population alone gives too few work items to fill the GPU.
 void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit) {
   const int64_t max_chunks = std::max<int64_t>(1, (M + unit - 1) / unit);
   int64_t C = std::max<int64_t>(1, (M + max_chunk_cases - 1) / max_chunk_cases);
@@ -95,6 +95,14 @@ void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int6
   const int64_t ch = round_up((M + C - 1) / C, unit);
   *chunk = ch;
   *n_chunks = int32_t((M + ch - 1) / ch);
+}
+
+void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks) {
+  // chunks of whole wide tiles, of half tiles where those leave under 4096
+  // work items; never more than 1024 chunks (the partial sums' memory)
+  const int64_t most = std::max<int64_t>(bgl::CHUNK_CASES, round_up((M + 1023) / 1024, bgl::TILE));
+  const int64_t unit = N * ((M + bgl::TILE - 1) / bgl::TILE) < 4096 ? bgl::CHUNK_UNIT : bgl::TILE;
+  choose_chunks(M, N, chunk, n_chunks, most, unit);
 }
 
 static __global__ void k_zero_i32(int32_t* p, int64_t n) {
@@ -115,20 +123,25 @@ using namespace bgl::host;
 
 // The pieces of workspace one evaluation uses.
 struct EvalLayout {
-  size_t code, aux, cval, s_stack, s_start, s_need, owner, cowner, meta, class_count, class_list, len_list, long_list,
-      work, Xt, yp, stats, part, gpart, coef, total;
+  size_t code, aux, vrow, cval, s_stack, s_start, s_need, owner, cowner, meta, class_count, class_list, len_list,
+      long_list, work, Xt, stats, part, gpart, coef, total;
+  int32_t derived, rows;          // derived input rows staged; rows per staged tile
   int64_t Mp, chunk, gchunk;      // case chunks of the evaluation and of the adjoint
   int32_t n_chunks, gn_chunks, slice;
 };
 
-EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice,
+EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, bool derived,
                        bool with_grad = false) {
   EvalLayout L{};
   Carve c;
+  L.derived = derived ? 1 : 0;
+  L.rows = bgl::stage_rows(d->D, L.derived);
   const int64_t nt = std::max<int64_t>(P->n_tokens, 1);
   const int64_t N = std::max<int32_t>(P->n_programs, 1);
   L.code = c.take<uint32_t>(nt);
   L.aux = c.take<uint32_t>(nt);
+  // (the row lists, a byte per token: an evaluation writes no adjoint words)
+  L.vrow = with_grad ? c.take<uint8_t>(nt) : L.aux;
   L.cval = c.take<float>(nt);
   L.s_stack = c.take<int32_t>(nt);
   L.s_start = c.take<int32_t>(nt);
@@ -142,14 +155,13 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   L.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
   L.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
   L.long_list = c.take<int32_t>(size_t(N));
-  L.Mp = round_up(d->M, bgl::CASES_PER_BLOCK_ITER);
-  L.Xt = c.take<float>(size_t(d->D) * L.Mp);
-  L.yp = c.take<float>(L.Mp);
+  L.Mp = round_up(d->M, bgl::TILE);
+  L.Xt = c.take<float>(size_t(L.rows) * L.Mp);
   L.stats = c.take<double>(4);
   L.slice = slice;
   // the chunking depends on the whole population only, so that a sliced
   // evaluation sums every program's partials in the same order
-  choose_chunks(d->M, N, &L.chunk, &L.n_chunks, 32768, bgl::CASES_PER_BLOCK_ITER);
+  eval_chunks(d->M, N, &L.chunk, &L.n_chunks);
   // the adjoint's kernels each walk one list of programs: shorter chunks
   // keep a short list from leaving most of the chip idle
   L.gchunk = 0;
@@ -184,6 +196,8 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   pa.code = reinterpret_cast<uint32_t*>(ws + L.code);
   pa.aux = reinterpret_cast<uint32_t*>(ws + L.aux);
   pa.cval = reinterpret_cast<float*>(ws + L.cval);
+  pa.vrow = reinterpret_cast<uint8_t*>(ws + L.vrow);
+  pa.derived = L.derived;
   pa.max_words = max_words;
   pa.scr_stack = reinterpret_cast<int32_t*>(ws + L.s_stack);
   pa.scr_start = reinterpret_cast<int32_t*>(ws + L.s_start);
@@ -208,13 +222,14 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   sa.M = d->M;
   sa.Mp = L.Mp;
   sa.D = d->D;
+  sa.derived = L.derived;
   sa.Xt = reinterpret_cast<float*>(ws + L.Xt);
-  sa.yp = reinterpret_cast<float*>(ws + L.yp);
   // staging of the cases beside the disjoint-ranges check (the fill and
   // mark passes return at once when the ranges are sorted and disjoint),
   // then programs of at most 64 tokens, then the ones longer than that
   const uint32_t pgrid = uint32_t((P->n_programs + 255) / 256);
-  const uint32_t sgrid = uint32_t(std::min<int64_t>((L.Mp + 255) / 256, 1 << 16));
+  const int64_t sthreads = L.Mp * d->D <= (1 << 18) ? L.Mp * d->D : L.Mp;  // (as k_stage_and_check splits)
+  const uint32_t sgrid = uint32_t(std::min<int64_t>((sthreads + 255) / 256, 1 << 16));
   hipLaunchKernelGGL(bgl::k_stage_and_check, dim3(sgrid + pgrid), dim3(256), 0, s, sa, pa, sgrid);
   hipLaunchKernelGGL(bgl::k_layout_fill, dim3(1024), dim3(256), 0, s, pa);
   hipLaunchKernelGGL(bgl::k_layout_mark, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, pa);
@@ -238,57 +253,31 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   return BEAGLE_OK;
 }
 
-// LDS of a values kernel: the case tile of D variables (256 floats each).
-size_t values_lds(int32_t D) { return size_t(D < 1 ? 1 : D) * 256 * sizeof(float); }
-
-beagle_status launch_values(char* ws, const beagle_programs* P, const beagle_dataset* d,
-                            const EvalLayout& L, int64_t m, float* out, int shift_mode, hipStream_t s) {
+beagle_status launch_values(char* ws, const beagle_programs* P, const EvalLayout& L, int64_t m, float* out,
+                            int shift_mode, hipStream_t s) {
   bgl::ValuesArgs va;
   va.code = reinterpret_cast<const uint32_t*>(ws + L.code);
   va.cval = reinterpret_cast<const float*>(ws + L.cval);
   va.tok_offset = P->tok_offset;
   va.meta = reinterpret_cast<bgl::ProgMeta*>(ws + L.meta);
   va.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-  va.Mp = L.Mp;
+  va.rows = L.rows;
   va.m = m;
-  va.D = d->D;
   va.n_programs = P->n_programs;
   va.out = out;
   va.shift_mode = shift_mode;
   const int64_t tiles = (m + 63) / 64;
   if (tiles > 65535) return fail(BEAGLE_E_UNSUPPORTED, "predict: M > 4194240");
-  hipLaunchKernelGGL(bgl::k_values, dim3(P->n_programs, uint32_t(tiles)), dim3(64), values_lds(d->D), s, va);
+  hipLaunchKernelGGL(bgl::k_values, dim3(P->n_programs, uint32_t(tiles)), dim3(64), 0, s, va);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "values launch");
   return BEAGLE_OK;
 }
 
 // The correlation shifts before an evaluation (correlation fitness and the
-// Eq. 2 score).  When the shape takes the resident-inputs kernels, the
-// shifts of classes 0 and 1 come from those kernels' first pass
-// (*in_kernel = true) and only the class-2 programs run the shift pass here.
-beagle_status launch_shifts(char* ws, const beagle_programs* P, const beagle_dataset* d, const EvalLayout& L,
-                            hipStream_t s, bool* in_kernel) {
-  *in_kernel = bgl::resident_eligible(d->M, d->D, L.n_chunks, P->n_programs);
-  if (!*in_kernel) return launch_values(ws, P, d, L, 1, nullptr, 1, s);
-  bgl::ValuesArgs va;
-  va.code = reinterpret_cast<const uint32_t*>(ws + L.code);
-  va.cval = reinterpret_cast<const float*>(ws + L.cval);
-  va.tok_offset = P->tok_offset;
-  va.meta = reinterpret_cast<bgl::ProgMeta*>(ws + L.meta);
-  va.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-  va.Mp = L.Mp;
-  va.m = 1;
-  va.D = d->D;
-  va.n_programs = P->n_programs;
-  va.out = nullptr;
-  va.shift_mode = 1;
-  hipLaunchKernelGGL(bgl::k_values_deep, dim3(2048), dim3(64), values_lds(d->D), s, va,
-                     reinterpret_cast<const int32_t*>(ws + L.class_count),
-                     reinterpret_cast<const int32_t*>(ws + L.class_list), P->n_programs);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "values launch");
-  return BEAGLE_OK;
+// Eq. 2 score); with one chunk the evaluation kernels find them themselves.
+beagle_status launch_shifts(char* ws, const beagle_programs* P, const EvalLayout& L, hipStream_t s) {
+  return L.n_chunks == 1 ? BEAGLE_OK : launch_values(ws, P, L, 1, nullptr, 1, s);
 }
 
 // Target statistics of data->y (correlation fitness, Eq. 2 score) into
@@ -462,10 +451,12 @@ EvalLayout capped_layout(const beagle_programs* progs, const beagle_dataset* dat
                          int32_t* slice_out) {
   const int n_sums = bgl::kind_sums(kind);
   int32_t slice = progs->n_programs;
-  EvalLayout L = eval_layout(progs, data, n_sums, slice);
+  EvalLayout L = eval_layout(progs, data, n_sums, slice, use_derived(progs->n_programs));
+  // without the derived rows where they do not fit (the same values)
+  if (cap && L.total > cap && L.derived) L = eval_layout(progs, data, n_sums, slice, false);
   while (cap && L.total > cap && slice > 1) {
     slice = (slice + 1) / 2;
-    L = eval_layout(progs, data, n_sums, slice);
+    L = eval_layout(progs, data, n_sums, slice, false);
   }
   *slice_out = slice;
   return L;
@@ -488,11 +479,11 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
     return st;
   st = prepare(ws, progs, data, L, status, s, ctx ? ctx->decoder : BEAGLE_DECODE_WAVE);
   if (st != BEAGLE_OK) return st;
-  bool shift_in_kernel = false;
+  const bool shift_in_kernel = with_stats && L.n_chunks == 1;
   if (with_stats) {
     // the shifts need only the decoded programs and the staged cases; the
     // interpreter launches that follow read the statistics
-    st = launch_shifts(ws, progs, data, L, s, &shift_in_kernel);
+    st = launch_shifts(ws, progs, L, s);
     if (st != BEAGLE_OK) return st;
     if ((st = join_target_stats(join, s)) != BEAGLE_OK) return st;
   }
@@ -502,11 +493,10 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
     ea.cval = reinterpret_cast<const float*>(ws + L.cval);
     ea.tok_offset = progs->tok_offset + p0;
     ea.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta) + p0;
+    ea.vrow = reinterpret_cast<const uint8_t*>(ws + L.vrow);
     ea.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-    ea.yp = reinterpret_cast<const float*>(ws + L.yp);
+    ea.rows = L.rows;
     ea.M = data->M;
-    ea.Mp = L.Mp;
-    ea.D = data->D;
     ea.n_programs = np;
     ea.n_chunks = L.n_chunks;
     ea.chunk = L.chunk;
@@ -669,7 +659,9 @@ beagle_status beagle_eval_workspace_size(const beagle_programs* progs, const bea
   if (st != BEAGLE_OK) return st;
   st = check_data(data, kind);
   if (st != BEAGLE_OK) return st;
-  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1)).total;
+  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1),
+                       use_derived(progs->n_programs))
+               .total;
   return BEAGLE_OK;
 }
 
@@ -687,12 +679,13 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  EvalLayout L = eval_layout(progs, data, 1, 1);
+  EvalLayout L = eval_layout(progs, data, 1, 1, use_derived(progs->n_programs));
+  if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, 1, 1, false);
   st = reserve(ctx, L.total);
   if (st != BEAGLE_OK) return st;
   st = prepare(ctx->ws, progs, data, L, status, s, ctx->decoder);
   if (st != BEAGLE_OK) return st;
-  st = launch_values(ctx->ws, progs, data, L, data->M, yhat, 0, s);
+  st = launch_values(ctx->ws, progs, L, data->M, yhat, 0, s);
   if (st != BEAGLE_OK) return st;
   clear_error();
   return BEAGLE_OK;
@@ -927,8 +920,8 @@ namespace {
 beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const beagle_dataset* data,
                         const EvalLayout& L, double* fitness, hipEvent_t join, hipStream_t s) {
   char* ws = ctx->ws;
-  bool shift_in_kernel = false;
-  beagle_status st = launch_shifts(ws, progs, data, L, s, &shift_in_kernel);
+  const bool shift_in_kernel = L.n_chunks == 1;
+  beagle_status st = launch_shifts(ws, progs, L, s);
   if (st != BEAGLE_OK) return st;
   if ((st = join_target_stats(join, s)) != BEAGLE_OK) return st;
   bgl::EvalArgs ea;
@@ -936,11 +929,10 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   ea.cval = reinterpret_cast<const float*>(ws + L.cval);
   ea.tok_offset = progs->tok_offset;
   ea.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta);
+  ea.vrow = reinterpret_cast<const uint8_t*>(ws + L.vrow);
   ea.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-  ea.yp = reinterpret_cast<const float*>(ws + L.yp);
+  ea.rows = L.rows;
   ea.M = data->M;
-  ea.Mp = L.Mp;
-  ea.D = data->D;
   ea.n_programs = progs->n_programs;
   ea.n_chunks = L.n_chunks;
   ea.chunk = L.chunk;
@@ -995,7 +987,7 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool corr = kind == BEAGLE_FIT_CORR;
-  EvalLayout L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, true);
+  EvalLayout L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, false, true);
   st = reserve(ctx, L.total);
   if (st != BEAGLE_OK) return st;
   hipEvent_t join = nullptr;
@@ -1022,9 +1014,8 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   ga.const_offset = progs->const_offset;
   ga.const_count = progs->const_count;
   ga.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-  ga.yp = reinterpret_cast<const float*>(ws + L.yp);
+  ga.rows = L.rows;
   ga.M = data->M;
-  ga.Mp = L.Mp;
   ga.D = data->D;
   ga.n_programs = progs->n_programs;
   ga.n_chunks = L.gn_chunks;

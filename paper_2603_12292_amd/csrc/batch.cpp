@@ -47,8 +47,7 @@ constexpr size_t MAX_GRAPHS = 8;
 
 struct Batch {
   bgl::BatchArgs args;
-  int max_d[bgl::N_BATCH_LISTS];
-  int has[bgl::N_BATCH_LISTS];
+  int has[bgl::N_LISTS];
   int64_t n_programs = 0, n_cases = 0;
   int n = 0;
 };
@@ -69,7 +68,7 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   hipLaunchKernelGGL(bgl::k_batch_items, dim3(1), dim3(64), 0, s, b.args);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = bgl::launch_eval_batch(b.args.kind, b.args, b.max_d, b.has, s, nullptr, nullptr);
+  e = bgl::launch_eval_batch(b.args.kind, b.args, b.has, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(bgl::k_finalize_batch, dim3(uint32_t((b.n_programs + 255) / 256)), dim3(256), 0, s, b.args);
   return hipGetLastError();
@@ -121,42 +120,48 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   });
   const int n = int(active.size());
 
-  // workspace layout
-  Carve c;
-  const size_t at_table = c.take<bgl::BatchProblem>(n);
-  const size_t at_items = c.take<int64_t>(size_t(bgl::N_BATCH_LISTS) * (n + 1));
-  const size_t at_work = c.take<unsigned long long>(bgl::N_BATCH_LISTS);
-  const size_t at_counts = c.take<int32_t>(size_t(64) * n);
+  // workspace layout, with derived input rows where they fit
   struct Off {
-    size_t code, aux, cval, s_stack, s_start, s_need, owner, meta, class_list, len_list, Xt, yp, stats, part;
+    size_t code, aux, cval, s_stack, s_start, s_need, owner, meta, class_list, len_list, Xt, stats, part;
     int64_t Mp, chunk;
-    int32_t n_chunks;
+    int32_t n_chunks, derived;
   };
   std::vector<Off> off(n);
-  for (int i = 0; i < n; ++i) {
-    const beagle_programs& P = progs[active[i]];
-    const beagle_dataset& d = data[active[i]];
-    const int64_t nt = std::max<int64_t>(P.n_tokens, 1);
-    const int64_t N = P.n_programs;
-    Off& o = off[i];
-    o.code = c.take<uint32_t>(nt);
-    o.aux = c.take<uint32_t>(nt);
-    o.cval = c.take<float>(nt);
-    o.s_stack = c.take<int32_t>(nt);
-    o.s_start = c.take<int32_t>(nt);
-    o.s_need = c.take<int32_t>(nt);
-    o.owner = c.take<int32_t>(nt);
-    o.meta = c.take<bgl::ProgMeta>(N);
-    o.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
-    o.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
-    o.Mp = round_up(d.M, bgl::CASES_PER_BLOCK_ITER);
-    o.Xt = c.take<float>(size_t(d.D) * o.Mp);
-    o.yp = c.take<float>(o.Mp);
-    o.stats = c.take<double>(4);
-    choose_chunks(d.M, N, &o.chunk, &o.n_chunks, 32768, bgl::CASES_PER_BLOCK_ITER);
-    o.part = c.take<double>(size_t(n_sums) * o.n_chunks * N);
-  }
-  beagle_status st = reserve(ctx, c.used + 256);
+  size_t at_table = 0, at_items = 0, at_work = 0, at_counts = 0;
+  auto lay_out = [&](bool derived) {
+    Carve c;
+    at_table = c.take<bgl::BatchProblem>(n);
+    at_items = c.take<int64_t>(size_t(bgl::N_LISTS) * (n + 1));
+    at_work = c.take<unsigned long long>(bgl::N_LISTS);
+    at_counts = c.take<int32_t>(size_t(64) * n);
+    for (int i = 0; i < n; ++i) {
+      const beagle_programs& P = progs[active[i]];
+      const beagle_dataset& d = data[active[i]];
+      const int64_t nt = std::max<int64_t>(P.n_tokens, 1);
+      const int64_t N = P.n_programs;
+      Off& o = off[i];
+      o.derived = derived && use_derived(N) ? 1 : 0;
+      o.code = c.take<uint32_t>(nt);
+      o.aux = c.take<uint32_t>(nt);
+      o.cval = c.take<float>(nt);
+      o.s_stack = c.take<int32_t>(nt);
+      o.s_start = c.take<int32_t>(nt);
+      o.s_need = c.take<int32_t>(nt);
+      o.owner = c.take<int32_t>(nt);
+      o.meta = c.take<bgl::ProgMeta>(N);
+      o.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
+      o.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
+      o.Mp = round_up(d.M, bgl::TILE);
+      o.Xt = c.take<float>(size_t(bgl::stage_rows(d.D, o.derived)) * o.Mp);
+      o.stats = c.take<double>(4);
+      eval_chunks(d.M, N, &o.chunk, &o.n_chunks);
+      o.part = c.take<double>(size_t(n_sums) * o.n_chunks * N);
+    }
+    return c.used + 256;
+  };
+  size_t need = lay_out(true);
+  if (ctx->cap && need > ctx->cap) need = lay_out(false);
+  beagle_status st = reserve(ctx, need);
   if (st != BEAGLE_OK) return st;
   char* ws = ctx->ws;
 
@@ -169,7 +174,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   Batch b;
   std::memset(&b.args, 0, sizeof(b.args));
   b.n = n;
-  for (int v = 0; v < bgl::N_BATCH_LISTS; ++v) b.max_d[v] = b.has[v] = 0;
+  for (int v = 0; v < bgl::N_LISTS; ++v) b.has[v] = 0;
   int32_t* counts = reinterpret_cast<int32_t*>(ws + at_counts);
   for (int i = 0; i < n; ++i) {
     const int q = active[i];
@@ -192,6 +197,8 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     pa.code = reinterpret_cast<uint32_t*>(ws + o.code);
     pa.aux = reinterpret_cast<uint32_t*>(ws + o.aux);
     pa.cval = reinterpret_cast<float*>(ws + o.cval);
+    pa.vrow = reinterpret_cast<uint8_t*>(ws + o.aux);  // (no adjoint words here)
+    pa.derived = o.derived;
     pa.max_words = bgl::MAX_LEN;
     pa.scr_stack = reinterpret_cast<int32_t*>(ws + o.s_stack);
     pa.scr_start = reinterpret_cast<int32_t*>(ws + o.s_start);
@@ -213,7 +220,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     t.X = d.X;
     t.y = d.y;
     t.Xt = reinterpret_cast<float*>(ws + o.Xt);
-    t.yp = reinterpret_cast<float*>(ws + o.yp);
+    t.rows = bgl::stage_rows(d.D, o.derived);
     t.stats = reinterpret_cast<double*>(ws + o.stats);
     t.part = reinterpret_cast<double*>(ws + o.part);
     t.fitness = fitness[q];
@@ -221,19 +228,13 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     t.Mp = o.Mp;
     t.chunk = o.chunk;
     t.n_chunks = o.n_chunks;
-    t.kv = d.D <= bgl::WIDE_TILE_MAX_D ? kv[q] : 1;
+    t.kv = o.chunk % bgl::TILE == 0 ? kv[q] : 1;
     t.prog_begin = b.n_programs;
     t.case_begin = b.n_cases;
     b.n_programs += P.n_programs;
     b.n_cases += o.Mp;
-    // the problem's lists: its class-0 tile variant and classes 1 and 2,
-    // in the bucket of its variable count
-    const int db = bgl::d_bucket(int(d.D));
-    for (int v : {int(t.kv), 2, 3}) {
-      const int vl = v * bgl::N_DBUCKETS + db;
-      b.has[vl] = 1;
-      b.max_d[vl] = std::max(b.max_d[vl], int(d.D));
-    }
+    // the problem's lists: its class-0 tile variant and classes 1 and 2
+    for (int v : {int(t.kv), 2, 3}) b.has[v] = 1;
   }
   if (b.n_programs >= (int64_t(1) << 31)) return fail(BEAGLE_E_UNSUPPORTED, "more than 2^31 programs in a batch");
   bgl::BatchArgs& a = b.args;
@@ -275,7 +276,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     }
     BatchGraph ng;
     ng.key = key;
-    bgl::prime_eval_batch(kind, b.max_d, b.has);
+    bgl::prime_eval_batch(kind);
     e = hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     hipError_t le = enqueue(b, counts, ctx->capture_stream);

@@ -11,8 +11,11 @@
 //
 //     word = handler | (arg << 8) | (wslot << 16) | (i0 << 24)
 //
-// arg is the variable index of VAR words, the constant slot of CONST words
-// (their value also sits in a side table by word position) and 0 otherwise.
+// arg is the input row of VAR words (the variable's index, or the row that
+// holds a base unary operator of a variable where such rows are staged: the
+// pair "VAR, unary operator" is then one word), the constant slot of CONST
+// words (their value also sits in a side table by word position) and 0
+// otherwise.  The rows of the VAR words are also listed in word order.
 //
 // The interpreter keeps the value on top of the stack in `top` and the n-1
 // values below it in stk[0..n-2] (n = stack size before the token).  Every
@@ -323,7 +326,8 @@ struct ProgMeta {
   int32_t need;    // register need of the expression tree (max stack size)
   int32_t len;     // decoded instruction words (fused pairs count once)
   float shift;     // correlation fitness: the program's output at case 0
-  uint32_t vmask;  // bit d set: the program reads input variable d (staged only then)
+  uint32_t vmask;  // bit d set: the program reads input variable d (the adjoint stages only those)
+  int32_t nv;      // VAR words (entries of the program's row list)
 };
 
 }  // namespace bgl

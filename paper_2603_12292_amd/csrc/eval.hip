@@ -1,27 +1,45 @@
 // Population evaluation: the stack interpreter, per-case fitness terms,
 // in-block reductions and the cross-chunk finalize.
 //
-// Work decomposition.  A workgroup of 4 waves evaluates ONE program on one
-// chunk of fitness cases; each wave walks the chunk in tiles of 64 lanes x
-// K cases, so every token of the program is decoded once per tile (a
-// wave-uniform scalar branch on the handler byte) and applied to K cases per
-// lane.  All lanes of a wave run the same program on different cases, the
-// mapping the paper's kernel uses to avoid divergence (section 2.1.2), but
-// with no cap on the number of cases.
+// Work decomposition.  A wave evaluates ONE program on one chunk of fitness
+// cases; it walks the chunk in tiles of 64 lanes x K cases, so every token of
+// the program is decoded once per tile (a wave-uniform scalar branch on the
+// handler byte) and applied to K cases per lane.  All lanes of a wave run the
+// same program on different cases, the mapping the paper's kernel uses to
+// avoid divergence (section 2.1.2), but with no cap on the number of cases.
 //
-// The decoded program stays in two VGPRs per 64 tokens (one word per lane,
+// The decoded program stays in a VGPR per 64 tokens (one word per lane,
 // fetched with v_readlane); constants come from a side table read the same
 // way.  The operand stack lives in registers with compile-time names: the
-// handler byte fixes the stack size at which a token runs.
+// handler byte fixes the stack size at which a token runs.  Input rows stream
+// through a ring of slots in LDS, in the order the program reads them (see
+// RowRing).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cmath>
+#include <mutex>
+#include <type_traits>
 
 #include "beagle_device.h"
 #include "kernels.h"
 #include "trig.h"
 
 namespace bgl {
+
+// The 4-case class-0 variant is held to CLASS0_NARROW_WAVES waves per SIMD.
+#ifndef CLASS0_NARROW_WAVES
+#define CLASS0_NARROW_WAVES 7
+#endif
+#ifndef RESIDENT_WAVES
+#define RESIDENT_WAVES 6
+#endif
+#ifndef CLASS0_WIDE_WAVES
+#define CLASS0_WIDE_WAVES 6
+#endif
+#ifndef BATCH_WIDE_WAVES
+#define BATCH_WIDE_WAVES 5
+#endif
 
 template <uint32_t O>
 __device__ __forceinline__ float binop(float a, float b) {
@@ -48,58 +66,200 @@ __device__ __forceinline__ void binop_tile(const float (&a)[K], const float (&b)
   }
 }
 
-// The wave's input tile in LDS: variable d of case k (k-th of this lane's K
-// cases) lives at  ((d * G + k / 4) * 64 + lane) * 4 + k % 4  floats, G =
-// ceil(K / 4): every 16-byte access of a wave is contiguous across lanes
-// (no bank conflicts).  xl points at lane * 4 floats of the tile.
+// Input rows of one wave, in the order in which its program reads them.  A
+// program reads a row for every VAR word (about ten of ~25 words) and the
+// targets after its last word; those reads are known in advance (the
+// decoder's list of rows), so the wave keeps the next RING of them in flight:
+// each fetch waits for the oldest row, reads its K values per lane from LDS
+// and has the row RING reads further on loaded into the slot just freed,
+// straight from global memory.  Nothing is staged per tile, the LDS of a wave
+// is RING rows whatever the number of variables (a tile of all of them held
+// occupancy down from D = 6 on), and the latency of a load is covered by the
+// words between RING reads.  K = 4: a row of 256 cases, one 16-byte load per
+// lane; K = 8: 512 cases, two.
 template <int K>
-struct XRow {
-  float v[K];
+struct RowRing {
+  static constexpr int LOADS = K / 4;
+  uint32_t at;        // LDS byte address of this lane's 16 bytes of slot 0
+  float* ring;        // the wave's slots
+  const float* tile;  // row 0 of the tile the look-ahead is in (uniform)
+  const float* last;  // ... of the chunk's last tile: the look-ahead stays there
+  uint32_t rows_f;    // floats per tile of the layout: rows x TILE
+  uint32_t half;      // K = 4: floats from a tile's first to its second half
+  const uint8_t* list;
+  int n, i, lane;     // reads per tile, look-ahead position in them
+  int yrow;
+  int stop;           // where the look-ahead position next wraps or needs another block of rows
+  int vt;             // rows of 64 reads, one per lane
+  uint32_t slot;      // byte offset of the slot of the next read
+  static constexpr uint32_t SLOT = K * 256u;  // bytes
+
+  __device__ __forceinline__ int block(int b) const {
+    const int j = b + lane;
+    return j < n - 1 ? int(list[j]) : yrow;
+  }
+  // The same in the middle of a tile (programs of 64 or more VAR words only).
+  // A load whose wait the compiler placed would be waited for on the common
+  // path as well, and with it every load in flight.
+  __device__ __forceinline__ int block_now(int b) const {
+    const int j = b + lane;
+    const uint8_t* at_j = list + (j < n - 1 ? j : 0);
+    int v;
+    asm volatile("global_load_ubyte %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(at_j) : "memory");
+    return j < n - 1 ? v : yrow;
+  }
+  // the look-ahead row into `slot`
+  __device__ __forceinline__ void issue() {
+    const uint32_t row = __builtin_amdgcn_readlane(uint32_t(vt), i & 63);
+    const char* src = (reinterpret_cast<const char*>(tile) + row * uint32_t(TILE * sizeof(float))) + uint32_t(lane) * 16u;
+    char* dst = reinterpret_cast<char*>(ring) + slot;
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+    if constexpr (LOADS == 2) __builtin_amdgcn_global_load_lds(src, dst, 16, 1024, 0);
+    slot = slot + SLOT == RING * SLOT ? 0u : slot + SLOT;
+    if (__builtin_expect(++i == stop, 0)) turn();
+  }
+  __device__ __forceinline__ void turn() {
+    if (i == n) {
+      i = 0;
+      if constexpr (K == 8) {
+        tile = tile == last ? last : tile + rows_f;
+      } else {
+        // the other half of the tile, or the next tile's first
+        tile = tile == last ? last : tile + half;
+        half = rows_f - half;
+      }
+    }
+    if (n > 64) vt = block_now(i);
+    stop = i + 64 < n ? i + 64 : n;
+  }
+  // starts at case `c0` (a multiple of the tile) of the chunk ending at `c1`
+  __device__ __forceinline__ void start(const EvalArgs& a, float* ring_, const uint8_t* list_, int nv, int64_t c0,
+                                        int64_t c1) {
+    lane = int(threadIdx.x & 63u);
+    ring = ring_;
+    at = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)ring_)) + uint32_t(lane) * 16u;
+    rows_f = uint32_t(a.rows) * TILE;
+    list = list_;
+    n = nv + 1;
+    yrow = a.rows - 1;
+    tile = a.Xt + (c0 / TILE) * int64_t(rows_f);
+    const int64_t cl = c1 - 1;
+    last = a.Xt + (cl / TILE) * int64_t(rows_f);
+    half = rows_f;
+    if constexpr (K == 4) {
+      // (tile pointers name half tiles: 256 cases)
+      tile += c0 % TILE;
+      last += cl % TILE / 256 * 256;
+      half = c0 % TILE ? rows_f - 256u : 256u;
+    }
+    i = 0;
+    stop = n < 64 ? n : 64;
+    vt = block(0);
+    slot = 0;
+#pragma unroll
+    for (int r = 0; r < RING; ++r) issue();
+  }
+  // The next read's K values per lane.  The wait leaves only the younger
+  // reads' loads in flight (loads complete in order; other memory operations
+  // among them make it wait longer, never shorter).
+  __device__ __forceinline__ void fetch(float (&x)[K]) {
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    const uint32_t addr = at + slot;
+    if constexpr (K == 8) {
+      v4 p, q;
+      asm volatile(
+          "s_waitcnt vmcnt(%3)\n\t"
+          "ds_read_b128 %0, %2\n\t"
+          "ds_read_b128 %1, %2 offset:1024\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(p), "=&v"(q)
+          : "v"(addr), "n"((RING - 1) * LOADS)
+          : "memory");
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        x[k] = p[k];
+        x[4 + k] = q[k];
+      }
+    } else {
+      v4 p;
+      asm volatile(
+          "s_waitcnt vmcnt(%2)\n\t"
+          "ds_read_b128 %0, %1\n\t"
+          "s_waitcnt lgkmcnt(0)"
+          : "=&v"(p)
+          : "v"(addr), "n"((RING - 1) * LOADS)
+          : "memory");
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = p[k];
+    }
+    issue();
+  }
+  __device__ __forceinline__ void row(uint32_t, float (&x)[K]) { fetch(x); }
+  __device__ __forceinline__ void targets(float (&x)[K]) { fetch(x); }
+  __device__ __forceinline__ void next_tile() {}
 };
 
+// Input rows of a whole case set held in LDS (the resident kernels), in the
+// staged layout.
 template <int K>
-__device__ __forceinline__ XRow<K> load_row(const float* xl, uint32_t d) {
-  constexpr int G = (K + 3) / 4;
-  XRow<K> r;
-  if constexpr (K >= 4) {
+struct TableRows {
+  const float* x;  // this lane's cases of row 0 of the current tile
+  uint32_t rows_f, half;
+  __device__ __forceinline__ void start(const EvalArgs& a, const float* table) {
+    x = table + (threadIdx.x & 63u) * 4u;
+    rows_f = uint32_t(a.rows) * TILE;
+    half = K == 4 ? 256u : 0u;
+  }
+  __device__ __forceinline__ void row(uint32_t r, float (&v)[K]) const {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float4 q = *reinterpret_cast<const float4*>(xl + (d * G + g) * 256);
-      r.v[4 * g + 0] = q.x;
-      r.v[4 * g + 1] = q.y;
-      r.v[4 * g + 2] = q.z;
-      r.v[4 * g + 3] = q.w;
+    for (int g = 0; g < K / 4; ++g) {
+      const float4 q = *reinterpret_cast<const float4*>(x + r * uint32_t(TILE) + g * 256);
+      v[4 * g + 0] = q.x;
+      v[4 * g + 1] = q.y;
+      v[4 * g + 2] = q.z;
+      v[4 * g + 3] = q.w;
     }
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.v[k] = xl[d * 256 + k];
   }
-  return r;
-}
+  __device__ __forceinline__ void targets(float (&v)[K]) const { row(rows_f / TILE - 1, v); }
+  __device__ __forceinline__ void next_tile() {
+    if constexpr (K == 8) {
+      x += rows_f;
+    } else {
+      // the other half of the tile, or the next tile's first
+      x += half;
+      half = rows_f - half;
+    }
+  }
+};
 
-template <int K>
-__device__ __forceinline__ void store_row(float* xl, uint32_t d, const XRow<K>& r) {
-  constexpr int G = (K + 3) / 4;
-  if constexpr (K >= 4) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-      *reinterpret_cast<float4*>(xl + (d * G + g) * 256) =
-          make_float4(r.v[4 * g + 0], r.v[4 * g + 1], r.v[4 * g + 2], r.v[4 * g + 3]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < K; ++k) xl[d * 256 + k] = r.v[k];
-  }
+// Rows read straight from global memory, one case per lane (the values
+// kernel).
+struct DirectRows {
+  const float* x;  // row 0 of the lane's case
+  __device__ __forceinline__ void row(uint32_t r, float (&v)[1]) const { v[0] = x[r * uint32_t(TILE)]; }
+};
+
+// A word and a constant per lane, loaded and waited for in one place: the
+// wait for an ordinary load would be placed where its path joins the common
+// one and hold up every tile.
+__device__ __forceinline__ void load_now(const uint32_t* w, const float* v, uint32_t& word, float& value) {
+  asm volatile(
+      "global_load_dword %0, %2, off\n\t"
+      "global_load_dword %1, %3, off\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(word), "=&v"(value)
+      : "v"(w), "v"(v)
+      : "memory");
 }
 
 // The stack interpreter for one program on K cases per lane.
-//   vc0/vv0, vc1/vv1: instruction words / constant values of tokens 0..63
-//   and 64..127 (one per lane); longer programs read later tokens from
-//   memory.  xl points at this lane's inputs in the wave's LDS tile (see
-//   load_row).
-template <int K, int S>
-__device__ __forceinline__ void interpret(uint32_t vc0, float vv0, uint32_t vc1, float vv1,
-                                          const uint32_t* __restrict__ code, const float* __restrict__ cval,
-                                          int L, int lane, const float* xl, float (&top)[K]) {
+//   vc0/vv0: instruction words / constant values of tokens 0..63 (one per
+//   lane); longer programs read later tokens from memory, 64 at a time.  rows
+//   gives the input rows of VAR words.
+template <int K, int S, class Rows>
+__device__ __forceinline__ void interpret(uint32_t vc0, float vv0, const uint32_t* __restrict__ code,
+                                          const float* __restrict__ cval,
+                                          int L, int lane, Rows& rows, float (&top)[K]) {
   // S slots: the unconditional store of a token at stack size n = S lands in
   // slot S-1, above the S-1 live values
   float stk[K][S];
@@ -110,18 +270,11 @@ __device__ __forceinline__ void interpret(uint32_t vc0, float vv0, uint32_t vc1,
     for (int j = 0; j < S; ++j) stk[k][j] = 0.0f;
   }
   for (int base = 0; base < L; base += 64) {
-    uint32_t vc;
-    float vv;
-    if (base == 0) {
-      vc = vc0;
-      vv = vv0;
-    } else if (base == 64) {
-      vc = vc1;
-      vv = vv1;
-    } else {
-      const int i = base + lane;
-      vc = i < L ? code[i] : 0u;
-      vv = i < L ? cval[i] : 0.0f;
+    uint32_t vc = vc0;
+    float vv = vv0;
+    if (base != 0) {
+      const int i = base + lane < L ? base + lane : L - 1;
+      load_now(code + i, cval + i, vc, vv);
     }
     const int n = __builtin_amdgcn_readfirstlane(L - base < 64 ? L - base : 64);
     for (int t = 0; t < n; ++t) {
@@ -132,9 +285,7 @@ __device__ __forceinline__ void interpret(uint32_t vc0, float vv0, uint32_t vc1,
       for (int k = 0; k < K; ++k) stk[k][ws] = top[k];
       switch (w & 0xFFu) {
         case H_VAR: {
-          const XRow<K> xv = load_row<K>(xl, arg);
-#pragma unroll
-          for (int k = 0; k < K; ++k) top[k] = xv.v[k];
+          rows.row(arg, top);
           break;
         }
         case H_CONST: {
@@ -168,10 +319,10 @@ __device__ __forceinline__ void interpret(uint32_t vc0, float vv0, uint32_t vc1,
 #undef BGL_BIN_ALL
 #define BGL_FUSED(O)                                                           \
   case H_FUSED + O: {                                                          \
-    const XRow<K> xv = load_row<K>(xl, arg);                                   \
-    float t_[K];                                                               \
+    float x_[K], t_[K];                                                        \
+    rows.row(arg, x_);                                                         \
     _Pragma("unroll") for (int k = 0; k < K; ++k) t_[k] = top[k];              \
-    binop_tile<O, K>(t_, xv.v, top);                                           \
+    binop_tile<O, K>(t_, x_, top);                                             \
     break;                                                                     \
   }                                                                            \
   case H_FUSED + 6 + O: {                                                      \
@@ -223,10 +374,10 @@ __device__ __forceinline__ void interpret(uint32_t vc0, float vv0, uint32_t vc1,
 // top; the handler index i0 (word bits 24..31) names the stack size, so each
 // handler reads and rewrites its slots in place and no word moves values
 // between registers.  st[k][j] is stack slot j of case k; the result is slot 0.
-template <int K>
-__device__ __forceinline__ void interpret_small(uint32_t vc0, float vv0, uint32_t vc1, float vv1,
-                                                const uint32_t* __restrict__ code, const float* __restrict__ cval,
-                                                int L, int lane, const float* xl, float (&res)[K]) {
+template <int K, class Rows>
+__device__ __forceinline__ void interpret_small(uint32_t vc0, float vv0, const uint32_t* __restrict__ code,
+                                                const float* __restrict__ cval,
+                                                int L, int lane, Rows& rows, float (&res)[K]) {
   constexpr int S = 4;
   float st[K][S];
 #pragma unroll
@@ -234,18 +385,11 @@ __device__ __forceinline__ void interpret_small(uint32_t vc0, float vv0, uint32_
 #pragma unroll
     for (int j = 0; j < S; ++j) st[k][j] = 0.0f;
   for (int base = 0; base < L; base += 64) {
-    uint32_t vc;
-    float vv;
-    if (base == 0) {
-      vc = vc0;
-      vv = vv0;
-    } else if (base == 64) {
-      vc = vc1;
-      vv = vv1;
-    } else {
-      const int i = base + lane;
-      vc = i < L ? code[i] : 0u;
-      vv = i < L ? cval[i] : 0.0f;
+    uint32_t vc = vc0;
+    float vv = vv0;
+    if (base != 0) {
+      const int i = base + lane < L ? base + lane : L - 1;
+      load_now(code + i, cval + i, vc, vv);
     }
     const int n = __builtin_amdgcn_readfirstlane(L - base < 64 ? L - base : 64);
     for (int t = 0; t < n; ++t) {
@@ -254,8 +398,9 @@ __device__ __forceinline__ void interpret_small(uint32_t vc0, float vv0, uint32_
       switch (w >> 24) {
 #define BGL_S_PUSH(N)                                                           \
   case I0_PUSH_VAR + N: {                                                       \
-    const XRow<K> xv = load_row<K>(xl, arg);                                    \
-    _Pragma("unroll") for (int k = 0; k < K; ++k) st[k][N] = xv.v[k];           \
+    float x_[K];                                                                \
+    rows.row(arg, x_);                                                          \
+    _Pragma("unroll") for (int k = 0; k < K; ++k) st[k][N] = x_[k];             \
     break;                                                                      \
   }                                                                             \
   case I0_PUSH_CONST + N: {                                                     \
@@ -320,10 +465,10 @@ __device__ __forceinline__ void interpret_small(uint32_t vc0, float vv0, uint32_
 #undef BGL_S_UN
 #define BGL_S_FUSED(O, N)                                                       \
   case I0_FUSED + 3 * O + (N - 1): {                                            \
-    const XRow<K> xv = load_row<K>(xl, arg);                                    \
-    float a_[K], r_[K];                                                         \
+    float x_[K], a_[K], r_[K];                                                  \
+    rows.row(arg, x_);                                                          \
     _Pragma("unroll") for (int k = 0; k < K; ++k) a_[k] = st[k][N - 1];         \
-    binop_tile<O, K>(a_, xv.v, r_);                                             \
+    binop_tile<O, K>(a_, x_, r_);                                               \
     _Pragma("unroll") for (int k = 0; k < K; ++k) st[k][N - 1] = r_[k];         \
     break;                                                                      \
   }                                                                             \
@@ -422,7 +567,7 @@ struct Acc {
   }
 };
 
-// One workgroup: program p on case chunk c.  Writes the chunk's partial sums
+// One wave: program p on case chunk c.  Writes the chunk's partial sums
 //   MSE  : part[0][c][p] = sum (yhat - y)^2
 //   CORR : part[j][c][p] = sum u, sum u^2, sum u*w   (u = yhat - shift_p,
 //          w = y - ybar), all in binary64
@@ -430,216 +575,58 @@ struct Acc {
 //   R4   : part[j][c][p] = c1, c2 (cases with one / two invalid values), and
 //          over the cases where both are valid sum u, sum u^2, sum u*w,
 //          sum w, sum w^2.
-template <int KIND, int K, int S>
-__device__ __forceinline__ void eval_block(const EvalArgs& a, int p, int c, float* xtile) {
-  const ProgMeta m = a.meta[p];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t off = a.tok_offset[p];
-  const uint32_t* code = a.code + off;
-  const float* cval = a.cval + off;
-  const int L = m.len;
-  const uint32_t vc0 = lane < L ? code[lane] : 0u;
-  const float vv0 = lane < L ? cval[lane] : 0.0f;
-  const uint32_t vc1 = lane + 64 < L ? code[lane + 64] : 0u;
-  const float vv1 = lane + 64 < L ? cval[lane + 64] : 0.0f;
-  const double shift = double(m.shift);
-  const uint32_t vmask = uint32_t(__builtin_amdgcn_readfirstlane(int(m.vmask)));
-  const double ybar = KIND == BEAGLE_FIT_CORR || KIND == BEAGLE_FIT_R4 ? a.stats[0] : 0.0;
-  const double smax = a.smax, s11 = a.smax / 11.0;
-  Acc<KIND> acc;
-  const int64_t c0 = int64_t(c) * a.chunk;
-  const int64_t c1 = c0 + a.chunk < a.M ? c0 + a.chunk : a.M;
-  // this wave's input tile (layout: load_row); G * 256 floats per variable
-  constexpr int G = (K + 3) / 4;
-  float* xw = xtile + wave * (a.D * G * 256);
-  float* xl = xw + lane * 4;
-  // Case order.  A sub-tile is 64 lanes x min(K, 4) cases; the block's
-  // waves take consecutive sub-tiles, and a lane with K = 8 holds two
-  // sub-tiles EVAL_WAVES sub-tiles apart.  Lane l holds cases 4l .. 4l+3 of a
-  // sub-tile (K >= 4; k * 64 + l for K = 2).  So each lane adds exactly the
-  // cases it would add with K = 4, in the same order: the tile width of
-  // class 0 changes no result bit.
-  constexpr int SUB = K < 4 ? K : 4;
-  constexpr int SPAN = EVAL_WAVES * 64 * SUB;  // cases of one sub-tile row of the block
-  constexpr int NSUB = K / SUB;
-  for (int64_t base = c0 + int64_t(wave) * (64 * SUB); base < c1; base += int64_t(NSUB) * SPAN) {
-    float yk[K];
-    if constexpr (K >= 4) {
-      // the tile's inputs go straight from global memory to LDS (16 bytes =
-      // 4 cases per lane, the layout load_row reads); every variable's loads
-      // are issued before one wait
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the last tile's LDS reads are done
-      for (int d = 0; d < a.D; ++d) {
-        if (!((vmask >> d) & 1u)) continue;  // a variable the program never reads
-#pragma unroll
-        for (int g = 0; g < NSUB; ++g)
-          __builtin_amdgcn_global_load_lds(a.Xt + int64_t(d) * a.Mp + base + g * SPAN + 4 * lane,
-                                           xw + (d * NSUB + g) * 256, 16, 0, 0);
-      }
-#pragma unroll
-      for (int g = 0; g < NSUB; ++g) {
-        const float4 q = *reinterpret_cast<const float4*>(a.yp + base + g * SPAN + 4 * lane);
-        yk[4 * g + 0] = q.x;
-        yk[4 * g + 1] = q.y;
-        yk[4 * g + 2] = q.z;
-        yk[4 * g + 3] = q.w;
-      }
-      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the tile is in LDS
-      __builtin_amdgcn_wave_barrier();
-    } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k) yk[k] = a.yp[base + k * 64 + lane];
-      // coalesced global reads, one LDS write per variable; the wave's tile
-      // is private to it, so a wave barrier suffices
-      for (int d = 0; d < a.D; ++d) {
-        if (!((vmask >> d) & 1u)) continue;
-        XRow<K> xv;
-#pragma unroll
-        for (int k = 0; k < K; ++k) xv.v[k] = a.Xt[int64_t(d) * a.Mp + base + k * 64 + lane];
-        __builtin_amdgcn_wave_barrier();
-        store_row<K>(xl, d, xv);
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the tile is in LDS
-    }
-    float top[K];
-    if constexpr (S == 4)
-      interpret_small<K>(vc0, vv0, vc1, vv1, code, cval, L, lane, xl, top);
-    else
-      interpret<K, S>(vc0, vv0, vc1, vv1, code, cval, L, lane, xl, top);
-    // a tile wholly inside the case set (every tile but the last) adds
-    // without per-case validity masks
-    if (base + int64_t(NSUB - 1) * SPAN + 64 * SUB <= a.M) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) acc.add(top[k], yk[k], true, shift, ybar, smax, s11);
-    } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const bool valid = base + (k / SUB) * SPAN + (K >= 4 ? 4 * lane + (k % 4) : k * 64 + lane) < a.M;
-        acc.add(top[k], yk[k], valid, shift, ybar, smax, s11);
-      }
-    }
-  }
-  // the waves' sums meet in the start of each wave's own tile (its tiles
-  // are done; no LDS beyond the tiles, so that eight workgroups of four
-  // waves fit a CU at D = 5)
-  constexpr int NS = kind_sums(KIND);
-  const int wstride = a.D * G * 256;  // floats per wave tile
-  double v[MAX_SUMS];
-  acc.wave_sums(v);
-  if (lane == 0) {
-    double* mine = reinterpret_cast<double*>(xw);
-#pragma unroll
-    for (int j = 0; j < NS; ++j) mine[j] = v[j];
-  }
-  __syncthreads();
-  if (threadIdx.x < NS) {
-    const int j = threadIdx.x;
-    auto red = [&](int w) { return reinterpret_cast<const double*>(xtile + w * wstride)[j]; };
-    const double t = ((red(0) + red(1)) + red(2)) + red(3);
-    a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p] = t;
-  }
-  __syncthreads();
-}
-
-// One register-need class: a persistent grid pulls (chunk, program) work
-// items from an atomic counter, chunk-major so that the workgroups running
-// at any moment share one chunk of cases in L2.  Which workgroup takes which
-// item does not change any result: each item writes its own partial.
-// The 4-case class-0 variant is held to CLASS0_NARROW_WAVES waves per SIMD
-// (7: 72 VGPRs instead of its natural 85, five waves; eight would not fit
-// the LDS of seven workgroups' input tiles at D = 5 anyway); the values this
-// moves to scratch are per-item and per-tile bookkeeping, none inside the
-// per-token loop.
-#ifndef CLASS0_NARROW_WAVES
-#define CLASS0_NARROW_WAVES 7
-#endif
-template <int KIND, int CLS, int KV>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 && KV == 1 ? CLASS0_NARROW_WAVES : 1)))
-k_eval_class(EvalArgs a) {
-  constexpr int S = class_stack(CLS);
-  constexpr int K = class_k(CLS, KV);
-  extern __shared__ float xtile[];
-  // the claimed item passes through the tiles' LDS (no tile is in use
-  // between items)
-  long long* s_item = reinterpret_cast<long long*>(xtile);
-  const int32_t count = a.class_count[CLS];
-  const int64_t items = int64_t(count) * a.n_chunks;
-  const int32_t* list = a.class_list + int64_t(CLS) * a.n_total;
-  // workgroups beyond the item count leave at once: on a short (or empty)
-  // list, one same-address atomic per workgroup of the persistent grid
-  // would serialise at the counter for longer than the work takes
-  if (int64_t(blockIdx.x) >= items) return;
-  for (;;) {
-    if (threadIdx.x == 0) *s_item = (long long)atomicAdd(a.work + CLS, 1ull);
-    __syncthreads();
-    const int64_t it = *s_item;
-    __syncthreads();
-    if (it >= items) break;  // uniform across the workgroup
-    const int c = int(it / count);
-    const int p = list[it % count] - a.prog_begin;
-    if (p < 0 || p >= a.n_programs) continue;  // a program of another slice
-    eval_block<KIND, K, S>(a, p, c, xtile);
-  }
-}
-
-// Small case sets (one chunk of at most RESIDENT_MAX_BYTES of inputs): every
-// workgroup copies the whole input set into LDS once, laid out per pass of
-// 64 K cases as the block kernel lays out a tile ([pass][variable][64 K]),
-// and each wave then takes whole programs of register-need class 0 from the
-// list and runs every pass, so that nothing is staged per program, no case
-// is padding beyond the last pass and no workgroup barrier is taken per
-// program.  A lane adds its cases in the order it would with either tile
-// width, so the width changes no result bit here either.
-template <int KIND, int K, int CLS>
-__device__ __forceinline__ void eval_wave_resident(const EvalArgs& a, int p, const float* xres, int passes) {
-  constexpr int K64 = K * 64;
+// Case order: lane l holds cases 4l .. 4l+3 of every 256 (a tile with K = 8
+// is two such runs), and adds its cases in increasing order, so the tile
+// width changes no result bit.
+// RESIDENT: `lds` is the table of the whole case set (one chunk), else the
+// wave's ring.
+template <int KIND, int K, int S, bool RESIDENT>
+__device__ __forceinline__ void eval_wave(const EvalArgs& a, int p, int c, float* lds) {
   const ProgMeta m = a.meta[p];
   const int lane = threadIdx.x & 63;
   const int64_t off = a.tok_offset[p];
   const uint32_t* code = a.code + off;
   const float* cval = a.cval + off;
-  const int L = m.len;
+  const int L = __builtin_amdgcn_readfirstlane(m.len);
+  const int64_t c0 = int64_t(c) * a.chunk;
+  const int64_t c1 = c0 + a.chunk < a.M ? c0 + a.chunk : a.M;
+  std::conditional_t<RESIDENT, TableRows<K>, RowRing<K>> rows;
+  if constexpr (RESIDENT)
+    rows.start(a, lds);
+  else
+    rows.start(a, lds, a.vrow + off, __builtin_amdgcn_readfirstlane(m.nv), c0, c1);
   const uint32_t vc0 = lane < L ? code[lane] : 0u;
   const float vv0 = lane < L ? cval[lane] : 0.0f;
-  const uint32_t vc1 = lane + 64 < L ? code[lane + 64] : 0u;
-  const float vv1 = lane + 64 < L ? cval[lane + 64] : 0.0f;
   constexpr bool SHIFTED = KIND == BEAGLE_FIT_CORR || KIND == BEAGLE_FIT_R4;
   double shift = double(m.shift);
   const double ybar = SHIFTED ? a.stats[0] : 0.0;
   const double smax = a.smax, s11 = a.smax / 11.0;
   Acc<KIND> acc;
-  for (int ps = 0; ps < passes; ++ps) {
-    const int64_t base = int64_t(ps) * K64;
-    float yk[K];
-#pragma unroll
-    for (int g = 0; g < K / 4; ++g) {
-      const float4 q = *reinterpret_cast<const float4*>(a.yp + base + g * 256 + 4 * lane);
-      yk[4 * g + 0] = q.x;
-      yk[4 * g + 1] = q.y;
-      yk[4 * g + 2] = q.z;
-      yk[4 * g + 3] = q.w;
-    }
-    float top[K];
-    if constexpr (CLS == 0)
-      interpret_small<K>(vc0, vv0, vc1, vv1, code, cval, L, lane, xres + ps * (a.D * K64) + 4 * lane, top);
+  for (int64_t base = c0; base < c1; base += 64 * K) {
+    float top[K], yk[K];
+    if constexpr (S == 4)
+      interpret_small<K>(vc0, vv0, code, cval, L, lane, rows, top);
     else
-      interpret<K, class_stack(CLS)>(vc0, vv0, vc1, vv1, code, cval, L, lane, xres + ps * (a.D * K64) + 4 * lane, top);
-    if (SHIFTED && ps == 0 && a.meta_shift) {
-      // the shift is the output at case 0 (lane 0, first case) when finite:
-      // the value the shift pass computes, from the same arithmetic
+      interpret<K, S>(vc0, vv0, code, cval, L, lane, rows, top);
+    rows.targets(yk);
+    rows.next_tile();
+    if (SHIFTED && a.meta_shift && base == c0) {
+      // (one chunk) the shift is the output at case 0 (lane 0, first case)
+      // when finite
       const float y0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(top[0]), 0));
       const float sh = isfinite(y0) ? y0 : 0.0f;
       if (lane == 0) a.meta_shift[p].shift = sh;
       shift = double(sh);
     }
-    if (base + K64 <= a.M) {
+    // a tile wholly inside the chunk (every tile but the last) adds without
+    // per-case validity masks
+    if (base + 64 * K <= c1) {
 #pragma unroll
       for (int k = 0; k < K; ++k) acc.add(top[k], yk[k], true, shift, ybar, smax, s11);
     } else {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const bool valid = base + (k / 4) * 256 + 4 * lane + (k % 4) < a.M;
+        const bool valid = base + (k / 4) * 256 + 4 * lane + (k % 4) < c1;
         acc.add(top[k], yk[k], valid, shift, ybar, smax, s11);
       }
     }
@@ -648,94 +635,140 @@ __device__ __forceinline__ void eval_wave_resident(const EvalArgs& a, int p, con
   acc.wave_sums(v);
   if (lane == 0) {
 #pragma unroll
-    for (int j = 0; j < kind_sums(KIND); ++j) a.part[int64_t(j) * a.n_programs + p] = v[j];
+    for (int j = 0; j < kind_sums(KIND); ++j) a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p] = v[j];
   }
+  // the look-ahead's last loads land before another item's are issued
+  if constexpr (!RESIDENT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 }
 
-template <int KIND, int K, int CLS>
-__global__ void __launch_bounds__(256) k_eval_resident(EvalArgs a) {
-  constexpr int K64 = K * 64;
-  extern __shared__ float xres[];
-  // A list of at most four programs per wave is walked statically (wave w
-  // takes programs w, w + W, ...: no atomics); a longer one through the
-  // shared counter, RESIDENT_BATCH programs per claim.  Workgroups whose
-  // waves would find nothing leave before staging the inputs.
-  const int32_t n_list = a.class_count[CLS];
-  const int32_t n_waves = int32_t(gridDim.x) * 4;
-  if (int64_t(blockIdx.x) * 4 >= n_list) return;
-  const int passes = int((a.M + K64 - 1) / K64);
-  const int per_pass = a.D * K64;
-  for (int i = threadIdx.x; i < passes * per_pass; i += blockDim.x) {
-    const int ps = i / per_pass, r = i - ps * per_pass, d = r / K64, j = r - d * K64;
-    xres[i] = a.Xt[int64_t(d) * a.Mp + int64_t(ps) * K64 + j];
+// Work items [0, items) of a persistent grid's waves.  A short list (at most
+// four items per wave) is walked statically (wave w takes items w, w + W, ...:
+// no atomics); a longer one through a shared counter, in claims that shrink
+// towards the list's end: long claims at the end leave waves idle, but
+// same-address atomics serialise at the counter (~10 ns each), so that items
+// of one tile are never claimed one by one (2^20 of them: 3.9 ms with single
+// claims over the last 4 %, 2.6 ms with eight).
+// The loop around next() must stay free of divergent branches: a lane-0-only
+// branch around the atomic lets the compiler restructure it so that after
+// the first item only lane 0 goes back to the atomic.  So every lane takes
+// part in the atomic (lane 0 adds the claim, the others 0) and the result is
+// read from lane 0 explicitly.
+__device__ __forceinline__ int64_t claim_least(int64_t cases) { return cases >= 8 * TILE ? 1 : cases >= 4 * TILE ? 2 : cases >= 2 * TILE ? 4 : 8; }
+struct WaveItems {
+  int64_t item, end, items, step;
+  int64_t waves;
+  unsigned long long* work;
+  int64_t least;  // items of one claim at least
+  bool claimed;
+  __device__ __forceinline__ WaveItems(int64_t items_, unsigned long long* work_, int64_t least_)
+      : items(items_), work(work_), least(least_) {
+    const int per = int(blockDim.x >> 6);
+    waves = int64_t(gridDim.x) * per;
+    claimed = items > 4 * waves;
+    const int64_t id = __builtin_amdgcn_readfirstlane(int(blockIdx.x) * per + int(threadIdx.x >> 6));
+    item = claimed ? 0 : id;
+    end = claimed ? 0 : items;
+    step = claimed ? 1 : waves;
   }
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  // The wave's loop must stay free of divergent branches: a lane-0-only
-  // branch around the atomic lets the compiler restructure the loop so that
-  // after the first program only lane 0 goes back to the atomic while the
-  // other lanes re-run the old item forever.  So every lane takes part in
-  // the atomic (lane 0 adds 1, the others 0: one atomic after the wave
-  // reduction), the item is read from lane 0 explicitly, the count is a
-  // scalar and no early continue splits the body.
-  // Each atomic claims RESIDENT_BATCH consecutive programs (one
-  // same-address atomic per program would serialise at the counter).
-  const int32_t count = __builtin_amdgcn_readfirstlane(a.class_count[CLS]);
-  const int32_t* list = a.class_list + int64_t(CLS) * a.n_total;
-  // Both walks in one loop around one call of the per-program routine (two
-  // inlined copies of the interpreter would not fit the instruction cache
-  // together): the static walk steps by the wave count from the wave's
-  // index; the claimed walk steps by one through each claimed batch and
-  // claims the next one at its end.  Every value deciding a branch is
-  // wave-uniform, so the atomic runs on all lanes.
-  const bool claimed = count > 4 * n_waves;
-  const int32_t wave_id = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x) * 4 + int32_t(threadIdx.x >> 6));
-  int64_t item = claimed ? 0 : wave_id;
-  int64_t end = claimed ? 0 : count;  // the walk's current range [item, end)
-  const int64_t step = claimed ? 1 : n_waves;
-  for (;;) {
+  // the next item, or -1
+  __device__ __forceinline__ int64_t next() {
     if (item >= end) {
-      if (!claimed) break;
-      const unsigned long long it = atomicAdd(a.work + CLS, lane == 0 ? (unsigned long long)RESIDENT_BATCH : 0ull);
+      if (!claimed) return -1;
+      // (`end` is where this wave's last claim stood: a lower bound of the
+      // counter, so the claim is at most 1/8 of a wave's share of the rest)
+      const int64_t left = (items - end) / (8 * waves);
+      const int64_t n = left > CLAIM_MAX ? CLAIM_MAX : left < least ? least : left;
+      const unsigned long long it = atomicAdd(work, (threadIdx.x & 63u) == 0 ? (unsigned long long)n : 0ull);
       const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(it), 0);
       const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(it >> 32), 0);
       const int64_t first = int64_t((uint64_t(hi) << 32) | lo);
-      if (first >= count) break;
+      if (first >= items) return -1;
       item = first;
-      end = first + RESIDENT_BATCH < count ? first + RESIDENT_BATCH : count;
+      end = first + n < items ? first + n : items;
     }
-    const int p = __builtin_amdgcn_readfirstlane(list[item] - a.prog_begin);
-    if (p >= 0 && p < a.n_programs) eval_wave_resident<KIND, K, CLS>(a, p, xres, passes);  // else another slice's
+    const int64_t r = item;
     item += step;
+    return r;
+  }
+};
+
+// One register-need class: a persistent grid's waves take (chunk, program)
+// work items, chunk-major so that the waves running at any moment share one
+// chunk of cases in L2.  Which wave takes which item does not change any
+// result: each item writes its own partial.
+template <int KIND, int CLS, int KV>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : CLASS0_WIDE_WAVES) : CLS == 1 ? 4 : 2)))
+k_eval_class(EvalArgs a) {
+  constexpr int S = class_stack(CLS);
+  constexpr int K = class_k(CLS, KV);
+  __shared__ __align__(16) float rings[EVAL_WAVES][RING * K * 64];
+  const int32_t count = __builtin_amdgcn_readfirstlane(a.class_count[CLS]);
+  const int64_t items = int64_t(count) * a.n_chunks;
+  const int32_t* list = a.class_list + int64_t(CLS) * a.n_total;
+  // workgroups beyond the items leave at once
+  if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;
+  float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
+  WaveItems work(items, a.work + CLS, claim_least(a.chunk));
+  for (;;) {
+    const int64_t it = work.next();
+    if (it < 0) break;
+    const int c = a.n_chunks == 1 ? 0 : int(it / count);
+    const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count] - a.prog_begin);
+    // (else a program of another slice)
+    if (p >= 0 && p < a.n_programs) eval_wave<KIND, K, S, false>(a, p, c, ring);
   }
 }
 
-// One work list of a batched evaluation (list vl: a work list of the
-// class and tile variant, for one bucket of variable counts): the same
-// persistent scheme over the (problem, chunk, program) items of the table's
-// problems in that list, problem by problem in table order and chunk-major
-// within a problem.  Items are claimed in increasing order, so a
-// workgroup's next item lies in its previous item's problem or a later one:
-// the problem is found by stepping forward from there when it is near, by
+// Small case sets (one chunk whose staged rows fit a compute unit's LDS):
+// every workgroup copies all of them once, and each wave then takes whole
+// programs, reading rows where it needs them: no look-ahead, no list of rows,
+// and a program's start (a few thousand cycles behind the ring's first loads
+// where a program has one tile) costs only its header.  The waves of a
+// workgroup are as many as let the workgroups that fit fill the SIMDs (see
+// resident_shape).
+template <int KIND, int K, int CLS>
+__global__ void __attribute__((amdgpu_flat_work_group_size(64, 1024), amdgpu_waves_per_eu(CLS == 0 ? RESIDENT_WAVES : 4)))
+k_eval_resident(EvalArgs a) {
+  extern __shared__ __align__(16) float table[];
+  const int32_t count = __builtin_amdgcn_readfirstlane(a.class_count[CLS]);
+  const int32_t* list = a.class_list + int64_t(CLS) * a.n_total;
+  // workgroups whose waves would find nothing leave before copying
+  if (int64_t(blockIdx.x) * int(blockDim.x >> 6) >= count) return;
+  const int n4 = int((a.M + TILE - 1) / TILE) * a.rows * (TILE / 4);
+  for (int i = threadIdx.x; i < n4; i += blockDim.x)
+    reinterpret_cast<float4*>(table)[i] = reinterpret_cast<const float4*>(a.Xt)[i];
+  __syncthreads();
+  WaveItems work(count, a.work + CLS, claim_least(a.M));
+  for (;;) {
+    const int64_t it = work.next();
+    if (it < 0) break;
+    const int p = __builtin_amdgcn_readfirstlane(list[it] - a.prog_begin);
+    if (p >= 0 && p < a.n_programs) eval_wave<KIND, K, class_stack(CLS), true>(a, p, 0, table);  // else another slice's
+  }
+}
+
+// One work list of a batched evaluation (a class and tile variant): the
+// same persistent scheme over the (problem, chunk, program) items of the
+// table's problems in that list, problem by problem in table order and
+// chunk-major within a problem.  Items are claimed in increasing order, so a
+// wave's next item lies in its previous item's problem or a later one: the
+// problem is found by stepping forward from there when it is near, by
 // bisection otherwise.
 template <int KIND, int CLS, int KV>
-__global__ void __launch_bounds__(256) k_eval_batch(BatchArgs b, int vl) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : BATCH_WIDE_WAVES) : CLS == 1 ? 4 : 2)))
+k_eval_batch(BatchArgs b, int vl) {
   constexpr int S = class_stack(CLS);
   constexpr int K = class_k(CLS, KV);
-  extern __shared__ float xtile[];
-  long long* s_item = reinterpret_cast<long long*>(xtile);  // (as in k_eval_class)
+  __shared__ __align__(16) float rings[EVAL_WAVES][RING * K * 64];
   const int64_t* off = b.item_off + int64_t(vl) * (b.n_problems + 1);
   const int64_t items = off[b.n_problems];
-  if (int64_t(blockIdx.x) >= items) return;  // (as in k_eval_class)
+  if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;  // (as in k_eval_class)
+  float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
+  WaveItems work(items, b.work + vl, 2);
   int lo = 0;  // the problem of the previous item (a lower bound for the next)
   for (;;) {
-    if (threadIdx.x == 0) *s_item = (long long)atomicAdd(b.work + vl, 1ull);
-    __syncthreads();
-    const uint64_t raw = uint64_t(*s_item);
-    __syncthreads();
-    const int64_t it = int64_t((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(raw >> 32)))) << 32) |
-                               uint32_t(__builtin_amdgcn_readfirstlane(int(raw))));
-    if (it >= items) break;  // uniform across the workgroup
+    const int64_t it = work.next();
+    if (it < 0) break;
     // the last problem q >= lo with off[q] <= it (problems without items in
     // this list have empty ranges and are stepped over)
     int steps = 0;
@@ -757,17 +790,16 @@ __global__ void __launch_bounds__(256) k_eval_batch(BatchArgs b, int vl) {
     const int32_t count = P.prep.class_count[CLS];
     const int64_t local = it - off[lo];
     const int c = int(local / count);
-    const int p = P.prep.class_list[int64_t(CLS) * P.prep.n_programs + local % count];
+    const int p = __builtin_amdgcn_readfirstlane(P.prep.class_list[int64_t(CLS) * P.prep.n_programs + local % count]);
     EvalArgs a;
     a.code = P.prep.code;
     a.cval = P.prep.cval;
+    a.vrow = P.prep.vrow;
     a.tok_offset = P.prep.tok_offset;
     a.meta = P.prep.meta;
     a.Xt = P.Xt;
-    a.yp = P.yp;
+    a.rows = P.rows;
     a.M = P.M;
-    a.Mp = P.Mp;
-    a.D = P.prep.D;
     a.n_programs = P.prep.n_programs;
     a.n_chunks = P.n_chunks;
     a.chunk = P.chunk;
@@ -778,14 +810,15 @@ __global__ void __launch_bounds__(256) k_eval_batch(BatchArgs b, int vl) {
     a.work = nullptr;
     a.n_total = P.prep.n_programs;
     a.prog_begin = 0;
-    eval_block<KIND, K, S>(a, p, c, xtile);
+    a.meta_shift = P.n_chunks == 1 ? P.prep.meta : nullptr;
+    eval_wave<KIND, K, S, false>(a, p, c, ring);
   }
 }
 
 // Per-case outputs of every program on cases [0, m): one wave per
 // (program, 64 cases).  In shift mode (m = 1) it stores the output at case
 // 0 as the program's shift for correlation sums.
-__device__ static void values_program(const ValuesArgs& a, int p, int64_t tile, float* xl_all) {
+__device__ static void values_program(const ValuesArgs& a, int p, int64_t tile) {
   const int lane = threadIdx.x;
   const int64_t i = tile * 64 + lane;
   const ProgMeta m = a.meta[p];
@@ -799,15 +832,10 @@ __device__ static void values_program(const ValuesArgs& a, int p, int64_t tile, 
   const int L = m.len;
   const uint32_t vc0 = lane < L ? code[lane] : 0u;
   const float vv0 = lane < L ? cval[lane] : 0.0f;
-  const uint32_t vc1 = lane + 64 < L ? code[lane + 64] : 0u;
-  const float vv1 = lane + 64 < L ? cval[lane + 64] : 0.0f;
   const int64_t ii = i < a.m ? i : 0;
-  float* xl = xl_all + lane * 4;
-  for (int d = 0; d < a.D; ++d) xl[d * 256] = a.Xt[int64_t(d) * a.Mp + ii];
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_s_waitcnt(0xc07f);
+  DirectRows rows{a.Xt + case_offset(ii, a.rows)};
   float top[1];
-  interpret<1, MAX_STACK>(vc0, vv0, vc1, vv1, code, cval, L, lane, xl, top);
+  interpret<1, MAX_STACK>(vc0, vv0, code, cval, L, lane, rows, top);
   if (a.shift_mode) {
     // a finite shift (a non-finite output at case 0 is either the whole
     // fitness, NaN, or an invalid pair of the paper's scores)
@@ -817,44 +845,27 @@ __device__ static void values_program(const ValuesArgs& a, int p, int64_t tile, 
   }
 }
 
-// (dynamic LDS: D * 256 floats, so that more waves fit per CU for small D)
-__global__ void __launch_bounds__(64) k_values(ValuesArgs a) {
-  extern __shared__ float xl_all[];
-  values_program(a, blockIdx.x, blockIdx.y, xl_all);
-}
+__global__ void __launch_bounds__(64) k_values(ValuesArgs a) { values_program(a, blockIdx.x, blockIdx.y); }
 
-// Correlation shifts of the class-2 programs only (the resident-inputs
-// kernels compute those of classes 0 and 1): a fixed grid striding over the
-// list, no counters.
-__global__ void __launch_bounds__(64) k_values_deep(ValuesArgs a, const int32_t* class_count,
-                                                    const int32_t* class_list, int32_t stride) {
-  extern __shared__ float xl_all[];  // D * 256 floats
-  const int32_t c2 = class_count[2];
-  for (int32_t item = blockIdx.x; item < c2; item += gridDim.x) {
-    values_program(a, class_list[2 * int64_t(stride) + item], 0, xl_all);
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// Correlation shifts of every program of the table (one wave per program).
+// Correlation shifts of every program of the table's problems of more than
+// one chunk (one wave per program; the evaluator finds the others').
 __global__ void __launch_bounds__(64) k_values_batch(BatchArgs b) {
-  __shared__ float xl_all[MAX_D * 256];
   const int64_t g = blockIdx.x;
   const int q = batch_find(b, g, [](const BatchProblem& t) { return t.prog_begin; });
   const BatchProblem& P = b.table[q];
+  if (P.n_chunks == 1) return;
   ValuesArgs a;
   a.code = P.prep.code;
   a.cval = P.prep.cval;
   a.tok_offset = P.prep.tok_offset;
   a.meta = P.prep.meta;
   a.Xt = P.Xt;
-  a.Mp = P.Mp;
+  a.rows = P.rows;
   a.m = 1;
-  a.D = P.prep.D;
   a.n_programs = P.prep.n_programs;
   a.out = nullptr;
   a.shift_mode = 1;
-  values_program(a, int(g - P.prog_begin), 0, xl_all);
+  values_program(a, int(g - P.prog_begin), 0);
 }
 
 // Fitness of every program from its chunk partials, summed in chunk order.
@@ -956,16 +967,15 @@ __global__ void k_finalize_batch(BatchArgs b) {
 // First work item of every problem in each work list (exclusive prefix sums
 // in table order), from the class counts that k_prepare_batch produced.
 __global__ void k_batch_items(BatchArgs b) {
-  const int vl = threadIdx.x;  // list v, bucket db
-  if (vl >= N_BATCH_LISTS) return;
-  const int v = vl / N_DBUCKETS, db = vl % N_DBUCKETS;
+  const int v = threadIdx.x;
+  if (v >= N_LISTS) return;
   const int cls = v == 0 ? 0 : v - 1;
-  int64_t* off = b.item_off + int64_t(vl) * (b.n_problems + 1);
+  int64_t* off = b.item_off + int64_t(v) * (b.n_problems + 1);
   int64_t acc = 0;
   for (int q = 0; q < b.n_problems; ++q) {
     off[q] = acc;
     const BatchProblem& P = b.table[q];
-    if ((v >= 2 || P.kv == v) && d_bucket(P.prep.D) == db) acc += int64_t(P.prep.class_count[cls]) * P.n_chunks;
+    if (v >= 2 || P.kv == v) acc += int64_t(P.prep.class_count[cls]) * P.n_chunks;
   }
   off[b.n_problems] = acc;
 }
@@ -973,22 +983,6 @@ __global__ void k_batch_items(BatchArgs b) {
 __global__ void k_zero_u64(unsigned long long* p, int n) {
   const int i = threadIdx.x;
   if (i < n) p[i] = 0ull;
-}
-
-// resident workgroups per CU of a class kernel at a given LDS size
-template <int KIND, int CLS, int KV>
-static int resident_blocks(size_t lds) {
-  static size_t cached_lds = size_t(-1);
-  static int cached = 0;
-  if (lds != cached_lds) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_eval_class<KIND, CLS, KV>, 256, lds) != hipSuccess ||
-        nb < 1)
-      nb = 1;
-    cached = nb;
-    cached_lds = lds;
-  }
-  return cached;
 }
 
 static int cu_count() {
@@ -1001,54 +995,66 @@ static int cu_count() {
   return n;
 }
 
+// Persistent grid of a class kernel: resident workgroups per CU, times the CUs.
+template <int KIND, int CLS, int KV>
+static int class_grid() {
+  static int cached = 0;
+  if (!cached) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_eval_class<KIND, CLS, KV>, 256, 0) != hipSuccess || nb < 1)
+      nb = 1;
+    cached = nb * cu_count();
+  }
+  return cached;
+}
+
 template <int KIND, int CLS, int KV>
 static hipError_t launch_class(const EvalArgs& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-  const size_t lds = size_t(EVAL_WAVES) * a.D * ((class_k(CLS, KV) + 3) / 4) * 256 * sizeof(float);
-  const int grid = resident_blocks<KIND, CLS, KV>(lds) * cu_count();
+  // (never more waves than programs x chunks)
+  const int64_t most = (int64_t(a.n_total) * a.n_chunks + EVAL_WAVES - 1) / EVAL_WAVES;
+  const int grid = int(std::min<int64_t>(class_grid<KIND, CLS, KV>(), std::max<int64_t>(most, 1)));
   // timing events, when asked for, are taken by the dispatch itself
   if (ev0 || ev1)
-    hipExtLaunchKernelGGL((k_eval_class<KIND, CLS, KV>), dim3(grid), dim3(256), uint32_t(lds), s, ev0, ev1, 0u, a);
+    hipExtLaunchKernelGGL((k_eval_class<KIND, CLS, KV>), dim3(grid), dim3(256), 0, s, ev0, ev1, 0u, a);
   else
-    hipLaunchKernelGGL((k_eval_class<KIND, CLS, KV>), dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL((k_eval_class<KIND, CLS, KV>), dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-// input bytes of the resident kernel with K cases per lane (the case set
-// padded to whole passes of 64 K cases)
-static size_t resident_bytes(const EvalArgs& a, int K) {
-  const int64_t k64 = 64 * K;
-  return size_t((a.M + k64 - 1) / k64) * size_t(a.D) * size_t(k64) * sizeof(float);
+// bytes of the staged case set
+static size_t resident_bytes(const EvalArgs& a) {
+  return size_t((a.M + TILE - 1) / TILE) * size_t(a.rows) * size_t(TILE) * sizeof(float);
 }
 
-// The resident kernel takes the call when there is one chunk, enough programs
-// to give every SIMD several waves, and inputs within RESIDENT_MAX_BYTES at
-// the wider tile's padding: the choice never depends on the tile width, so
-// the tuner's pick cannot switch kernels (and summation orders).
-bool resident_eligible(int64_t M, int32_t D, int32_t n_chunks, int32_t n_total) {
-  const size_t b8 = size_t((M + 511) / 512) * size_t(D) * 512u * sizeof(float);
-  return n_chunks == 1 && n_total >= RESIDENT_MIN_PROGRAMS && b8 <= RESIDENT_MAX_BYTES;
+// The resident kernels take the call when there is one chunk whose rows fit
+// and enough programs to repay the copies; both give the same bits (a wave
+// adds a program's cases in the same order).
+static bool resident_eligible(const EvalArgs& a) {
+  return a.n_chunks == 1 && a.n_total >= RESIDENT_MIN_PROGRAMS && resident_bytes(a) <= RESIDENT_MAX_BYTES;
 }
-
-static bool resident_eligible(const EvalArgs& a) { return resident_eligible(a.M, a.D, a.n_chunks, a.n_total); }
 
 template <int KIND, int K, int CLS>
-static hipError_t launch_resident(const EvalArgs& a, size_t lds, hipStream_t s, hipEvent_t ev0 = nullptr,
-                                  hipEvent_t ev1 = nullptr) {
-  static size_t cached_lds = size_t(-1);
-  static int cached = 0;
-  if (lds != cached_lds) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_eval_resident<KIND, K, CLS>, 256, lds) != hipSuccess ||
-        nb < 1)
-      nb = 1;
-    cached = nb;
-    cached_lds = lds;
-  }
+static hipError_t launch_resident(const EvalArgs& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+  const size_t lds = resident_bytes(a);
+  // workgroups per CU that fit, and waves of each: together the waves that the
+  // registers allow (RESIDENT_WAVES per SIMD, 4 for the deeper class), at most
+  // 16 in one workgroup
+  const int want = 4 * (CLS == 0 ? RESIDENT_WAVES : 4);
+  const int fit = std::max(1, std::min(want / 4, int(RESIDENT_MAX_BYTES / lds)));
+  // (a multiple of four: a wave of each workgroup more on one SIMD than on
+  // another would keep the next workgroup out)
+  const int waves = std::max(4, std::min(16, want / fit / 4 * 4));
+  const int grid = fit * cu_count();
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_eval_resident<KIND, K, CLS>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, int(RESIDENT_MAX_BYTES));
+  });
   if (ev0 || ev1)
-    hipExtLaunchKernelGGL((k_eval_resident<KIND, K, CLS>), dim3(cached * cu_count()), dim3(256), uint32_t(lds), s,
-                          ev0, ev1, 0u, a);
+    hipExtLaunchKernelGGL((k_eval_resident<KIND, K, CLS>), dim3(grid), dim3(waves * 64), uint32_t(lds), s, ev0, ev1, 0u,
+                          a);
   else
-    hipLaunchKernelGGL((k_eval_resident<KIND, K, CLS>), dim3(cached * cu_count()), dim3(256), lds, s, a);
+    hipLaunchKernelGGL((k_eval_resident<KIND, K, CLS>), dim3(grid), dim3(waves * 64), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1058,17 +1064,17 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
   if (!counters_clear) hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, a.work, N_CLASSES);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool wide = kv == 0 && a.D <= WIDE_TILE_MAX_D;
-  const bool resident = resident_eligible(a);
-  if (resident)
-    e = wide ? launch_resident<KIND, 8, 0>(a, resident_bytes(a, 8), s, ev0, ev1)
-             : launch_resident<KIND, 4, 0>(a, resident_bytes(a, 4), s, ev0, ev1);
-  else
-    e = wide ? launch_class<KIND, 0, 0>(a, s, ev0, ev1) : launch_class<KIND, 0, 1>(a, s, ev0, ev1);
+  // (a chunk of half a tile: only the narrow tile starts inside a tile)
+  const bool wide = kv == 0 && a.chunk % TILE == 0;
+  if (resident_eligible(a)) {
+    e = wide ? launch_resident<KIND, 8, 0>(a, s, ev0, ev1) : launch_resident<KIND, 4, 0>(a, s, ev0, ev1);
+    if (e != hipSuccess) return e;
+    if ((e = launch_resident<KIND, 4, 1>(a, s)) != hipSuccess) return e;
+    return launch_class<KIND, 2, 0>(a, s);
+  }
+  e = wide ? launch_class<KIND, 0, 0>(a, s, ev0, ev1) : launch_class<KIND, 0, 1>(a, s, ev0, ev1);
   if (e != hipSuccess) return e;
-  // class 1 (register need 5..8, and every program with one of the further
-  // operators) resident too when the shape allows, 4 cases per lane
-  e = resident ? launch_resident<KIND, 4, 1>(a, resident_bytes(a, 4), s) : launch_class<KIND, 1, 0>(a, s);
+  e = launch_class<KIND, 1, 0>(a, s);
   if (e != hipSuccess) return e;
   return launch_class<KIND, 2, 0>(a, s);
 }
@@ -1087,83 +1093,56 @@ hipError_t launch_eval(int kind, int kv, const EvalArgs& a, hipStream_t s, hipEv
   }
 }
 
-// Persistent grid of a work-list kernel: resident workgroups per CU at the
-// list's LDS tile size, times the CUs (cached per largest D, 1..MAX_D, so
-// that the occupancy queries all happen before a graph capture).
+// Persistent grid of a work-list kernel (the occupancy queries all happen
+// before a graph capture: prime_eval_batch).
 template <int KIND, int CLS, int KV>
-static int list_grid(int max_d) {
-  static int cached[MAX_D + 1] = {0};
-  const int d = max_d < 1 ? 1 : (max_d > MAX_D ? MAX_D : max_d);
-  if (cached[d] == 0) {
-    const size_t lds = size_t(EVAL_WAVES) * d * ((class_k(CLS, KV) + 3) / 4) * 256 * sizeof(float);
+static int list_grid() {
+  static int cached = 0;
+  if (!cached) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_eval_batch<KIND, CLS, KV>, 256, lds) != hipSuccess ||
-        nb < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_eval_batch<KIND, CLS, KV>, 256, 0) != hipSuccess || nb < 1)
       nb = 1;
-    cached[d] = nb * cu_count();
+    cached = nb * cu_count();
   }
-  return cached[d];
+  return cached;
 }
 
 template <int KIND, int CLS, int KV>
-static hipError_t launch_list(const BatchArgs& b, int vl, int max_d, hipStream_t s) {
-  const size_t lds = size_t(EVAL_WAVES) * max_d * ((class_k(CLS, KV) + 3) / 4) * 256 * sizeof(float);
-  hipLaunchKernelGGL((k_eval_batch<KIND, CLS, KV>), dim3(list_grid<KIND, CLS, KV>(max_d)), dim3(256), lds, s, b, vl);
+static hipError_t launch_list(const BatchArgs& b, int v, const int* has, hipStream_t s) {
+  if (!has[v]) return hipSuccess;
+  hipLaunchKernelGGL((k_eval_batch<KIND, CLS, KV>), dim3(list_grid<KIND, CLS, KV>()), dim3(256), 0, s, b, v);
   return hipGetLastError();
 }
 
-// every bucket of list v (its lists are v * N_DBUCKETS + bucket)
-template <int KIND, int CLS, int KV>
-static hipError_t launch_buckets(const BatchArgs& b, int v, const int* max_d, const int* has, hipStream_t s) {
-  for (int db = 0; db < N_DBUCKETS; ++db) {
-    const int vl = v * N_DBUCKETS + db;
-    if (!has[vl]) continue;
-    const hipError_t e = launch_list<KIND, CLS, KV>(b, vl, max_d[vl], s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-template <int KIND, int CLS, int KV>
-static void prime_buckets(int v, const int* max_d, const int* has) {
-  for (int db = 0; db < N_DBUCKETS; ++db)
-    if (has[v * N_DBUCKETS + db]) (void)list_grid<KIND, CLS, KV>(max_d[v * N_DBUCKETS + db]);
-}
-
 template <int KIND>
-static void prime_kind(const int* max_d, const int* has) {
-  prime_buckets<KIND, 0, 0>(0, max_d, has);
-  prime_buckets<KIND, 0, 1>(1, max_d, has);
-  prime_buckets<KIND, 1, 0>(2, max_d, has);
-  prime_buckets<KIND, 2, 0>(3, max_d, has);
+static void prime_kind() {
+  (void)list_grid<KIND, 0, 0>();
+  (void)list_grid<KIND, 0, 1>();
+  (void)list_grid<KIND, 1, 0>();
+  (void)list_grid<KIND, 2, 0>();
 }
 
-void prime_eval_batch(int kind, const int* max_d, const int* has_items) {
+void prime_eval_batch(int kind) {
   if (kind == BEAGLE_FIT_MSE)
-    prime_kind<BEAGLE_FIT_MSE>(max_d, has_items);
+    prime_kind<BEAGLE_FIT_MSE>();
   else
-    prime_kind<BEAGLE_FIT_CORR>(max_d, has_items);
+    prime_kind<BEAGLE_FIT_CORR>();
 }
 
 template <int KIND>
-static hipError_t launch_batch_kind(const BatchArgs& b, const int* max_d, const int* has, hipStream_t s,
-                                    hipEvent_t ev0, hipEvent_t ev1) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, b.work, N_BATCH_LISTS);
+static hipError_t launch_batch_kind(const BatchArgs& b, const int* has, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, b.work, N_LISTS);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (ev0) (void)hipEventRecord(ev0, s);
-  if ((e = launch_buckets<KIND, 0, 0>(b, 0, max_d, has, s)) != hipSuccess) return e;
-  if ((e = launch_buckets<KIND, 0, 1>(b, 1, max_d, has, s)) != hipSuccess) return e;
-  if (ev1) (void)hipEventRecord(ev1, s);
-  if ((e = launch_buckets<KIND, 1, 0>(b, 2, max_d, has, s)) != hipSuccess) return e;
-  if ((e = launch_buckets<KIND, 2, 0>(b, 3, max_d, has, s)) != hipSuccess) return e;
-  return hipSuccess;
+  if ((e = launch_list<KIND, 0, 0>(b, 0, has, s)) != hipSuccess) return e;
+  if ((e = launch_list<KIND, 0, 1>(b, 1, has, s)) != hipSuccess) return e;
+  if ((e = launch_list<KIND, 1, 0>(b, 2, has, s)) != hipSuccess) return e;
+  return launch_list<KIND, 2, 0>(b, 3, has, s);
 }
 
-hipError_t launch_eval_batch(int kind, const BatchArgs& b, const int* max_d, const int* has_items, hipStream_t s,
-                             hipEvent_t ev0, hipEvent_t ev1) {
-  return kind == BEAGLE_FIT_MSE ? launch_batch_kind<BEAGLE_FIT_MSE>(b, max_d, has_items, s, ev0, ev1)
-                                : launch_batch_kind<BEAGLE_FIT_CORR>(b, max_d, has_items, s, ev0, ev1);
+hipError_t launch_eval_batch(int kind, const BatchArgs& b, const int* has_items, hipStream_t s) {
+  return kind == BEAGLE_FIT_MSE ? launch_batch_kind<BEAGLE_FIT_MSE>(b, has_items, s)
+                                : launch_batch_kind<BEAGLE_FIT_CORR>(b, has_items, s);
 }
 
 }  // namespace bgl

@@ -6,6 +6,7 @@
 
 #include "../../include/beagle.h"
 #include "beagle_device.h"
+#include "kernels.h"
 
 namespace bgl {
 
@@ -76,9 +77,9 @@ struct GradArgs {
   const ProgMeta* meta;
   const int64_t* const_offset;
   const int32_t* const_count;
-  const float* Xt;  // [D x Mp]
-  const float* yp;  // [Mp]
-  int64_t M, Mp;
+  const float* Xt;  // staged cases (kernels.h), the targets in the last row
+  int32_t rows;
+  int64_t M;
   int32_t D;
   int32_t n_programs;
   int32_t n_chunks;

@@ -255,8 +255,9 @@ __device__ void grad_item(const GradArgs& a, int p, int c, float* lds) {
   for (int64_t base = c0; base < c1; base += 64) {
     const int64_t i = base + lane;
     const bool valid = i < a.M;
-    for (int d = 0; d < a.D; ++d) xl[d * 64] = a.Xt[int64_t(d) * a.Mp + i];
-    const float yk = a.yp[i];
+    const float* xg = a.Xt + case_offset(i, a.rows);
+    for (int d = 0; d < a.D; ++d) xl[d * 64] = xg[d * TILE];
+    const float yk = xg[(a.rows - 1) * TILE];
     __builtin_amdgcn_wave_barrier();
     // ---- forward with tape
     float top = 0.0f;
@@ -787,12 +788,13 @@ __device__ __forceinline__ void dtape_item(const GradArgs& a, int p, int c, floa
     // the tile's inputs go straight from global memory to LDS (64 cases per
     // instruction), every variable's loads issued before one wait
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the last tile's LDS reads are done
+    // (a tile of 64 G cases lies within one staged tile)
+    const float* xg = a.Xt + case_offset(base, a.rows) + lane;
     for (int d = 0; d < a.D; ++d) {
       if (!((vmask >> d) & 1u)) continue;
-      BGL_K(G) __builtin_amdgcn_global_load_lds(a.Xt + int64_t(d) * a.Mp + base + 64 * k + lane,
-                                                lds + (d * G + k) * 64, 4, 0, 0);
+      BGL_K(G) __builtin_amdgcn_global_load_lds(xg + d * TILE + 64 * k, lds + (d * G + k) * 64, 4, 0, 0);
     }
-    BGL_K(G) yv[k] = a.yp[base + 64 * k + lane];
+    BGL_K(G) yv[k] = xg[(a.rows - 1) * TILE + 64 * k];
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the tile is in LDS
     __builtin_amdgcn_wave_barrier();
     // ---- forward: values on the stack, partial derivatives on the tape

@@ -98,6 +98,11 @@ int64_t round_up(int64_t v, int64_t m);
 // a multiple of unit, the cases one kernel iteration covers), more when the
 // population alone gives too few work items.
 void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit);
+// The evaluation's chunks (see CHUNK_CASES).
+void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
+// Whether an evaluation of N programs stages derived input rows: computing
+// them costs about eight programs' work per case.
+inline bool use_derived(int64_t N) { return N >= 16; }
 void zero_i32(int32_t* p, int64_t n, hipStream_t s);
 
 // Tile variant of class 0 for a problem (0 wide, 1 narrow).  Under

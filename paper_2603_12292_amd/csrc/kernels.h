@@ -23,6 +23,11 @@ struct PrepareArgs {
   uint32_t* code;      // [n_tokens] decoded words
   uint32_t* aux;       // [n_tokens] adjoint operands per decoded word
   float* cval;         // [n_tokens] CONST values by output position
+  uint8_t* vrow;       // [n_tokens] input rows of the VAR words, in word order
+  // nonzero: the staged cases hold the base operators' values of every
+  // variable as rows of their own (see derived_row), and "unary operator of a
+  // variable" decodes to a VAR word of such a row
+  int32_t derived;
   int32_t max_words;   // decoded words allowed (longer -> BEAGLE_PROG_TOO_LONG)
   int32_t* scr_stack;  // [n_tokens] scratch
   int32_t* scr_start;  // [n_tokens] scratch
@@ -55,14 +60,34 @@ struct PrepareArgs {
   int32_t wave_programs;
 };
 
+// Staged cases: tiles of TILE cases, row-major within a tile (`rows` rows of
+// TILE cases: the D variables, the derived rows when there are any, the
+// targets last), so that a row of a tile is one run of 2 KB and a tile's rows
+// lie together.
+constexpr int TILE = 512;
+// offset of a case of row 0 in floats
+__host__ __device__ constexpr int64_t case_offset(int64_t i, int32_t rows) {
+  return (i / TILE) * (int64_t(rows) * TILE) + i % TILE;
+}
+// Derived rows: base unary operator u (SIN .. SQRT: 0..4) of variable d.
+// Of the arithmetic of random programs a quarter is an operator of the base
+// set applied to a variable itself; computing those 5 D rows once per call and
+// reading them costs a few programs' work.
+__host__ __device__ constexpr int derived_row(int u, int d, int D) { return D + u * D + d; }
+constexpr int DERIVED_OPS = 5;
+__host__ __device__ constexpr int32_t stage_rows(int32_t D, int derived) {
+  return (derived ? (1 + DERIVED_OPS) * D : D) + 1;
+}
+static_assert((1 + DERIVED_OPS) * MAX_D <= 256, "rows are bytes");
+
 struct StageArgs {
   const float* X;
   const float* y;
   int64_t M;
-  int64_t Mp;
+  int64_t Mp;  // padded to whole tiles
   int32_t D;
-  float* Xt;  // [D x Mp]
-  float* yp;  // [Mp]
+  int32_t derived;
+  float* Xt;  // [Mp / TILE][rows][TILE]
 };
 
 // Partial sums per (chunk, program) of each fitness kind (the evaluator's
@@ -75,16 +100,15 @@ constexpr int MAX_SUMS = 8;
 struct EvalArgs {
   const uint32_t* code;
   const float* cval;
+  const uint8_t* vrow;
   const int64_t* tok_offset;
   const ProgMeta* meta;
-  const float* Xt;  // [D x Mp]
-  const float* yp;  // [Mp]
+  const float* Xt;  // staged cases
+  int32_t rows;     // rows per tile
   int64_t M;
-  int64_t Mp;
-  int32_t D;
   int32_t n_programs;
   int32_t n_chunks;
-  int64_t chunk;          // cases per chunk, a multiple of CASES_PER_BLOCK_ITER
+  int64_t chunk;          // cases per chunk, a multiple of CHUNK_UNIT
   double* part;           // [n_sums][n_chunks][n_programs]
   const double* stats;    // target statistics (correlation fitness)
   const int32_t* class_count;       // [N_CLASSES]
@@ -93,9 +117,8 @@ struct EvalArgs {
   int32_t n_total;                  // programs in the whole population
   int32_t prog_begin;               // first program of this launch (slice-local index 0)
   double smax = 0.0;                // the paper's scores: maximum score S
-  // correlation and Eq. 2: when set, the resident-inputs kernels take each
-  // class-0 and class-1 program's shift from their own first pass and store
-  // it here (the same array as meta); the shift pass then covers class 2 only
+  // correlation and Eq. 2 in one chunk: the kernels take each program's shift
+  // from their own first tile and store it here (the same array as meta)
   ProgMeta* meta_shift = nullptr;
 };
 
@@ -120,9 +143,8 @@ struct ValuesArgs {
   const int64_t* tok_offset;
   ProgMeta* meta;
   const float* Xt;
-  int64_t Mp;
+  int32_t rows;
   int64_t m;        // cases evaluated: [0, m)
-  int32_t D;
   int32_t n_programs;
   float* out;       // [n_programs x m] or null (shift mode)
   int32_t shift_mode;
@@ -135,8 +157,8 @@ struct BatchProblem {
   PrepareArgs prep;  // programs, decode targets, class lists, status output
   const float* X;    // [M x D] caller's cases
   const float* y;    // [M]
-  float* Xt;         // [D x Mp]
-  float* yp;         // [Mp]
+  float* Xt;         // staged cases
+  int32_t rows;      // rows per tile
   double* stats;     // [4] target statistics
   double* part;      // [n_sums][n_chunks][n_programs]
   double* fitness;   // [n_programs] caller's output
@@ -150,18 +172,8 @@ struct BatchProblem {
 };
 
 // Work lists of a batched evaluation: class 0 wide tile, class 0 narrow
-// tile, class 1, class 2; each split by the problems' variable count into
-// N_DBUCKETS lists, launched separately so that each launch sizes its input
-// tiles in LDS, and hence its occupancy, for its own largest D instead of the
-// batch's.  The buckets (D <= 5, 6, 7..8, more) end where the workgroups
-// per CU change: the 8-case tiles fit four workgroups up to D = 5 (their
-// registers allow no more), three at 6, two at 7 and 8; the 4-case ones seven
-// up to 5, six at 6, five at 7 and 8, four at 9.
+// tile, class 1, class 2.
 constexpr int N_LISTS = 4;
-constexpr int N_DBUCKETS = 4;
-constexpr int N_BATCH_LISTS = N_LISTS * N_DBUCKETS;
-static_assert(N_BATCH_LISTS <= 64, "one wave clears and offsets the work lists");
-__host__ __device__ constexpr int d_bucket(int D) { return D <= 5 ? 0 : (D == 6 ? 1 : (D <= 8 ? 2 : 3)); }
 
 struct BatchArgs {
   const BatchProblem* table;
@@ -169,8 +181,8 @@ struct BatchArgs {
   int32_t kind;
   int64_t n_programs;          // over the whole table
   int64_t n_cases;             // padded cases over the whole table
-  int64_t* item_off;           // [N_BATCH_LISTS][n_problems + 1] first work item of each problem per list
-  unsigned long long* work;    // [N_BATCH_LISTS] work-item counters, zero at launch
+  int64_t* item_off;           // [N_LISTS][n_problems + 1] first work item of each problem per list
+  unsigned long long* work;    // [N_LISTS] work-item counters, zero at launch
 };
 
 // The problem holding batch-wide index x of a prefix field (prog_begin or
@@ -189,19 +201,23 @@ __device__ __forceinline__ int batch_find(const BatchArgs& b, int64_t x, F field
 }
 
 constexpr int EVAL_WAVES = 4;
-constexpr int CASES_PER_WAVE_ITER = 64 * 8;                             // cases of one wave tile (K <= 8)
-constexpr int CASES_PER_BLOCK_ITER = CASES_PER_WAVE_ITER * EVAL_WAVES;  // chunk granularity and case padding
-// Cases per lane of the register-need classes (variant KV selects the
-// narrower tile of class 0, used when the LDS input tile of the wide one
-// would exceed WIDE_TILE_MAX_D variables).
-constexpr int WIDE_TILE_MAX_D = 8;
+// rows a wave keeps in flight: two are enough behind the other waves of a
+// SIMD, and four cost the fifth of them (the workgroup's 32 KB leave room for
+// four): 1.67 against 1.83 ms on 4096 programs x 10^5 cases
+constexpr int RING = 2;
+// Case chunks: a wave takes one program on one chunk.  At most CHUNK_CASES
+// cases (eight tiles: long enough that a work item's start is a few per cent of
+// it, short enough that the last items end together and that a chunk's rows
+// stay in an XCD's L2), a multiple of CHUNK_UNIT (a narrow tile).
+constexpr int64_t CHUNK_CASES = 4096;
+constexpr int64_t CHUNK_UNIT = 256;
 // The resident-inputs evaluator (small case sets, register-need classes 0
-// and 1): inputs of at most this many bytes per workgroup, populations of at
-// least this many programs.
-constexpr size_t RESIDENT_MAX_BYTES = 64 * 1024;
+// and 1): staged rows of at most this many bytes, populations of at least this
+// many programs.
+constexpr size_t RESIDENT_MAX_BYTES = 158 * 1024;
 constexpr int32_t RESIDENT_MIN_PROGRAMS = 4096;
-constexpr int RESIDENT_BATCH = 16;  // programs a wave claims per atomic (long lists)
-__host__ __device__ constexpr int class_k(int c, int kv) { return c == 0 ? (kv == 0 ? 8 : 4) : (c == 1 ? 4 : 2); }
+constexpr int64_t CLAIM_MAX = 16;  // work items of one claim at most
+__host__ __device__ constexpr int class_k(int c, int kv) { return c == 0 ? (kv == 0 ? 8 : 4) : 4; }
 
 // decoding: programs of at most 64 tokens in k_prepare_wave (a wave per
 // program) or k_prepare (a thread per program, narrow LDS scratch), the
@@ -229,28 +245,17 @@ __global__ void k_finalize_batch(BatchArgs b);
 __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* __restrict__ stats);
 __global__ void k_finalize(FinalizeArgs a);
 __global__ void k_values(ValuesArgs a);
-// correlation shifts of the programs of register-need class 2 (a persistent
-// grid walking its class list)
-__global__ void k_values_deep(ValuesArgs a, const int32_t* class_count, const int32_t* class_list, int32_t stride);
-// whether an evaluation of this shape takes the resident-inputs kernels for
-// classes 0 and 1 (one chunk, enough programs, inputs within
-// RESIDENT_MAX_BYTES)
-bool resident_eligible(int64_t M, int32_t D, int32_t n_chunks, int32_t n_total);
-
 // host launchers of the templated evaluation kernels (eval.hip)
 // ev0/ev1 (may be null) are recorded on `s` right before and after the
 // fast-path kernel.
-// kv selects the tile variant of class 0 (forced to the narrow one above
-// WIDE_TILE_MAX_D variables).
+// kv selects the tile variant of class 0.
 // counters_clear: a.work is known to be zero (else it is cleared first).
 hipError_t launch_eval(int kind, int kv, const EvalArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                        bool counters_clear = false);
-// The work-list kernels of a batched evaluation; max_d[v] is the largest D
-// among the problems of list v (sizes the LDS tile), lists with
-// has_items[v] == 0 are skipped.
-hipError_t launch_eval_batch(int kind, const BatchArgs& b, const int* max_d, const int* has_items, hipStream_t s,
-                             hipEvent_t ev0, hipEvent_t ev1);
+// The work-list kernels of a batched evaluation; lists with has_items[v] == 0
+// are skipped.
+hipError_t launch_eval_batch(int kind, const BatchArgs& b, const int* has_items, hipStream_t s);
 // Runs the occupancy queries of those launches (before a stream capture).
-void prime_eval_batch(int kind, const int* max_d, const int* has_items);
+void prime_eval_batch(int kind);
 
 }  // namespace bgl

@@ -5,6 +5,7 @@
 #include "beagle_device.h"
 #include "grad.h"
 #include "kernels.h"
+#include "trig.h"
 
 namespace bgl {
 
@@ -80,7 +81,7 @@ __device__ static void dtape_words(const uint32_t* code, uint32_t* aux, int L, S
 struct ListIds {
   int cls = -1, lc = -1;
   // the wave decoders' program header fields (ProgMeta): status | need << 8
-  // | len << 16, and the variable mask (shift is 0 after decoding)
+  // | len << 16 | nv << 24, and the variable mask (shift is 0 after decoding)
   int32_t head = 0;
   uint32_t vmask = 0u;
 };
@@ -110,6 +111,7 @@ __device__ static ListIds prepare_program(const PrepareArgs& a, int p, ST tok, S
   int need_root = 0;
   int L_dec = 0;
   int n_ent = 0;  // derivative-tape entries per case (adjoint)
+  int nv = 0;     // VAR words
   uint32_t vmask = 0;
   bool ext = false;  // uses one of the further operators (SQUARE .. TANH)
   if (L <= 0) {
@@ -203,7 +205,17 @@ __device__ static ListIds prepare_program(const PrepareArgs& a, int p, ST tok, S
       int n = 0, nmax = 0, out = 0;
       for (int i = 0; i < L; ++i) {
         const uint32_t w = uint32_t(ord.get(i));
-        const uint32_t op = w & 0xFFu, arg = (w >> 8) & 0xFFu;
+        const uint32_t op = w & 0xFFu;
+        uint32_t arg = (w >> 8) & 0xFFu;
+        if (a.derived && op == OP_VAR && i + 1 < L) {
+          // a base unary operator of the variable: its row, one terminal
+          const uint32_t u = (uint32_t(ord.get(i + 1)) & 0xFFu) - OP_SIN;
+          if (u < uint32_t(DERIVED_OPS)) {
+            arg = uint32_t(derived_row(int(u), int(arg), a.D));
+            ++i;
+          }
+        }
+        if (op == OP_VAR) a.vrow[off + nv++] = uint8_t(arg);
         const uint32_t wslot = n > 0 ? uint32_t(n - 1) : 0u;
         uint32_t h, i0, pa = 0u, rws, rid;
         bool wcf;   // constant-free subtree
@@ -298,6 +310,7 @@ __device__ static ListIds prepare_program(const PrepareArgs& a, int p, ST tok, S
   m.len = status == BEAGLE_PROG_OK ? L_dec : 0;
   m.shift = 0.0f;
   m.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
+  m.nv = nv;
   a.meta[p] = m;
   if (a.status_out) a.status_out[p] = int8_t(status);
   ListIds ids;
@@ -758,7 +771,8 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
       const uint32_t e = act ? sh.b[lane] : 0x010000FFu;  // (no token: arity 1, stack unchanged)
       __builtin_amdgcn_wave_barrier();
       // ---- words, in output order (lane o holds output token o)
-      const uint32_t o_op = e & 0xFFu, o_arg = (e >> 8) & 0xFFu;
+      const uint32_t o_op = e & 0xFFu;
+      uint32_t o_arg = (e >> 8) & 0xFFu;
       // a CONST word's value, loaded as soon as the slot is known (its
       // latency then overlaps the word's assembly; stored with the word)
       float cvv = 0.0f;
@@ -766,20 +780,29 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
       const int o_st = int((e >> 16) & 0xFFu);  // start of its subtree
       const uint32_t o_ar = e >> 24;
       const bool o_bin = o_ar == 2u;
-      const bool o_term = o_ar == 0u;  // VAR or CONST
       const int o_delta = 1 - int(o_ar);
       const int n_after = scan_add(o_delta);
-      const int n = n_after - o_delta;  // stack size before the token
+      // a base unary operator of a variable whose row is staged: the operator
+      // becomes the terminal (mgm), the variable before it no word (mgm >> 1)
+      const uint64_t varm = __builtin_amdgcn_ballot_w64(o_op == OP_VAR) & actm;
+      const uint64_t mgm =
+          a.derived ? __builtin_amdgcn_ballot_w64(o_op - uint32_t(OP_SIN) < uint32_t(DERIVED_OPS)) & (varm << 1) & actm : 0ull;
+      const bool merged = __builtin_amdgcn_inverse_ballot_w64(mgm);
+      const uint32_t row = (o_op - uint32_t(OP_SIN) + 1u) * uint32_t(a.D) + ((uint32_t(dpp<0x138, 0xF>(int(e))) >> 8) & 0xFFu);
+      o_arg = sel(merged, row, o_arg);
+      const uint64_t termm = (__builtin_amdgcn_ballot_w64(o_ar == 0u) & ~(mgm >> 1)) | mgm;
+      const bool o_term = __builtin_amdgcn_inverse_ballot_w64(termm);  // VAR or CONST
+      const int n = n_after - o_delta - int(merged);  // stack size before the token
       const uint32_t nxt = uint32_t(from(int(o_op), lane < 63 ? lane + 1 : 63));
       // fused pairs: a terminal on a non-empty stack followed by a binary
       // operator; words: every token but such a terminal -- lane masks
       // combined on the scalar side, turned back into lane conditions by
       // inverse ballots (no VALU work)
-      const uint64_t fm = __builtin_amdgcn_ballot_w64(o_term) & __builtin_amdgcn_ballot_w64(n >= 1) &
+      const uint64_t fm = termm & __builtin_amdgcn_ballot_w64(n >= 1) &
                           (__builtin_amdgcn_ballot_w64(nxt < 4u) | __builtin_amdgcn_ballot_w64(nxt - 100u < 6u)) &
                           (actm >> 1);
       const bool fused = __builtin_amdgcn_inverse_ballot_w64(fm);
-      const uint64_t wm = actm & ~(fm << 1);
+      const uint64_t wm = actm & ~(fm << 1) & ~(mgm >> 1);
       const bool ws = __builtin_amdgcn_inverse_ballot_w64(wm);
       const int E = int(__builtin_amdgcn_mbcnt_hi(uint32_t(wm >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(wm), 0u)));
       const int widx = ws ? E : E - 1;  // word of each token (a fused pair's operator: the pair's word)
@@ -794,10 +817,14 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
       const uint32_t u = unary_index(o_op);
       const uint32_t isc1 = isc ? 1u : 0u;
       const int kind = fused ? 0 : o_term ? 1 : o_bin ? 2 : 3;
-      const uint32_t key = fused ? 20u + 6u * isc1 + ob : o_op >= 100u ? o_op - 86u : o_op;
+      const uint32_t key = fused ? 20u + 6u * isc1 + ob : merged ? uint32_t(OP_VAR) : o_op >= 100u ? o_op - 86u : o_op;
       const uint32_t wslot = n > 0 ? un - 1u : 0u;
       const uint32_t warg = o_term ? o_arg : 0u;
       const uint32_t word = word_handlers(wt, key, un) | (warg << 8) | (wslot << 16);
+      // the rows of the VAR words, in word order
+      const uint64_t vm = (varm & ~(mgm >> 1)) | mgm;
+      const int vidx = int(__builtin_amdgcn_mbcnt_hi(uint32_t(vm >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(vm), 0u)));
+      if (__builtin_amdgcn_inverse_ballot_w64(vm)) a.vrow[off + vidx] = uint8_t(o_arg);
       // (the largest stack size in output order equals need_root: the
       // larger operand first reaches max(a, b + 1) for needs a >= b)
       if (need_root > MAX_STACK || L_dec > a.max_words) status = BEAGLE_PROG_TOO_LONG;
@@ -892,7 +919,7 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
         if (ext && ids.cls == 0) ids.cls = 1;
         ids.lc = lc_short;
       }
-      ids.head = status | (need_root << 8) | (L_dec << 16);
+      ids.head = status | (need_root << 8) | (L_dec << 16) | (__popcll(vm) << 24);
       ids.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
       return ids;
     }
@@ -1054,24 +1081,34 @@ __device__ static ListIds decode_seg(const PrepareArgs& a, int p, int64_t off, i
   const uint32_t e = live ? sh.b[lane] : 0x010000FFu;  // (as in decode_wave)
   __builtin_amdgcn_wave_barrier();
   // ---- words, in output order (position sl holds output token sl)
-  const uint32_t o_op = e & 0xFFu, o_arg = (e >> 8) & 0xFFu;
+  const uint32_t o_op = e & 0xFFu;
+  uint32_t o_arg = (e >> 8) & 0xFFu;
   float cvv = 0.0f;  // (loaded early, as in decode_wave)
   if (o_op == OP_CONST) cvv = a.consts[coff + o_arg];
   const uint32_t o_ar = e >> 24;
-  const bool o_term = o_ar == 0u;
   const int o_delta = 1 - int(o_ar);
   const int n_after = seg_scan_add<SEG>(o_delta);
-  const int n = n_after - o_delta;
+  constexpr uint64_t SEGFIRST = SEG == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;
+  constexpr uint64_t SEGLAST = SEGFIRST << (SEG - 1);
+  // (as in decode_wave: base unary operators of variables)
+  const uint64_t varm = __builtin_amdgcn_ballot_w64(o_op == OP_VAR) & livem;
+  const uint64_t mgm = a.derived ? __builtin_amdgcn_ballot_w64(o_op - uint32_t(OP_SIN) < uint32_t(DERIVED_OPS)) &
+                                       (varm << 1) & ~SEGFIRST & livem
+                                 : 0ull;
+  const bool merged = __builtin_amdgcn_inverse_ballot_w64(mgm);
+  const uint32_t row = (o_op - uint32_t(OP_SIN) + 1u) * uint32_t(a.D) + ((uint32_t(dpp<0x138, 0xF>(int(e))) >> 8) & 0xFFu);
+  o_arg = sel(merged, row, o_arg);
+  const uint64_t termm = (__builtin_amdgcn_ballot_w64(o_ar == 0u) & ~(mgm >> 1)) | mgm;
+  const bool o_term = __builtin_amdgcn_inverse_ballot_w64(termm);
+  const int n = n_after - o_delta - int(merged);
   const uint32_t nxt = uint32_t(sfrom(int(o_op), sl < SEG - 1 ? sl + 1 : SEG - 1));
   // (as in decode_wave; the next token must be in the same segment, and a
   // segment's first token absorbs nothing)
-  constexpr uint64_t SEGFIRST = SEG == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;
-  constexpr uint64_t SEGLAST = SEGFIRST << (SEG - 1);
-  const uint64_t fm = __builtin_amdgcn_ballot_w64(o_term) & __builtin_amdgcn_ballot_w64(n >= 1) &
+  const uint64_t fm = termm & __builtin_amdgcn_ballot_w64(n >= 1) &
                       (__builtin_amdgcn_ballot_w64(nxt < 4u) | __builtin_amdgcn_ballot_w64(nxt - 100u < 6u)) &
                       (livem >> 1) & ~SEGLAST & livem;
   const bool fused = __builtin_amdgcn_inverse_ballot_w64(fm);
-  const uint64_t wm = livem & ~((fm << 1) & ~SEGFIRST);
+  const uint64_t wm = livem & ~((fm << 1) & ~SEGFIRST) & ~(mgm >> 1);
   const bool ws = __builtin_amdgcn_inverse_ballot_w64(wm);
   const uint64_t below = sb == 0 ? 0ull : wm & ((1ull << sb) - 1ull);  // words of the segments below
   const int E = int(__builtin_amdgcn_mbcnt_hi(uint32_t(wm >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(wm), 0u))) -
@@ -1081,10 +1118,15 @@ __device__ static ListIds decode_seg(const PrepareArgs& a, int p, int64_t off, i
   const uint32_t un = uint32_t(n);
   const uint32_t ob = nxt >= 100u ? nxt - 100u : nxt;
   const bool isc = o_op == OP_CONST;
-  const uint32_t key = fused ? 20u + 6u * (isc ? 1u : 0u) + ob : o_op >= 100u ? o_op - 86u : o_op;
+  const uint32_t key =
+      fused ? 20u + 6u * (isc ? 1u : 0u) + ob : merged ? uint32_t(OP_VAR) : o_op >= 100u ? o_op - 86u : o_op;
   const uint32_t wslot = n > 0 ? un - 1u : 0u;
   const uint32_t warg = o_term ? o_arg : 0u;
   const uint32_t word = word_handlers(wt, key, un) | (warg << 8) | (wslot << 16);
+  const uint64_t vm = (varm & ~(mgm >> 1)) | mgm;
+  const int vidx = int(__builtin_amdgcn_mbcnt_hi(uint32_t(vm >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(vm), 0u))) -
+                   __popcll(sb == 0 ? 0ull : vm & ((1ull << sb) - 1ull));
+  if (__builtin_amdgcn_inverse_ballot_w64(vm)) a.vrow[off + vidx] = uint8_t(o_arg);
   if (ok && (need_root > MAX_STACK || L_dec > a.max_words)) status = BEAGLE_PROG_TOO_LONG;
   if (ws) {
     a.code[off + widx] = word;
@@ -1096,7 +1138,8 @@ __device__ static ListIds decode_seg(const PrepareArgs& a, int p, int64_t off, i
     if (ext && ids.cls == 0) ids.cls = 1;
   }
   // (a program stopped by its length keeps its need)
-  ids.head = status | ((ok ? need_root : 0) << 8) | ((status == BEAGLE_PROG_OK ? L_dec : 0) << 16);
+  ids.head = status | ((ok ? need_root : 0) << 8) | ((status == BEAGLE_PROG_OK ? L_dec : 0) << 16) |
+             (__popcll(segbits(vm)) << 24);
   ids.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
   return ids;
 }
@@ -1257,9 +1300,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
     ProgMeta m;
     m.status = head & 0xFF;
     m.need = (head >> 8) & 0xFF;
-    m.len = head >> 16;
+    m.len = (head >> 16) & 0xFF;
     m.shift = 0.0f;
     m.vmask = vmask;
+    m.nv = (head >> 24) & 0xFF;
     a.meta[p] = m;
     if (a.status_out) a.status_out[p] = int8_t(m.status);
   }
@@ -1368,12 +1412,30 @@ __global__ void __launch_bounds__(PREP_BLOCK) k_prepare_batch(BatchArgs b) {
   append_one(a, p, prepare_one(a, p, lds));
 }
 
-// X [M x D] row-major -> Xt [D x Mp] (case index fastest), y -> yp [Mp];
-// cases M..Mp-1 repeat case 0 (their outputs are masked out of every sum).
-__device__ static void stage_case(const StageArgs& a, int64_t i) {
+// Variables d0, d0 + split, ... of case i (see StageArgs): the variable's row
+// and, where derived rows are staged, the base unary operators' values of it,
+// by the interpreter's own functions; the target with the first of them.
+// Cases M..Mp-1 repeat case 0 (their outputs are masked out of every sum).
+__device__ static void stage_case(const StageArgs& a, int64_t i, int d0, int split) {
   const int64_t src = i < a.M ? i : 0;
-  for (int d = 0; d < a.D; ++d) a.Xt[int64_t(d) * a.Mp + i] = a.X[src * a.D + d];
-  a.yp[i] = a.y[src];
+  const int32_t rows = stage_rows(a.D, a.derived);
+  float* x = a.Xt + case_offset(i, rows);
+  for (int d = d0; d < a.D; d += split) {
+    const float v = a.X[src * a.D + d];
+    x[d * TILE] = v;
+    if (a.derived) {
+      float f[1] = {v};
+      trig_tile<false, 1>(f);
+      x[derived_row(0, d, a.D) * TILE] = f[0];
+      f[0] = v;
+      trig_tile<true, 1>(f);
+      x[derived_row(1, d, a.D) * TILE] = f[0];
+      x[derived_row(2, d, a.D) * TILE] = op_exp(v);
+      x[derived_row(3, d, a.D) * TILE] = op_log(v);
+      x[derived_row(4, d, a.D) * TILE] = op_sqrt(v);
+    }
+  }
+  if (d0 == 0) x[(rows - 1) * TILE] = a.y[src];
 }
 
 // Staging and the disjoint-ranges check in one launch (neither reads what
@@ -1382,9 +1444,13 @@ __device__ static void stage_case(const StageArgs& a, int64_t i) {
 __global__ void k_stage_and_check(StageArgs sa, PrepareArgs pa, uint32_t stage_blocks) {
   if (blockIdx.x < stage_blocks) {
     // (grid-stride: the staging part of the grid is capped)
-    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < sa.Mp;
-         i += int64_t(stage_blocks) * blockDim.x)
-      stage_case(sa, i);
+    // a thread per case, on few cases a thread per case and variable
+    const int split = sa.Mp * sa.D <= (1 << 18) ? sa.D : 1;
+    for (int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; g < sa.Mp * split;
+         g += int64_t(stage_blocks) * blockDim.x) {
+      const int d0 = split == 1 ? 0 : int(g / sa.Mp);
+      stage_case(sa, g - int64_t(d0) * sa.Mp, d0, split);
+    }
   } else {
     const int64_t p = int64_t(blockIdx.x - stage_blocks) * blockDim.x + threadIdx.x;
     if (p < pa.n_programs) layout_pair(pa, int(p));
@@ -1403,9 +1469,9 @@ __global__ void k_stage_batch(BatchArgs b) {
   a.M = P.M;
   a.Mp = P.Mp;
   a.D = P.prep.D;
+  a.derived = P.prep.derived;
   a.Xt = P.Xt;
-  a.yp = P.yp;
-  stage_case(a, g - P.case_begin);
+  stage_case(a, g - P.case_begin, 0, 1);
 }
 
 // Target statistics for the correlation fitness and the paper's r^4 score,

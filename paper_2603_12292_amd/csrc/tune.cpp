@@ -49,7 +49,7 @@ static void save_tune_file(const beagle_ctx* ctx) {
 }
 
 bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, double mean_len, int* kv) {
-  if (D > WIDE_TILE_MAX_D || ctx->tuning == BEAGLE_TUNE_NARROW) {
+  if (ctx->tuning == BEAGLE_TUNE_NARROW) {
     *kv = 1;
     return true;
   }
