@@ -86,10 +86,10 @@ int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Case chunking: at most max_chunk_cases cases per chunk, more chunks when
 // the population alone gives too few work items to fill the GPU.
-void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit) {
+void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit,
+                   int64_t target_blocks) {
   const int64_t max_chunks = std::max<int64_t>(1, (M + unit - 1) / unit);
   int64_t C = std::max<int64_t>(1, (M + max_chunk_cases - 1) / max_chunk_cases);
-  const int64_t target_blocks = 4096;
   if (N * C < target_blocks) C = std::max<int64_t>(C, (target_blocks + N - 1) / std::max<int64_t>(N, 1));
   C = std::min(C, max_chunks);
   const int64_t ch = round_up((M + C - 1) / C, unit);
@@ -253,8 +253,10 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   return BEAGLE_OK;
 }
 
-beagle_status launch_values(char* ws, const beagle_programs* P, const EvalLayout& L, int64_t m, float* out,
-                            int shift_mode, hipStream_t s) {
+// The correlation shifts before an evaluation (correlation fitness and the
+// Eq. 2 score); with one chunk the evaluation kernels find them themselves.
+beagle_status launch_shifts(char* ws, const beagle_programs* P, const EvalLayout& L, hipStream_t s) {
+  if (L.n_chunks == 1) return BEAGLE_OK;
   bgl::ValuesArgs va;
   va.code = reinterpret_cast<const uint32_t*>(ws + L.code);
   va.cval = reinterpret_cast<const float*>(ws + L.cval);
@@ -262,22 +264,10 @@ beagle_status launch_values(char* ws, const beagle_programs* P, const EvalLayout
   va.meta = reinterpret_cast<bgl::ProgMeta*>(ws + L.meta);
   va.Xt = reinterpret_cast<const float*>(ws + L.Xt);
   va.rows = L.rows;
-  va.m = m;
-  va.n_programs = P->n_programs;
-  va.out = out;
-  va.shift_mode = shift_mode;
-  const int64_t tiles = (m + 63) / 64;
-  if (tiles > 65535) return fail(BEAGLE_E_UNSUPPORTED, "predict: M > 4194240");
-  hipLaunchKernelGGL(bgl::k_values, dim3(P->n_programs, uint32_t(tiles)), dim3(64), 0, s, va);
+  hipLaunchKernelGGL(bgl::k_shifts, dim3(P->n_programs), dim3(64), 0, s, va);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "values launch");
+  if (e != hipSuccess) return hip_fail(e, "shifts launch");
   return BEAGLE_OK;
-}
-
-// The correlation shifts before an evaluation (correlation fitness and the
-// Eq. 2 score); with one chunk the evaluation kernels find them themselves.
-beagle_status launch_shifts(char* ws, const beagle_programs* P, const EvalLayout& L, hipStream_t s) {
-  return L.n_chunks == 1 ? BEAGLE_OK : launch_values(ws, P, L, 1, nullptr, 1, s);
 }
 
 // Target statistics of data->y (correlation fitness, Eq. 2 score) into
@@ -325,6 +315,32 @@ beagle_status join_target_stats(hipEvent_t join, hipStream_t s) {
   if (!join) return BEAGLE_OK;
   const hipError_t e = hipStreamWaitEvent(s, join, 0);
   return e == hipSuccess ? BEAGLE_OK : hip_fail(e, "side stream join");
+}
+
+// Arguments of the interpreter kernels for the whole population.
+bgl::EvalArgs eval_args(char* ws, const EvalLayout& L, const beagle_programs* P, const beagle_dataset* d,
+                        bool shift_in_kernel) {
+  bgl::EvalArgs ea;
+  ea.code = reinterpret_cast<const uint32_t*>(ws + L.code);
+  ea.cval = reinterpret_cast<const float*>(ws + L.cval);
+  ea.vrow = reinterpret_cast<const uint8_t*>(ws + L.vrow);
+  ea.tok_offset = P->tok_offset;
+  ea.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta);
+  ea.Xt = reinterpret_cast<const float*>(ws + L.Xt);
+  ea.rows = L.rows;
+  ea.M = d->M;
+  ea.n_programs = P->n_programs;
+  ea.n_chunks = L.n_chunks;
+  ea.chunk = L.chunk;
+  ea.part = reinterpret_cast<double*>(ws + L.part);
+  ea.stats = reinterpret_cast<const double*>(ws + L.stats);
+  ea.class_count = reinterpret_cast<const int32_t*>(ws + L.class_count);
+  ea.class_list = reinterpret_cast<const int32_t*>(ws + L.class_list);
+  ea.work = reinterpret_cast<unsigned long long*>(ws + L.work);
+  ea.n_total = P->n_programs;
+  ea.prog_begin = 0;
+  ea.meta_shift = shift_in_kernel ? reinterpret_cast<bgl::ProgMeta*>(ws + L.meta) : nullptr;
+  return ea;
 }
 
 // One evaluation slice for the tile-width tuner.
@@ -488,27 +504,13 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
     if ((st = join_target_stats(join, s)) != BEAGLE_OK) return st;
   }
   auto slice_args = [&](int32_t p0, int32_t np) {
-    bgl::EvalArgs ea;
-    ea.code = reinterpret_cast<const uint32_t*>(ws + L.code);
-    ea.cval = reinterpret_cast<const float*>(ws + L.cval);
-    ea.tok_offset = progs->tok_offset + p0;
-    ea.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta) + p0;
-    ea.vrow = reinterpret_cast<const uint8_t*>(ws + L.vrow);
-    ea.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-    ea.rows = L.rows;
-    ea.M = data->M;
+    bgl::EvalArgs ea = eval_args(ws, L, progs, data, shift_in_kernel);
+    ea.tok_offset += p0;
+    ea.meta += p0;
     ea.n_programs = np;
-    ea.n_chunks = L.n_chunks;
-    ea.chunk = L.chunk;
-    ea.part = reinterpret_cast<double*>(ws + L.part);
-    ea.stats = reinterpret_cast<const double*>(ws + L.stats);
-    ea.class_count = reinterpret_cast<const int32_t*>(ws + L.class_count);
-    ea.class_list = reinterpret_cast<const int32_t*>(ws + L.class_list);
-    ea.work = reinterpret_cast<unsigned long long*>(ws + L.work);
-    ea.n_total = progs->n_programs;
     ea.prog_begin = p0;
     ea.smax = smax;
-    ea.meta_shift = shift_in_kernel ? reinterpret_cast<bgl::ProgMeta*>(ws + L.meta) + p0 : nullptr;
+    if (shift_in_kernel) ea.meta_shift += p0;
     return ea;
   };
   int kv = 1;
@@ -676,17 +678,26 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   if (!yhat) return fail(BEAGLE_E_INVALID_ARG, "yhat is NULL");
   if (int64_t(progs->n_programs) * data->M > (int64_t(1) << 31))
     return fail(BEAGLE_E_UNSUPPORTED, "predict: n_programs * M > 2^31");
+  if (data->M > 4194240) return fail(BEAGLE_E_UNSUPPORTED, "predict: M > 4194240");
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   EvalLayout L = eval_layout(progs, data, 1, 1, use_derived(progs->n_programs));
   if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, 1, 1, false);
+  // (outputs depend on no chunk: several work items per wave even for a few
+  // programs, so that the waves end together)
+  choose_chunks(data->M, progs->n_programs, &L.chunk, &L.n_chunks, bgl::CHUNK_CASES, bgl::TILE, 32768);
   st = reserve(ctx, L.total);
   if (st != BEAGLE_OK) return st;
   st = prepare(ctx->ws, progs, data, L, status, s, ctx->decoder);
   if (st != BEAGLE_OK) return st;
-  st = launch_values(ctx->ws, progs, L, data->M, yhat, 0, s);
-  if (st != BEAGLE_OK) return st;
+  bgl::EvalArgs ea = eval_args(ctx->ws, L, progs, data, false);
+  ea.out = yhat;
+  hipError_t e = bgl::launch_eval(bgl::KIND_OUTPUTS, 0, ea, s, nullptr, nullptr, true);
+  if (e != hipSuccess) return hip_fail(e, "eval launch");
+  hipLaunchKernelGGL(bgl::k_nan_rows, dim3(progs->n_programs), dim3(256), 0, s, ea.meta, data->M, yhat);
+  e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, "nan rows launch");
   clear_error();
   return BEAGLE_OK;
 }
@@ -924,26 +935,7 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   beagle_status st = launch_shifts(ws, progs, L, s);
   if (st != BEAGLE_OK) return st;
   if ((st = join_target_stats(join, s)) != BEAGLE_OK) return st;
-  bgl::EvalArgs ea;
-  ea.code = reinterpret_cast<const uint32_t*>(ws + L.code);
-  ea.cval = reinterpret_cast<const float*>(ws + L.cval);
-  ea.tok_offset = progs->tok_offset;
-  ea.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta);
-  ea.vrow = reinterpret_cast<const uint8_t*>(ws + L.vrow);
-  ea.Xt = reinterpret_cast<const float*>(ws + L.Xt);
-  ea.rows = L.rows;
-  ea.M = data->M;
-  ea.n_programs = progs->n_programs;
-  ea.n_chunks = L.n_chunks;
-  ea.chunk = L.chunk;
-  ea.part = reinterpret_cast<double*>(ws + L.part);
-  ea.stats = reinterpret_cast<const double*>(ws + L.stats);
-  ea.class_count = reinterpret_cast<const int32_t*>(ws + L.class_count);
-  ea.class_list = reinterpret_cast<const int32_t*>(ws + L.class_list);
-  ea.work = reinterpret_cast<unsigned long long*>(ws + L.work);
-  ea.n_total = progs->n_programs;
-  ea.prog_begin = 0;
-  ea.meta_shift = shift_in_kernel ? reinterpret_cast<bgl::ProgMeta*>(ws + L.meta) : nullptr;
+  const bgl::EvalArgs ea = eval_args(ws, L, progs, data, shift_in_kernel);
   int kv = 0;
   TuneSlice ts{BEAGLE_FIT_CORR, ea};
   st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s,

@@ -63,7 +63,7 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   hipLaunchKernelGGL(bgl::k_stage_batch, dim3(uint32_t((b.n_cases + 255) / 256)), dim3(256), 0, s, b.args);
   if (b.args.kind == BEAGLE_FIT_CORR) {
     hipLaunchKernelGGL(bgl::k_target_stats_batch, dim3(uint32_t(b.n)), dim3(1024), 0, s, b.args);
-    hipLaunchKernelGGL(bgl::k_values_batch, dim3(uint32_t(b.n_programs)), dim3(64), 0, s, b.args);
+    hipLaunchKernelGGL(bgl::k_shifts_batch, dim3(uint32_t(b.n_programs)), dim3(64), 0, s, b.args);
   }
   hipLaunchKernelGGL(bgl::k_batch_items, dim3(1), dim3(64), 0, s, b.args);
   hipError_t e = hipGetLastError();

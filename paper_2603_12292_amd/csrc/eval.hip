@@ -87,8 +87,8 @@ struct RowRing {
   uint32_t rows_f;    // floats per tile of the layout: rows x TILE
   uint32_t half;      // K = 4: floats from a tile's first to its second half
   const uint8_t* list;
-  int n, i, lane;     // reads per tile, look-ahead position in them
-  int yrow;
+  int n, i, lane;     // reads per tile (at least one), look-ahead position in them
+  int nv, yrow;       // VAR words; the targets' row
   int stop;           // where the look-ahead position next wraps or needs another block of rows
   int vt;             // rows of 64 reads, one per lane
   uint32_t slot;      // byte offset of the slot of the next read
@@ -96,17 +96,17 @@ struct RowRing {
 
   __device__ __forceinline__ int block(int b) const {
     const int j = b + lane;
-    return j < n - 1 ? int(list[j]) : yrow;
+    return j < nv ? int(list[j]) : yrow;
   }
   // The same in the middle of a tile (programs of 64 or more VAR words only).
   // A load whose wait the compiler placed would be waited for on the common
   // path as well, and with it every load in flight.
   __device__ __forceinline__ int block_now(int b) const {
     const int j = b + lane;
-    const uint8_t* at_j = list + (j < n - 1 ? j : 0);
+    const uint8_t* at_j = list + (j < nv ? j : 0);
     int v;
     asm volatile("global_load_ubyte %0, %1, off\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(at_j) : "memory");
-    return j < n - 1 ? v : yrow;
+    return j < nv ? v : yrow;
   }
   // the look-ahead row into `slot`
   __device__ __forceinline__ void issue() {
@@ -132,15 +132,17 @@ struct RowRing {
     if (n > 64) vt = block_now(i);
     stop = i + 64 < n ? i + 64 : n;
   }
-  // starts at case `c0` (a multiple of the tile) of the chunk ending at `c1`
-  __device__ __forceinline__ void start(const EvalArgs& a, float* ring_, const uint8_t* list_, int nv, int64_t c0,
-                                        int64_t c1) {
+  // starts at case `c0` (a multiple of the tile) of the chunk ending at `c1`;
+  // the targets are read after the last word or not at all
+  __device__ __forceinline__ void start(const EvalArgs& a, float* ring_, const uint8_t* list_, int nv_, bool targets,
+                                        int64_t c0, int64_t c1) {
     lane = int(threadIdx.x & 63u);
     ring = ring_;
     at = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)ring_)) + uint32_t(lane) * 16u;
     rows_f = uint32_t(a.rows) * TILE;
     list = list_;
-    n = nv + 1;
+    nv = nv_;
+    n = targets || nv == 0 ? nv + 1 : nv;
     yrow = a.rows - 1;
     tile = a.Xt + (c0 / TILE) * int64_t(rows_f);
     const int64_t cl = c1 - 1;
@@ -232,10 +234,9 @@ struct TableRows {
   }
 };
 
-// Rows read straight from global memory, one case per lane (the values
-// kernel).
+// Rows of case 0, read straight from global memory (the shifts).
 struct DirectRows {
-  const float* x;  // row 0 of the lane's case
+  const float* x;
   __device__ __forceinline__ void row(uint32_t r, float (&v)[1]) const { v[0] = x[r * uint32_t(TILE)]; }
 };
 
@@ -594,7 +595,7 @@ __device__ __forceinline__ void eval_wave(const EvalArgs& a, int p, int c, float
   if constexpr (RESIDENT)
     rows.start(a, lds);
   else
-    rows.start(a, lds, a.vrow + off, __builtin_amdgcn_readfirstlane(m.nv), c0, c1);
+    rows.start(a, lds, a.vrow + off, __builtin_amdgcn_readfirstlane(m.nv), KIND != KIND_OUTPUTS, c0, c1);
   const uint32_t vc0 = lane < L ? code[lane] : 0u;
   const float vv0 = lane < L ? cval[lane] : 0.0f;
   constexpr bool SHIFTED = KIND == BEAGLE_FIT_CORR || KIND == BEAGLE_FIT_R4;
@@ -608,6 +609,27 @@ __device__ __forceinline__ void eval_wave(const EvalArgs& a, int p, int c, float
       interpret_small<K>(vc0, vv0, code, cval, L, lane, rows, top);
     else
       interpret<K, S>(vc0, vv0, code, cval, L, lane, rows, top);
+    if constexpr (KIND == KIND_OUTPUTS) {
+      rows.next_tile();
+      const int64_t i = base + 4 * lane;
+      float* out = a.out + int64_t(p) * a.M + i;
+      // (four cases of a lane are one 16-byte store where a program's outputs
+      // start on 16 bytes)
+      const bool quads = (reinterpret_cast<uintptr_t>(a.out) & 15u) == 0 && (a.M & 3) == 0;
+#pragma unroll
+      for (int g = 0; g < K / 4; ++g) {
+        if (quads) {
+          if (i + g * 256 < c1)
+            *reinterpret_cast<float4*>(out + g * 256) =
+                make_float4(top[4 * g], top[4 * g + 1], top[4 * g + 2], top[4 * g + 3]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (i + g * 256 + k < c1) out[g * 256 + k] = top[4 * g + k];
+        }
+      }
+      continue;
+    }
     rows.targets(yk);
     rows.next_tile();
     if (SHIFTED && a.meta_shift && base == c0) {
@@ -631,11 +653,13 @@ __device__ __forceinline__ void eval_wave(const EvalArgs& a, int p, int c, float
       }
     }
   }
-  double v[MAX_SUMS];
-  acc.wave_sums(v);
-  if (lane == 0) {
+  if constexpr (KIND != KIND_OUTPUTS) {
+    double v[MAX_SUMS];
+    acc.wave_sums(v);
+    if (lane == 0) {
 #pragma unroll
-    for (int j = 0; j < kind_sums(KIND); ++j) a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p] = v[j];
+      for (int j = 0; j < kind_sums(KIND); ++j) a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p] = v[j];
+    }
   }
   // the look-ahead's last loads land before another item's are issued
   if constexpr (!RESIDENT) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -815,41 +839,30 @@ k_eval_batch(BatchArgs b, int vl) {
   }
 }
 
-// Per-case outputs of every program on cases [0, m): one wave per
-// (program, 64 cases).  In shift mode (m = 1) it stores the output at case
-// 0 as the program's shift for correlation sums.
-__device__ static void values_program(const ValuesArgs& a, int p, int64_t tile) {
+// Every program's output at case 0, where finite, as the shift of its
+// correlation sums (a non-finite one is either the whole fitness, NaN, or an
+// invalid pair of the paper's scores): one wave per program.
+__device__ static void shift_program(const ValuesArgs& a, int p) {
   const int lane = threadIdx.x;
-  const int64_t i = tile * 64 + lane;
   const ProgMeta m = a.meta[p];
-  if (m.status != BEAGLE_PROG_OK) {
-    if (!a.shift_mode && i < a.m) a.out[int64_t(p) * a.m + i] = __int_as_float(0x7FC00000);
-    return;
-  }
+  if (m.status != BEAGLE_PROG_OK) return;
   const int64_t off = a.tok_offset[p];
   const uint32_t* code = a.code + off;
   const float* cval = a.cval + off;
   const int L = m.len;
   const uint32_t vc0 = lane < L ? code[lane] : 0u;
   const float vv0 = lane < L ? cval[lane] : 0.0f;
-  const int64_t ii = i < a.m ? i : 0;
-  DirectRows rows{a.Xt + case_offset(ii, a.rows)};
+  DirectRows rows{a.Xt};
   float top[1];
   interpret<1, MAX_STACK>(vc0, vv0, code, cval, L, lane, rows, top);
-  if (a.shift_mode) {
-    // a finite shift (a non-finite output at case 0 is either the whole
-    // fitness, NaN, or an invalid pair of the paper's scores)
-    if (tile == 0 && lane == 0) a.meta[p].shift = isfinite(top[0]) ? top[0] : 0.0f;
-  } else if (i < a.m) {
-    a.out[int64_t(p) * a.m + i] = top[0];
-  }
+  if (lane == 0) a.meta[p].shift = isfinite(top[0]) ? top[0] : 0.0f;
 }
 
-__global__ void __launch_bounds__(64) k_values(ValuesArgs a) { values_program(a, blockIdx.x, blockIdx.y); }
+__global__ void __launch_bounds__(64) k_shifts(ValuesArgs a) { shift_program(a, blockIdx.x); }
 
 // Correlation shifts of every program of the table's problems of more than
 // one chunk (one wave per program; the evaluator finds the others').
-__global__ void __launch_bounds__(64) k_values_batch(BatchArgs b) {
+__global__ void __launch_bounds__(64) k_shifts_batch(BatchArgs b) {
   const int64_t g = blockIdx.x;
   const int q = batch_find(b, g, [](const BatchProblem& t) { return t.prog_begin; });
   const BatchProblem& P = b.table[q];
@@ -861,11 +874,12 @@ __global__ void __launch_bounds__(64) k_values_batch(BatchArgs b) {
   a.meta = P.prep.meta;
   a.Xt = P.Xt;
   a.rows = P.rows;
-  a.m = 1;
-  a.n_programs = P.prep.n_programs;
-  a.out = nullptr;
-  a.shift_mode = 1;
-  values_program(a, int(g - P.prog_begin), 0);
+  shift_program(a, int(g - P.prog_begin));
+}
+
+__global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int64_t M, float* out) {
+  if (meta[blockIdx.x].status == BEAGLE_PROG_OK) return;
+  for (int64_t i = threadIdx.x; i < M; i += 256) out[int64_t(blockIdx.x) * M + i] = __int_as_float(0x7FC00000);
 }
 
 // Fitness of every program from its chunk partials, summed in chunk order.
@@ -1088,6 +1102,8 @@ hipError_t launch_eval(int kind, int kv, const EvalArgs& a, hipStream_t s, hipEv
       return launch_kind<BEAGLE_FIT_CORR>(kv, a, s, ev0, ev1, counters_clear);
     case BEAGLE_FIT_POINT:
       return launch_kind<BEAGLE_FIT_POINT>(kv, a, s, ev0, ev1, counters_clear);
+    case KIND_OUTPUTS:
+      return launch_kind<KIND_OUTPUTS>(kv, a, s, ev0, ev1, counters_clear);
     default:
       return launch_kind<BEAGLE_FIT_R4>(kv, a, s, ev0, ev1, counters_clear);
   }

@@ -97,7 +97,8 @@ int64_t round_up(int64_t v, int64_t m);
 // Case chunks of one call: at most max_chunk_cases cases each (rounded up to
 // a multiple of unit, the cases one kernel iteration covers), more when the
 // population alone gives too few work items.
-void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit);
+void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit,
+                   int64_t target_blocks = 4096);
 // The evaluation's chunks (see CHUNK_CASES).
 void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
 // Whether an evaluation of N programs stages derived input rows: computing

@@ -90,6 +90,10 @@ struct StageArgs {
   float* Xt;  // [Mp / TILE][rows][TILE]
 };
 
+// Evaluation without a fitness: every case's output is written (beside the
+// library's fitness kinds).
+constexpr int KIND_OUTPUTS = 4;
+
 // Partial sums per (chunk, program) of each fitness kind (the evaluator's
 // epilogue: MSE 1, CORR 3, the paper's POINT score 1, its R4 score 7).
 __host__ __device__ constexpr int kind_sums(int kind) {
@@ -117,6 +121,7 @@ struct EvalArgs {
   int32_t n_total;                  // programs in the whole population
   int32_t prog_begin;               // first program of this launch (slice-local index 0)
   double smax = 0.0;                // the paper's scores: maximum score S
+  float* out = nullptr;             // KIND_OUTPUTS: [n_programs][M]
   // correlation and Eq. 2 in one chunk: the kernels take each program's shift
   // from their own first tile and store it here (the same array as meta)
   ProgMeta* meta_shift = nullptr;
@@ -144,10 +149,6 @@ struct ValuesArgs {
   ProgMeta* meta;
   const float* Xt;
   int32_t rows;
-  int64_t m;        // cases evaluated: [0, m)
-  int32_t n_programs;
-  float* out;       // [n_programs x m] or null (shift mode)
-  int32_t shift_mode;
 };
 
 // One problem of a batched evaluation: an entry of the device problem table.
@@ -239,17 +240,20 @@ __global__ void k_stage_and_check(StageArgs sa, PrepareArgs pa, uint32_t stage_b
 __global__ void k_prepare_batch(BatchArgs b);
 __global__ void k_stage_batch(BatchArgs b);
 __global__ void k_target_stats_batch(BatchArgs b);
-__global__ void k_values_batch(BatchArgs b);
+__global__ void k_shifts_batch(BatchArgs b);
 __global__ void k_batch_items(BatchArgs b);
 __global__ void k_finalize_batch(BatchArgs b);
 __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* __restrict__ stats);
 __global__ void k_finalize(FinalizeArgs a);
-__global__ void k_values(ValuesArgs a);
+__global__ void k_shifts(ValuesArgs a);
+// NaN rows of the invalid programs of a prediction (a workgroup per program)
+__global__ void k_nan_rows(const ProgMeta* meta, int64_t M, float* out);
 // host launchers of the templated evaluation kernels (eval.hip)
 // ev0/ev1 (may be null) are recorded on `s` right before and after the
 // fast-path kernel.
 // kv selects the tile variant of class 0.
 // counters_clear: a.work is known to be zero (else it is cleared first).
+// kind: a fitness kind or KIND_OUTPUTS.
 hipError_t launch_eval(int kind, int kv, const EvalArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                        bool counters_clear = false);
 // The work-list kernels of a batched evaluation; lists with has_items[v] == 0
