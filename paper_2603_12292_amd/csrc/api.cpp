@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -125,13 +126,18 @@ using namespace bgl::host;
 struct EvalLayout {
   size_t code, aux, vrow, cval, s_stack, s_start, s_need, owner, cowner, meta, class_count, class_list, len_list,
       long_list, work, Xt, stats, part, gpart, coef, total;
+  size_t f_tokens, f_len, f_consts, f_coff, f_cc, f_mapn, f_maps, f_mapd;  // folded programs (fold)
+  int32_t fold;                   // constant subtrees folded
   int32_t derived, rows;          // derived input rows staged; rows per staged tile
   int64_t Mp, chunk, gchunk;      // case chunks of the evaluation and of the adjoint
   int32_t n_chunks, gn_chunks, slice;
 };
 
-EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, bool derived,
+// extras: the workspace that only speed needs (derived rows, folded
+// programs); false where it does not fit.
+EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, bool extras,
                        bool with_grad = false) {
+  const bool derived = extras && !with_grad && use_derived(P->n_programs);
   EvalLayout L{};
   Carve c;
   L.derived = derived ? 1 : 0;
@@ -166,10 +172,25 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   // keep a short list from leaving most of the chip idle
   L.gchunk = 0;
   L.gn_chunks = 0;
-  if (with_grad) choose_chunks(d->M, N, &L.gchunk, &L.gn_chunks, bgl::GRAD_CHUNK_CASES, bgl::GRAD_TILE_CASES);
+  if (with_grad) choose_chunks(d->M, N, &L.gchunk, &L.gn_chunks, bgl::GRAD_CHUNK_CASES, bgl::GRAD_TILE_CASES,
+                               16384);
   L.part = c.take<double>(std::max<size_t>(size_t(n_sums) * L.n_chunks * slice, size_t(L.gn_chunks) * N));
   L.gpart = with_grad ? c.take<double>(size_t(L.gn_chunks) * std::max<int64_t>(P->n_consts, 1)) : 0;
   L.coef = with_grad ? c.take<double>(size_t(3) * N) : 0;
+  L.fold = extras && (with_grad ? d->M >= bgl::FOLD_MIN_CASES_ADJOINT
+                                : d->M >= bgl::FOLD_MIN_CASES && d->M * N >= bgl::FOLD_MIN_WORK)
+               ? 1
+               : 0;
+  if (L.fold) {
+    L.f_tokens = c.take<uint16_t>(nt);
+    L.f_len = c.take<int32_t>(N);
+    L.f_consts = c.take<float>(size_t(P->n_consts) + nt);
+    L.f_coff = c.take<int64_t>(N);
+    L.f_cc = c.take<int32_t>(N);
+    L.f_mapn = with_grad ? c.take<int32_t>(N) : 0;
+    L.f_maps = with_grad ? c.take<uint16_t>(nt) : 0;
+    L.f_mapd = with_grad ? c.take<double>(nt) : 0;
+  }
   L.total = c.used + 256;
   return L;
 }
@@ -233,6 +254,28 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   hipLaunchKernelGGL(bgl::k_stage_and_check, dim3(sgrid + pgrid), dim3(256), 0, s, sa, pa, sgrid);
   hipLaunchKernelGGL(bgl::k_layout_fill, dim3(1024), dim3(256), 0, s, pa);
   hipLaunchKernelGGL(bgl::k_layout_mark, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, pa);
+  if (L.fold) {
+    // constant subtrees folded; the decoders read the rewritten programs
+    bgl::FoldArgs fa;
+    fa.in = pa;
+    fa.tokens = reinterpret_cast<uint16_t*>(ws + L.f_tokens);
+    fa.tok_len = reinterpret_cast<int32_t*>(ws + L.f_len);
+    fa.consts = reinterpret_cast<float*>(ws + L.f_consts);
+    fa.const_offset = reinterpret_cast<int64_t*>(ws + L.f_coff);
+    fa.const_count = reinterpret_cast<int32_t*>(ws + L.f_cc);
+    fa.map_n = reinterpret_cast<int32_t*>(ws + L.f_mapn);
+    fa.map_slots = reinterpret_cast<uint16_t*>(ws + L.f_maps);
+    fa.map_der = reinterpret_cast<double*>(ws + L.f_mapd);
+    bgl::launch_fold(fa, s);
+    pa.tokens = fa.tokens;
+    pa.tok_len = fa.tok_len;
+    pa.consts = fa.consts;
+    // (slots of invalid programs may point anywhere: no valid one reads them)
+    pa.n_consts = std::numeric_limits<int64_t>::max() / 2;
+    pa.const_offset = fa.const_offset;
+    pa.const_count = fa.const_count;
+    pa.layout = nullptr;  // (checked by the fold)
+  }
   if (decoder == BEAGLE_DECODE_THREAD)
     hipLaunchKernelGGL(bgl::k_prepare, dim3((P->n_programs + 63) / 64), dim3(64), 0, s, pa);
   else {
@@ -467,9 +510,9 @@ EvalLayout capped_layout(const beagle_programs* progs, const beagle_dataset* dat
                          int32_t* slice_out) {
   const int n_sums = bgl::kind_sums(kind);
   int32_t slice = progs->n_programs;
-  EvalLayout L = eval_layout(progs, data, n_sums, slice, use_derived(progs->n_programs));
-  // without the derived rows where they do not fit (the same values)
-  if (cap && L.total > cap && L.derived) L = eval_layout(progs, data, n_sums, slice, false);
+  EvalLayout L = eval_layout(progs, data, n_sums, slice, true);
+  // without the extras where they do not fit (the same values)
+  if (cap && L.total > cap) L = eval_layout(progs, data, n_sums, slice, false);
   while (cap && L.total > cap && slice > 1) {
     slice = (slice + 1) / 2;
     L = eval_layout(progs, data, n_sums, slice, false);
@@ -661,9 +704,7 @@ beagle_status beagle_eval_workspace_size(const beagle_programs* progs, const bea
   if (st != BEAGLE_OK) return st;
   st = check_data(data, kind);
   if (st != BEAGLE_OK) return st;
-  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1),
-                       use_derived(progs->n_programs))
-               .total;
+  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1), true).total;
   return BEAGLE_OK;
 }
 
@@ -682,7 +723,7 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  EvalLayout L = eval_layout(progs, data, 1, 1, use_derived(progs->n_programs));
+  EvalLayout L = eval_layout(progs, data, 1, 1, true);
   if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, 1, 1, false);
   // (outputs depend on no chunk: several work items per wave even for a few
   // programs, so that the waves end together)
@@ -979,7 +1020,8 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool corr = kind == BEAGLE_FIT_CORR;
-  EvalLayout L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, false, true);
+  EvalLayout L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, true, true);
+  if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, false, true);
   st = reserve(ctx, L.total);
   if (st != BEAGLE_OK) return st;
   hipEvent_t join = nullptr;
@@ -1003,8 +1045,8 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   ga.cval = reinterpret_cast<const float*>(ws + L.cval);
   ga.tok_offset = progs->tok_offset;
   ga.meta = reinterpret_cast<const bgl::ProgMeta*>(ws + L.meta);
-  ga.const_offset = progs->const_offset;
-  ga.const_count = progs->const_count;
+  ga.const_offset = progs->const_offset;  // (the partial gradients' layout)
+  ga.const_count = L.fold ? reinterpret_cast<const int32_t*>(ws + L.f_cc) : progs->const_count;
   ga.Xt = reinterpret_cast<const float*>(ws + L.Xt);
   ga.rows = L.rows;
   ga.M = data->M;
@@ -1029,6 +1071,10 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   fa.gpart = ga.gpart;
   fa.const_offset = progs->const_offset;
   fa.const_count = progs->const_count;
+  fa.tok_offset = progs->tok_offset;
+  fa.map_n = L.fold ? reinterpret_cast<const int32_t*>(ws + L.f_mapn) : nullptr;
+  fa.map_slots = reinterpret_cast<const uint16_t*>(ws + L.f_maps);
+  fa.map_der = reinterpret_cast<const double*>(ws + L.f_mapd);
   fa.M = data->M;
   fa.n_consts = progs->n_consts;
   fa.n_programs = progs->n_programs;

@@ -27,8 +27,6 @@ constexpr int GRAD_LANE_SLOTS = 8;
 // tile of every adjoint kernel covers
 constexpr int64_t GRAD_CHUNK_CASES = 1024;
 constexpr int64_t GRAD_TILE_CASES = 256;
-// work items a wave claims per atomic in the adjoint kernels
-constexpr int GRAD_BATCH = 4;
 
 // Reverse handler of a decoded word in the derivative-tape adjoint (bits
 // 24..31 of the word's aux entry).  n is the stack size before the word in
@@ -101,6 +99,12 @@ struct GradFinalizeArgs {
   const double* gpart;
   const int64_t* const_offset;
   const int32_t* const_count;
+  const int64_t* tok_offset;
+  // folded constants (kernels.h, FoldArgs; map_n null: none): the partial
+  // gradients are those of the folded constants
+  const int32_t* map_n;
+  const uint16_t* map_slots;
+  const double* map_der;
   int64_t M;
   int64_t n_consts;
   int32_t n_programs;

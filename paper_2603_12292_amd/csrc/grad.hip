@@ -24,46 +24,15 @@
 // wave (slots >= 8), reduced in a fixed order and written as per-chunk
 // partials; a finalize kernel sums the chunks in order.
 #include "beagle_device.h"
+#include "deriv.h"
 #include "grad.h"
 #include "trig.h"
+#include "wave_items.h"
 
 namespace bgl {
 
 constexpr int GRAD_S = MAX_STACK;
 constexpr int LANE_SLOTS = GRAD_LANE_SLOTS;  // constant slots accumulated per lane
-
-template <uint32_t O>
-__device__ __forceinline__ float gbinop(float a, float b) {
-  if constexpr (O == B_ADD) return a + b;
-  if constexpr (O == B_SUB) return a - b;
-  if constexpr (O == B_MUL) return a * b;
-  if constexpr (O == B_DIV) return op_div(a, b);
-  if constexpr (O == B_RSUB) return b - a;
-  if constexpr (O == B_RDIV) return op_div(b, a);
-  return 0.0f;
-}
-
-// partial derivatives of binop<O>(A, B): (d/dA, d/dB); 0 where a protected
-// division replaces the quotient by 1
-template <uint32_t O>
-__device__ __forceinline__ void dbinop(float A, float B, float& dA, float& dB) {
-  if constexpr (O == B_ADD) { dA = 1.0f; dB = 1.0f; }
-  if constexpr (O == B_SUB) { dA = 1.0f; dB = -1.0f; }
-  if constexpr (O == B_MUL) { dA = B; dB = A; }
-  if constexpr (O == B_DIV) {
-    const bool nz = B != 0.0f;
-    const float r = __builtin_amdgcn_rcpf(nz ? B : 1.0f);
-    dA = nz ? r : 0.0f;
-    dB = nz ? -A * r * r : 0.0f;
-  }
-  if constexpr (O == B_RSUB) { dA = -1.0f; dB = 1.0f; }
-  if constexpr (O == B_RDIV) {
-    const bool nz = A != 0.0f;
-    const float r = __builtin_amdgcn_rcpf(nz ? A : 1.0f);
-    dA = nz ? -B * r * r : 0.0f;
-    dB = nz ? r : 0.0f;
-  }
-}
 
 // binop<O> and its partial derivatives on G cases per lane: the protected
 // quotients through div_tile_r, whose reciprocal the derivatives reuse
@@ -108,38 +77,6 @@ __device__ __forceinline__ void binop_tile_g(const float (&A)[G], const float (&
   } else {
 #pragma unroll
     for (int k = 0; k < G; ++k) q[k] = gbinop<O>(A[k], B[k]);
-  }
-}
-
-// sin (COS = false) or cos of one value per lane, the interpreter's functions
-template <bool COS>
-__device__ __forceinline__ float trig1(float x) {
-  float v[1] = {x};
-  trig_tile<COS, 1>(v);
-  return v[0];
-}
-
-// d/dx of unary operator u at operand x with value y
-__device__ __forceinline__ float dunary(uint32_t u, float x, float y) {
-  switch (u) {
-    case 0: return trig1<true>(x);
-    case 1: return -trig1<false>(x);
-    case 2: return (x > 80.0f || x < -80.0f) ? 0.0f : y;
-    case 3: return x != 0.0f ? __builtin_amdgcn_rcpf(x) : 0.0f;
-    case 4: return x != 0.0f ? copysignf(0.5f, x) * __builtin_amdgcn_rcpf(y) : 0.0f;
-    case 5: return 2.0f * x;
-    case 6: return -(y * y);
-    case 7: return 1.0f + y * y;
-    case 8: return rsqrtf((1.0f - x) * (1.0f + x));
-    case 9: return -rsqrtf((1.0f - x) * (1.0f + x));
-    case 10: return 1.0f / (1.0f + x * x);
-    default: {
-      // tanh: sech^2 x = 4e / (1 + e)^2 with e = exp(-2|x|) (1 - y^2 cancels
-      // where tanh saturates)
-      const float e = op_exp(-2.0f * __builtin_fabsf(x));
-      const float ep = 1.0f + e;
-      return (4.0f * e) / (ep * ep);
-    }
   }
 }
 
@@ -442,26 +379,15 @@ __global__ void __launch_bounds__(64) k_grad(GradArgs a) {
   const int32_t count = a.list_count[LONG ? 1 : 0];
   const int64_t items = int64_t(count) * a.n_chunks;
   const int32_t* list = a.list + (LONG ? int64_t(a.n_programs) : 0);
-  // waves beyond the item batches leave at once (no atomic on a short list)
-  if (int64_t(blockIdx.x) * GRAD_BATCH >= items) return;
+  // waves beyond the items leave at once (no atomic on a short list)
+  if (int64_t(blockIdx.x) >= items) return;
+  WaveItems work(items, a.work + (LONG ? 1 : 0), 1);
   for (;;) {
-    // as in k_grad_dtape: every lane in the atomic, a batch per atomic
-    const unsigned long long it =
-        atomicAdd(a.work + (LONG ? 1 : 0), threadIdx.x == 0 ? (unsigned long long)GRAD_BATCH : 0ull);
-    const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(it), 0);
-    const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(it >> 32), 0);
-    const int64_t first = int64_t((uint64_t(hi) << 32) | lo);
-    if (first >= items) break;
-    const int n = int(first + GRAD_BATCH < items ? GRAD_BATCH : items - first);
-    int c = int(first / count), i = int(first - int64_t(c) * count);
-    for (int k = 0; k < n; ++k) {
-      const int p = __builtin_amdgcn_readfirstlane(list[i]);
-      grad_item<LONG>(a, p, c, lds);
-      if (++i == count) {
-        i = 0;
-        ++c;
-      }
-    }
+    const int64_t it = work.next();
+    if (it < 0) break;
+    const int c = int(it / count);
+    const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count]);
+    grad_item<LONG>(a, p, c, lds);
   }
 }
 
@@ -971,33 +897,19 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIST ==
   const int32_t count = a.list_count[LIST];
   const int64_t items = int64_t(count) * a.n_chunks;
   const int32_t* list = a.list + LIST * int64_t(a.n_programs);
-  if (int64_t(blockIdx.x) * GRAD_BATCH >= items) return;  // (as in k_grad)
+  if (int64_t(blockIdx.x) >= items) return;  // (as in k_grad)
+  WaveItems work(items, a.work + LIST, 1);
   for (;;) {
-    // every lane takes part (lane 0 adds GRAD_BATCH): no divergent branch in
-    // the persistent loop, the first item read from lane 0 explicitly; a
-    // batch of items per atomic (one same-address atomic per item would
-    // serialise at the counter)
-    const unsigned long long it = atomicAdd(a.work + LIST, threadIdx.x == 0 ? (unsigned long long)GRAD_BATCH : 0ull);
-    const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(it), 0);
-    const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(it >> 32), 0);
-    const int64_t first = int64_t((uint64_t(hi) << 32) | lo);
-    if (first >= items) break;
-    const int n = int(first + GRAD_BATCH < items ? GRAD_BATCH : items - first);
-    // item = c * count + i, stepped without a division per item
-    int c = int(first / count), i = int(first - int64_t(c) * count);
-    for (int k = 0; k < n; ++k) {
-      const int p = __builtin_amdgcn_readfirstlane(list[i]);
-      dtape_list_item<LIST>(a, p, c, lds);
-      if (++i == count) {
-        i = 0;
-        ++c;
-      }
-    }
+    const int64_t it = work.next();
+    if (it < 0) break;
+    const int c = int(it / count);
+    const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count]);
+    dtape_list_item<LIST>(a, p, c, lds);
   }
 }
 #undef BGL_K
 
-// One wave per program: lane 0 sums the fitness partials, lane j the
+// One wave per program (a workgroup): lane 0 sums the fitness partials, lane j the
 // gradient partials of constant slot j (and j + 64, ...), each over the
 // chunks in chunk order.
 __global__ void __launch_bounds__(64) k_grad_finalize(GradFinalizeArgs a) {
@@ -1018,10 +930,33 @@ __global__ void __launch_bounds__(64) k_grad_finalize(GradFinalizeArgs a) {
     for (int c = 0; c < a.n_chunks; ++c) s += a.part[int64_t(c) * a.n_programs + p];
     a.fitness[p] = s / double(a.M);
   }
-  for (int j = lane; j < cc; j += 64) {
+  const int n_map = a.map_n ? a.map_n[p] : 0;
+  if (n_map == 0) {
+    for (int j = lane; j < cc; j += 64) {
+      double g = 0.0;
+#pragma unroll 8
+      for (int c = 0; c < a.n_chunks; ++c) g += a.gpart[int64_t(c) * a.n_consts + coff + j];
+      a.grad[coff + j] = float(g);
+    }
+    return;
+  }
+  // a folded program (at most 64 CONST tokens): lane e takes entry e's folded
+  // constant times its derivative, slot j sums its entries in token order
+  __shared__ double term[64];
+  __shared__ int slot[64];
+  if (lane < n_map) {
+    const int64_t off = a.tok_offset[p];
+    const uint32_t ms = a.map_slots[off + lane];
     double g = 0.0;
 #pragma unroll 8
-    for (int c = 0; c < a.n_chunks; ++c) g += a.gpart[int64_t(c) * a.n_consts + coff + j];
+    for (int c = 0; c < a.n_chunks; ++c) g += a.gpart[int64_t(c) * a.n_consts + coff + (ms >> 8)];
+    term[lane] = g * a.map_der[off + lane];
+    slot[lane] = int(ms & 0xFFu);
+  }
+  __syncthreads();
+  for (int j = lane; j < cc; j += 64) {
+    double g = 0.0;
+    for (int e = 0; e < n_map; ++e) g += slot[e] == j ? term[e] : 0.0;
     a.grad[coff + j] = float(g);
   }
 }
@@ -1042,31 +977,26 @@ size_t grad_lds_bytes(int D, bool long_tape) {
   return b;
 }
 
-hipError_t launch_grad(const GradArgs& a, hipStream_t s) {
-  const int cus = grad_cu_count();
-  const size_t l0 = grad_lds_bytes(a.D, false), l1 = grad_lds_bytes(a.D, true);
-  const size_t l2 = size_t(a.D) * dtape_cases(2) * 64 * sizeof(float) + size_t(LANE_SLOTS) * 64 * sizeof(double);
-  const size_t l3 = size_t(a.D) * dtape_cases(3) * 64 * sizeof(float) + size_t(LANE_SLOTS) * 64 * sizeof(double);
-  int nb0 = 0, nb1 = 0, nb2 = 0, nb3 = 0, nb4 = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb0, k_grad<false>, 64, l0) != hipSuccess || nb0 < 1) nb0 = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb1, k_grad<true>, 64, l1) != hipSuccess || nb1 < 1) nb1 = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb2, k_grad_dtape<2>, 64, l2) != hipSuccess || nb2 < 1) nb2 = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb3, k_grad_dtape<3>, 64, l3) != hipSuccess || nb3 < 1) nb3 = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb4, k_grad_dtape<4>, 64, l3) != hipSuccess || nb4 < 1) nb4 = 1;
-  hipLaunchKernelGGL(k_grad_dtape<2>, dim3(nb2 * cus), dim3(64), l2, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_grad_dtape<3>, dim3(nb3 * cus), dim3(64), l3, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_grad_dtape<4>, dim3(nb4 * cus), dim3(64), l3, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_grad<false>, dim3(nb0 * cus), dim3(64), l0, s, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_grad<true>, dim3(nb1 * cus), dim3(64), l1, s, a);
+// One list's kernel over its persistent grid (resident workgroups per CU,
+// times the CUs).
+template <class Kernel>
+static hipError_t launch_list(Kernel k, const GradArgs& a, size_t lds, hipStream_t s) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 64, lds) != hipSuccess || nb < 1) nb = 1;
+  hipLaunchKernelGGL(k, dim3(nb * grad_cu_count()), dim3(64), lds, s, a);
   return hipGetLastError();
+}
+
+hipError_t launch_grad(const GradArgs& a, hipStream_t s) {
+  auto dtape_lds = [&](int list) {
+    return size_t(a.D) * dtape_cases(list) * 64 * sizeof(float) + size_t(LANE_SLOTS) * 64 * sizeof(double);
+  };
+  hipError_t e = launch_list(k_grad_dtape<2>, a, dtape_lds(2), s);
+  if (e == hipSuccess) e = launch_list(k_grad_dtape<3>, a, dtape_lds(3), s);
+  if (e == hipSuccess) e = launch_list(k_grad_dtape<4>, a, dtape_lds(4), s);
+  if (e == hipSuccess) e = launch_list(k_grad<false>, a, grad_lds_bytes(a.D, false), s);
+  if (e == hipSuccess) e = launch_list(k_grad<true>, a, grad_lds_bytes(a.D, true), s);
+  return e;
 }
 
 }  // namespace bgl

@@ -60,6 +60,25 @@ struct PrepareArgs {
   int32_t wave_programs;
 };
 
+// Folding of constant subtrees (fold.hip): the rewritten programs, at their
+// own token offsets, and their constants behind room for the caller's (copied
+// for the programs that are kept as they are).
+struct FoldArgs {
+  PrepareArgs in;         // the caller's programs and the ranges check's results
+  uint16_t* tokens;       // [n_tokens]
+  int32_t* tok_len;       // [n_programs]; -1: the ranges check failed
+  float* consts;          // [n_consts + n_tokens]
+  int64_t* const_offset;  // [n_programs]
+  int32_t* const_count;   // [n_programs]
+  // adjoint: per program, map_n entries at its token offset, one per CONST
+  // token: original slot | folded slot << 8, and the derivative (map_n = 0:
+  // a program kept as it is)
+  int32_t* map_n;
+  uint16_t* map_slots;
+  double* map_der;
+};
+void launch_fold(const FoldArgs& f, hipStream_t s);
+
 // Staged cases: tiles of TILE cases, row-major within a tile (`rows` rows of
 // TILE cases: the D variables, the derived rows when there are any, the
 // targets last), so that a row of a tile is one run of 2 KB and a tile's rows
@@ -217,6 +236,12 @@ constexpr int64_t CHUNK_UNIT = 256;
 // many programs.
 constexpr size_t RESIDENT_MAX_BYTES = 158 * 1024;
 constexpr int32_t RESIDENT_MIN_PROGRAMS = 4096;
+// Cases from which constant subtrees are folded: the fold costs a program a
+// few hundred instructions, and saves about a hundred per 512 cases of an
+// evaluation, three times that of a gradient.
+constexpr int64_t FOLD_MIN_CASES = 2048;
+constexpr int64_t FOLD_MIN_WORK = int64_t(1) << 26;  // programs x cases that repay its launch
+constexpr int64_t FOLD_MIN_CASES_ADJOINT = 512;
 constexpr int64_t CLAIM_MAX = 16;  // work items of one claim at most
 __host__ __device__ constexpr int class_k(int c, int kv) { return c == 0 ? (kv == 0 ? 8 : 4) : 4; }
 
