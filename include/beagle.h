@@ -255,7 +255,9 @@ typedef enum { BEAGLE_TUNE_AUTO = 0, BEAGLE_TUNE_WIDE = 1, BEAGLE_TUNE_NARROW = 
  * (BEAGLE_TUNE_NARROW).  BEAGLE_TUNE_AUTO, the
  * default, times both the first time an evaluation meets a problem-shape
  * bucket (fitness kind, D, log2 M, log2 of the mean program length) -- that
- * call synchronises the device -- and keeps the faster in the context.  When
+ * call synchronises the device -- and keeps the faster in the context (calls
+ * of few programs on few cases take one launch of one width and measure
+ * nothing).  When
  * the environment variable BEAGLE_AUTOTUNE_CACHE names a file, buckets are
  * read from it when a context is created and every new measurement is
  * written back to it.  The choice changes no result bit: with either width a

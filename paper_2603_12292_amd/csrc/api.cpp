@@ -234,8 +234,9 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   pa.long_count = reinterpret_cast<int32_t*>(ws + L.class_count) + 16;
   pa.long_list = reinterpret_cast<int32_t*>(ws + L.long_list);
   pa.layout = reinterpret_cast<int32_t*>(ws + L.class_count) + 32;
-  pa.owner = reinterpret_cast<int32_t*>(ws + L.owner);
-  pa.cowner = adjoint ? reinterpret_cast<int32_t*>(ws + L.cowner) : nullptr;
+  const bool owners = P->n_programs >= bgl::OWNER_MIN_PROGRAMS;
+  pa.owner = owners ? reinterpret_cast<int32_t*>(ws + L.owner) : nullptr;
+  pa.cowner = owners && adjoint ? reinterpret_cast<int32_t*>(ws + L.cowner) : nullptr;
   pa.wave_programs = 64;
   bgl::StageArgs sa;
   sa.X = d->X;
@@ -252,8 +253,10 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   const int64_t sthreads = L.Mp * d->D <= (1 << 18) ? L.Mp * d->D : L.Mp;  // (as k_stage_and_check splits)
   const uint32_t sgrid = uint32_t(std::min<int64_t>((sthreads + 255) / 256, 1 << 16));
   hipLaunchKernelGGL(bgl::k_stage_and_check, dim3(sgrid + pgrid), dim3(256), 0, s, sa, pa, sgrid);
-  hipLaunchKernelGGL(bgl::k_layout_fill, dim3(1024), dim3(256), 0, s, pa);
-  hipLaunchKernelGGL(bgl::k_layout_mark, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, pa);
+  if (owners) {
+    hipLaunchKernelGGL(bgl::k_layout_fill, dim3(1024), dim3(256), 0, s, pa);
+    hipLaunchKernelGGL(bgl::k_layout_mark, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, pa);
+  }
   if (L.fold) {
     // constant subtrees folded; the decoders read the rewritten programs
     bgl::FoldArgs fa;
@@ -317,11 +320,14 @@ beagle_status launch_shifts(char* ws, const beagle_programs* P, const EvalLayout
 // `stats`.  They read nothing else, so with a context they run on its side
 // stream (default priority), forked from s here and beside the decoding and
 // staging that follow on s; *join is then the event s waits for before the
-// statistics are read.  Without a context they run on s (*join = null).
+// statistics are read.  Without a context, and on few cases, where they take
+// less than the two events (5 against about 10 us), they run on s (*join =
+// null).
 beagle_status launch_target_stats(beagle_ctx* ctx, const beagle_dataset* data, double* stats, hipStream_t s,
                                   hipEvent_t* join) {
   *join = nullptr;
   hipStream_t t = s;
+  if (data->M <= 8192) ctx = nullptr;
   if (ctx) {
     if (!ctx->side) {
       hipStream_t ns = nullptr;
@@ -560,7 +566,7 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
   // the work counters are clear for the first launch unless the tuner's
   // timed runs used them
   bool counters_clear = true;
-  if (ctx) {
+  if (ctx && !bgl::mixed_launch(progs->n_programs, L.n_chunks)) {
     counters_clear = known_tile_variant(ctx, kind, data->D, data->M,
                                         double(progs->n_tokens) / progs->n_programs, &kv);
     TuneSlice ts{kind, slice_args(0, std::min(slice, progs->n_programs))};
@@ -979,8 +985,9 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   const bgl::EvalArgs ea = eval_args(ws, L, progs, data, shift_in_kernel);
   int kv = 0;
   TuneSlice ts{BEAGLE_FIT_CORR, ea};
-  st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s,
-                    run_slice, &ts, &kv);
+  if (!bgl::mixed_launch(progs->n_programs, L.n_chunks))
+    st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s,
+                      run_slice, &ts, &kv);
   if (st != BEAGLE_OK) return st;
   hipError_t e = bgl::launch_eval(BEAGLE_FIT_CORR, kv, ea, s, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(e, "eval launch");

@@ -48,6 +48,7 @@ constexpr size_t MAX_GRAPHS = 8;
 struct Batch {
   bgl::BatchArgs args;
   int has[bgl::N_LISTS];
+  bool owners = false;  // some problem's ranges check uses the owner arrays
   int64_t n_programs = 0, n_cases = 0;
   int n = 0;
 };
@@ -57,8 +58,10 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   zero_i32(counts, int64_t(64) * b.n, s);
   const uint32_t pgrid = uint32_t((b.n_programs + 255) / 256);
   hipLaunchKernelGGL(bgl::k_layout_check_batch, dim3(pgrid), dim3(256), 0, s, b.args);
-  hipLaunchKernelGGL(bgl::k_layout_fill_batch, dim3(64, uint32_t(b.n)), dim3(256), 0, s, b.args);
-  hipLaunchKernelGGL(bgl::k_layout_mark_batch, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, b.args);
+  if (b.owners) {
+    hipLaunchKernelGGL(bgl::k_layout_fill_batch, dim3(64, uint32_t(b.n)), dim3(256), 0, s, b.args);
+    hipLaunchKernelGGL(bgl::k_layout_mark_batch, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, b.args);
+  }
   hipLaunchKernelGGL(bgl::k_prepare_batch, dim3(uint32_t((b.n_programs + 63) / 64)), dim3(64), 0, s, b.args);
   hipLaunchKernelGGL(bgl::k_stage_batch, dim3(uint32_t((b.n_cases + 255) / 256)), dim3(256), 0, s, b.args);
   if (b.args.kind == BEAGLE_FIT_CORR) {
@@ -107,6 +110,15 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   for (int q : active) {
     const double mean_len = double(progs[q].n_tokens) / progs[q].n_programs;
     if (!known_tile_variant(ctx, kind, data[q].D, data[q].M, mean_len, &kv[q])) {
+      int64_t chunk = 0;
+      int32_t n_chunks = 0;
+      eval_chunks(data[q].M, progs[q].n_programs, &chunk, &n_chunks);
+      if (bgl::mixed_launch(progs[q].n_programs, n_chunks)) {
+        // too few work items alone to be measured: the wide tile, which is the
+        // faster one wherever chunks hold whole tiles
+        kv[q] = 0;
+        continue;
+      }
       beagle_status st = beagle_eval(ctx, &progs[q], &data[q], kind, fitness[q], status ? status[q] : nullptr,
                                      stream);
       if (st != BEAGLE_OK) return st;
@@ -214,7 +226,8 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     pa.long_count = nullptr;  // k_prepare_batch decodes every program itself
     pa.long_list = nullptr;
     pa.layout = counts + int64_t(64) * i + 32;
-    pa.owner = reinterpret_cast<int32_t*>(ws + o.owner);
+    pa.owner = P.n_programs >= bgl::OWNER_MIN_PROGRAMS ? reinterpret_cast<int32_t*>(ws + o.owner) : nullptr;
+    b.owners |= pa.owner != nullptr;
     pa.cowner = nullptr;
     pa.wave_programs = 64;
     t.X = d.X;

@@ -264,7 +264,14 @@ __device__ __forceinline__ void interpret(uint32_t vc0, float vv0, const uint32_
                                           int L, int lane, Rows& rows, float (&top)[K]) {
   // S slots: the unconditional store of a token at stack size n = S lands in
   // slot S-1, above the S-1 live values
-  float stk[K][S];
+  // (at S = 16 an array per case: one of all cases would be too large to be
+  // indexed in registers; at S = 8 one array is a third faster)
+  static_assert(K <= 4, "at most four cases per lane");
+  constexpr bool ONE = S <= 8;
+  float all[ONE ? K : 1][S];
+  float s0[ONE ? 1 : S], s1[ONE ? 1 : S], s2[ONE ? 1 : S], s3[ONE ? 1 : S];
+  float* const stk[4] = {ONE ? all[0] : s0, ONE ? all[K > 1 ? 1 : 0] : s1, ONE ? all[K > 2 ? 2 : 0] : s2,
+                         ONE ? all[K > 3 ? 3 : 0] : s3};
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     top[k] = 0.0f;
@@ -671,7 +678,7 @@ __device__ __forceinline__ void eval_wave(const EvalArgs& a, int p, int c, float
 // chunk of cases in L2.  Which wave takes which item does not change any
 // result: each item writes its own partial.
 template <int KIND, int CLS, int KV>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : CLASS0_WIDE_WAVES) : CLS == 1 ? 4 : 2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : CLASS0_WIDE_WAVES) : CLS == 1 ? 4 : 1)))
 k_eval_class(EvalArgs a) {
   constexpr int S = class_stack(CLS);
   constexpr int K = class_k(CLS, KV);
@@ -690,6 +697,34 @@ k_eval_class(EvalArgs a) {
     const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count] - a.prog_begin);
     // (else a program of another slice)
     if (p >= 0 && p < a.n_programs) eval_wave<KIND, K, S, false>(a, p, c, ring);
+  }
+}
+
+// All register-need classes in one launch, for few work items.
+template <int KIND>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) k_eval_mixed(EvalArgs a) {
+  __shared__ __align__(16) float rings[EVAL_WAVES][RING * 4 * 64];
+  const int32_t n0 = __builtin_amdgcn_readfirstlane(a.class_count[0]);
+  const int32_t n01 = n0 + __builtin_amdgcn_readfirstlane(a.class_count[1]);
+  const int32_t count = n01 + __builtin_amdgcn_readfirstlane(a.class_count[2]);
+  const int64_t items = int64_t(count) * a.n_chunks;
+  if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;
+  float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
+  WaveItems work(items, a.work, 1);
+  for (;;) {
+    const int64_t it = work.next();
+    if (it < 0) break;
+    const int c = int(it / count), i = int(it - int64_t(c) * count);
+    const int cls = i < n0 ? 0 : i < n01 ? 1 : 2;
+    const int p = __builtin_amdgcn_readfirstlane(
+        a.class_list[int64_t(cls) * a.n_total + i - (cls == 0 ? 0 : cls == 1 ? n0 : n01)] - a.prog_begin);
+    if (p < 0 || p >= a.n_programs) continue;  // a program of another slice
+    if (cls == 0)
+      eval_wave<KIND, 4, 4, false>(a, p, c, ring);
+    else if (cls == 1)
+      eval_wave<KIND, 4, 8, false>(a, p, c, ring);
+    else
+      eval_wave<KIND, 4, 16, false>(a, p, c, ring);
   }
 }
 
@@ -729,7 +764,7 @@ k_eval_resident(EvalArgs a) {
 // problem is found by stepping forward from there when it is near, by
 // bisection otherwise.
 template <int KIND, int CLS, int KV>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : BATCH_WIDE_WAVES) : CLS == 1 ? 4 : 2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CLS == 0 ? (KV == 1 ? CLASS0_NARROW_WAVES : BATCH_WIDE_WAVES) : CLS == 1 ? 4 : 1)))
 k_eval_batch(BatchArgs b, int vl) {
   constexpr int S = class_stack(CLS);
   constexpr int K = class_k(CLS, KV);
@@ -1035,6 +1070,14 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
     if (e != hipSuccess) return e;
     if ((e = launch_resident<KIND, 4, 1>(a, s)) != hipSuccess) return e;
     return launch_class<KIND, 2, 0>(a, s);
+  }
+  if (mixed_launch(a.n_total, a.n_chunks)) {
+    const int grid = int((int64_t(a.n_total) * a.n_chunks + EVAL_WAVES - 1) / EVAL_WAVES);
+    if (ev0 || ev1)
+      hipExtLaunchKernelGGL(k_eval_mixed<KIND>, dim3(grid), dim3(256), 0, s, ev0, ev1, 0u, a);
+    else
+      hipLaunchKernelGGL(k_eval_mixed<KIND>, dim3(grid), dim3(256), 0, s, a);
+    return hipGetLastError();
   }
   e = wide ? launch_class<KIND, 0, 0>(a, s, ev0, ev1) : launch_class<KIND, 0, 1>(a, s, ev0, ev1);
   if (e != hipSuccess) return e;

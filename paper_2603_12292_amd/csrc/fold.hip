@@ -27,6 +27,7 @@
 #include "beagle_device.h"
 #include "deriv.h"
 #include "kernels.h"
+#include "layout.h"
 
 namespace bgl {
 
@@ -121,10 +122,14 @@ __global__ void __launch_bounds__(256) k_fold(FoldArgs f) {
   } else {
     // ownership of the ranges where they are not sorted and disjoint
     bool mine = true;
-    if (a.layout[0])
+    if (!a.owner) {
+      if (a.layout[0] | a.layout[1])
+        for (int q0 = 0; q0 < p && mine; q0 += 64)
+          mine = __builtin_amdgcn_ballot_w64(q0 + lane < p && overlaps(a, q0 + lane, off, L0, coff, cc)) == 0;
+    } else if (a.layout[0])
       for (int32_t j0 = 0; j0 < L0 && mine; j0 += 64)
         mine = __builtin_amdgcn_ballot_w64(j0 + lane < L0 && a.owner[off + j0 + lane] != p) == 0;
-    if (ADJ && mine && a.layout[1])
+    if (ADJ && a.owner && mine && a.layout[1])
       for (int32_t j0 = 0; j0 < cc && mine; j0 += 64)
         mine = __builtin_amdgcn_ballot_w64(j0 + lane < cc && a.cowner[coff + j0 + lane] != p) == 0;
     if (!mine && L0 > 0) out_len = -1;

@@ -53,6 +53,8 @@ struct PrepareArgs {
   // then owner / cowner hold, per token / constant slot, the lowest index of
   // a program whose range covers it, and a program finding another index in
   // its range gets BEAGLE_PROG_BAD_LAYOUT.
+  // On few programs (OWNER_MIN_PROGRAMS) owner and cowner are null and each
+  // program of a flagged layout looks through the lower-indexed ones itself.
   int32_t* layout;
   int32_t* owner;   // [n_tokens]
   int32_t* cowner;  // [n_consts] (adjoint only)
@@ -220,6 +222,9 @@ __device__ __forceinline__ int batch_find(const BatchArgs& b, int64_t x, F field
   return lo;
 }
 
+// programs from which the owner arrays are filled: two launches, for a check
+// that otherwise reads every lower-indexed header only where a layout is flagged
+constexpr int32_t OWNER_MIN_PROGRAMS = 4097;
 constexpr int EVAL_WAVES = 4;
 // rows a wave keeps in flight: two are enough behind the other waves of a
 // SIMD, and four cost the fifth of them (the workgroup's 32 KB leave room for
@@ -242,6 +247,12 @@ constexpr int32_t RESIDENT_MIN_PROGRAMS = 4096;
 constexpr int64_t FOLD_MIN_CASES = 2048;
 constexpr int64_t FOLD_MIN_WORK = int64_t(1) << 26;  // programs x cases that repay its launch
 constexpr int64_t FOLD_MIN_CASES_ADJOINT = 512;
+// Work items (programs x chunks) up to which one launch runs all register-need
+// classes (its registers allow three waves per SIMD): two launches fewer count
+// for more there than the waves.
+constexpr int64_t MIXED_MAX_ITEMS = 4096;
+// (that launch has one tile width: nothing to tune)
+inline bool mixed_launch(int64_t n_programs, int64_t n_chunks) { return n_programs * n_chunks <= MIXED_MAX_ITEMS; }
 constexpr int64_t CLAIM_MAX = 16;  // work items of one claim at most
 __host__ __device__ constexpr int class_k(int c, int kv) { return c == 0 ? (kv == 0 ? 8 : 4) : 4; }
 

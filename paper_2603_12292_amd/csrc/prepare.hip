@@ -5,6 +5,7 @@
 #include "beagle_device.h"
 #include "grad.h"
 #include "kernels.h"
+#include "layout.h"
 #include "trig.h"
 
 namespace bgl {
@@ -91,7 +92,12 @@ struct ListIds {
 // else when every slot of its ranges carries its own index as the lowest
 // covering one (see PrepareArgs::layout).
 __device__ static bool owns_ranges(const PrepareArgs& a, int p, int64_t off, int32_t L, int64_t coff, int32_t cc) {
-  if (!a.layout) return true;
+  if (!a.layout || !(a.layout[0] | a.layout[1])) return true;
+  if (!a.owner) {
+    for (int q = 0; q < p; ++q)
+      if (overlaps(a, q, off, L, coff, cc)) return false;
+    return true;
+  }
   if (a.layout[0])
     for (int32_t i = 0; i < L; ++i)
       if (a.owner[off + i] != p) return false;
@@ -643,8 +649,11 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
   if (status == BEAGLE_PROG_OK && (lay_tok | lay_const)) {
     // ranges not sorted and disjoint: every slot must carry p as its owner
     bool mine = true;
-    if (lay_tok) mine = __builtin_amdgcn_ballot_w64(lane < L && a.owner[off + lane] != p) == 0;
-    if (ADJ && mine && lay_const)
+    if (!a.owner) {
+      for (int q0 = 0; q0 < p && mine; q0 += 64)
+        mine = __builtin_amdgcn_ballot_w64(q0 + lane < p && overlaps(a, q0 + lane, off, L, coff, cc)) == 0;
+    } else if (lay_tok) mine = __builtin_amdgcn_ballot_w64(lane < L && a.owner[off + lane] != p) == 0;
+    if (ADJ && mine && lay_const && a.owner)
       for (int32_t j0 = 0; j0 < cc && mine; j0 += 64)
         mine = __builtin_amdgcn_ballot_w64(j0 + lane < cc && a.cowner[coff + j0 + lane] != p) == 0;
     if (!mine) status = BEAGLE_PROG_BAD_LAYOUT;
@@ -1321,20 +1330,6 @@ template __global__ void k_prepare_wave<false>(PrepareArgs a);
 template __global__ void k_prepare_wave<true>(PrepareArgs a);
 
 // ---- disjoint-ranges check -------------------------------------------------
-// Token range of program p when it lies within the token array (else
-// false: the program is rejected by the layout checks of the decoder).
-__device__ static bool tok_range(const PrepareArgs& a, int p, int64_t& off, int32_t& L) {
-  off = a.tok_offset[p];
-  L = a.tok_len[p];
-  return L >= 0 && L <= MAX_LEN && off >= 0 && off + L <= a.n_tokens;
-}
-
-__device__ static bool const_range(const PrepareArgs& a, int p, int64_t& off, int32_t& n) {
-  off = a.const_offset[p];
-  n = a.const_count[p];
-  return n >= 0 && (n == 0 || (off >= 0 && off + n <= a.n_consts));
-}
-
 // Program p against program p + 1: ranges out of order, overlapping, or out
 // of bounds (conservatively) set the flag.
 __device__ static void layout_pair(const PrepareArgs& a, int p) {
@@ -1352,6 +1347,7 @@ __device__ static void layout_pair(const PrepareArgs& a, int p) {
 // grid-stride fill of the owner arrays with the largest index (only after a
 // flagged layout)
 __device__ static void layout_fill(const PrepareArgs& a, int64_t i0, int64_t stride) {
+  if (!a.owner) return;
   if (a.layout[0])
     for (int64_t i = i0; i < a.n_tokens; i += stride) a.owner[i] = 0x7FFFFFFF;
   if (a.adjoint && a.layout[1])
@@ -1360,6 +1356,7 @@ __device__ static void layout_fill(const PrepareArgs& a, int64_t i0, int64_t str
 
 // program p marks its ranges with its index (the lowest index wins)
 __device__ static void layout_mark(const PrepareArgs& a, int p) {
+  if (!a.owner) return;
   int64_t off;
   int32_t n;
   if (a.layout[0] && tok_range(a, p, off, n))
