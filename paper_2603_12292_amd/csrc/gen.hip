@@ -332,11 +332,12 @@ __global__ void __launch_bounds__(256) k_generation(GenStepArgs a) {
   }
 }
 
-// Children per wave: 64, fewer (not below the GEN_GROUPS that the second
+// Children per wave: 32 (64 left the second phase's last waves alone: 243
+// against 228 us for 10^6 children), fewer (not below the GEN_GROUPS that the second
 // phase writes at a time) where that would leave under 8192 waves, eight per
 // SIMD: the phases are chains of dependent reads, which only other waves hide.
 void launch_generation(GenStepArgs a, hipStream_t s) {
-  int per = 64;
+  int per = 32;
   while (per > GEN_GROUPS && int64_t(a.n) < int64_t(8192) * per) per >>= 1;
   a.per_wave = per;
   const int64_t waves = (int64_t(a.n) + per - 1) / per;
