@@ -596,7 +596,7 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
     fa.fitness = fitness + p0;
     fa.coef = nullptr;
     fa.smax = smax;
-    hipLaunchKernelGGL(bgl::k_finalize, dim3((np + 255) / 256), dim3(256), 0, s, fa);
+    hipLaunchKernelGGL(bgl::k_finalize, dim3((np + 63) / 64), dim3(64), 0, s, fa);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
   }
@@ -1001,7 +1001,7 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   fa.kind = BEAGLE_FIT_CORR;
   fa.fitness = fitness;
   fa.coef = reinterpret_cast<double*>(ws + L.coef);
-  hipLaunchKernelGGL(bgl::k_finalize, dim3((progs->n_programs + 255) / 256), dim3(256), 0, s, fa);
+  hipLaunchKernelGGL(bgl::k_finalize, dim3((progs->n_programs + 63) / 64), dim3(64), 0, s, fa);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "finalize launch");
   return BEAGLE_OK;

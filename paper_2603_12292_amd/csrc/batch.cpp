@@ -73,7 +73,7 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   if (e != hipSuccess) return e;
   e = bgl::launch_eval_batch(b.args.kind, b.args, b.has, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bgl::k_finalize_batch, dim3(uint32_t((b.n_programs + 255) / 256)), dim3(256), 0, s, b.args);
+  hipLaunchKernelGGL(bgl::k_finalize_batch, dim3(uint32_t((b.n_programs + 63) / 64)), dim3(64), 0, s, b.args);
   return hipGetLastError();
 }
 

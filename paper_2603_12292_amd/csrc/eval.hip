@@ -868,6 +868,23 @@ __global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int64_t 
 }
 
 // Fitness of every program from its chunk partials, summed in chunk order.
+// Eight chunks' partials are loaded ahead of their additions: one load after
+// the other, the 73 chunks of a problem took 55 us.
+__device__ static double chunk_sum(const FinalizeArgs& a, int j, int p) {
+  const double* part = a.part + int64_t(j) * a.n_chunks * a.n_programs + p;
+  double s = 0.0;
+  int c = 0;
+  for (; c + 8 <= a.n_chunks; c += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[int64_t(c + u) * a.n_programs];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; c < a.n_chunks; ++c) s += part[int64_t(c) * a.n_programs];
+  return s;
+}
+
 __device__ static void finalize_program(const FinalizeArgs& a, int p) {
   const ProgMeta m = a.meta[p];
   const double nan = __longlong_as_double(0x7FF8000000000000LL);
@@ -875,19 +892,13 @@ __device__ static void finalize_program(const FinalizeArgs& a, int p) {
   if (m.status != BEAGLE_PROG_OK) {
     F = nan;
   } else if (a.kind == BEAGLE_FIT_MSE) {
-    double s = 0.0;
-    for (int c = 0; c < a.n_chunks; ++c) s += a.part[int64_t(c) * a.n_programs + p];
-    F = s / double(a.M);
+    F = chunk_sum(a, 0, p) / double(a.M);
   } else if (a.kind == BEAGLE_FIT_POINT) {
-    double s = 0.0;
-    for (int c = 0; c < a.n_chunks; ++c) s += a.part[int64_t(c) * a.n_programs + p];
-    F = s;
+    F = chunk_sum(a, 0, p);
   } else if (a.kind == BEAGLE_FIT_R4) {
     double s[7];
-    for (int j = 0; j < 7; ++j) {
-      s[j] = 0.0;
-      for (int c = 0; c < a.n_chunks; ++c) s[j] += a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p];
-    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) s[j] = chunk_sum(a, j, p);
     const double c1 = s[0], c2 = s[1], n = double(a.M) - c1 - c2;
     double r = 0.0;
     if (n >= 2.0) {
@@ -899,9 +910,9 @@ __device__ static void finalize_program(const FinalizeArgs& a, int p) {
     const double r2 = r * r;
     F = a.smax * (r2 * r2) * n - a.smax * (c1 - c2);
   } else {
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int j = 0; j < 3; ++j)
-      for (int c = 0; c < a.n_chunks; ++c) s[j] += a.part[(int64_t(j) * a.n_chunks + c) * a.n_programs + p];
+    double s[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = chunk_sum(a, j, p);
     const double Md = double(a.M);
     const double syy = a.stats[2], sw = a.stats[1];
     // gradient seed (1 - r^2 differentiated, unclamped; zero for a constant
