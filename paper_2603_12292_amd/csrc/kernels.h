@@ -248,8 +248,8 @@ constexpr int64_t FOLD_MIN_CASES = 2048;
 constexpr int64_t FOLD_MIN_WORK = int64_t(1) << 26;  // programs x cases that repay its launch
 constexpr int64_t FOLD_MIN_CASES_ADJOINT = 512;
 // Work items (programs x chunks) up to which one launch runs all register-need
-// classes (its registers allow three waves per SIMD): two launches fewer count
-// for more there than the waves.
+// classes (its registers allow fewer waves per SIMD): two launches fewer count
+// for more there than the waves (256 programs x 1000 cases: 32 -> 25 us).
 constexpr int64_t MIXED_MAX_ITEMS = 4096;
 // (that launch has one tile width: nothing to tune)
 inline bool mixed_launch(int64_t n_programs, int64_t n_chunks) { return n_programs * n_chunks <= MIXED_MAX_ITEMS; }

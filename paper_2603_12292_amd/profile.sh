@@ -52,19 +52,19 @@ paper|adjoint|ragged|loop)
   # or the adjoint of the differentiation workload
   if [ "$what" = paper ]; then
     run_cmd="python3 -m paper_2603_12292_amd.profiling paper --steps 2"
-    kernels="k_prepare,k_eval_resident,k_eval_class,k_finalize,k_stage"
+    kernels="k_prepare,k_eval_resident,k_eval_class,k_finalize,k_stage,k_layout"
     title="paper regime: 2^20 programs (plain-mid x256, L~U{5..64}, D=5) on 512 cases, MSE"
   elif [ "$what" = loop ]; then
     run_cmd="python3 -m paper_2603_12292_amd.profiling loop --generations 3"
-    kernels="k_generation,k_micro,k_init,k_prepare,k_eval_resident,k_eval_class,k_finalize,k_stage,k_target,k_values"
+    kernels="k_generation,k_micro,k_init,k_prepare,k_eval_resident,k_eval_class,k_finalize,k_stage,k_target,k_shifts"
     title="paper loop: 5e6 individuals (ramped half-and-half, depths 2..5, max length 64, 9 base operators), correlation fitness on 512 cases (D=5), microcosm selection (sample 100, keep 0.5), mutation only; one untimed and 3 profiled generations"
   elif [ "$what" = ragged ]; then
     run_cmd="python3 -m paper_2603_12292_amd.profiling ragged --steps 2"
-    kernels="k_eval_batch,k_prepare,k_stage,k_finalize,k_eval_class,k_eval_resident,k_target"
+    kernels="k_eval_batch,k_prepare,k_stage,k_finalize,k_eval_class,k_eval_resident,k_target,k_shifts"
     title="ragged: 64 problems x 1024 programs, L~U{5..96}, D~U{1..9}, M=round(10^U(3,6)), MSE; batched (replayed graph), then one call per problem"
   else
     run_cmd="python3 -m paper_2603_12292_amd.profiling run --steps 2 --adjoint"
-    kernels="k_grad,k_prepare,k_finalize"
+    kernels="k_grad,k_prepare,k_finalize,k_fold"
     title="adjoint: N=4096 programs with 1..8 constants, L~U{8..64}, D=5, M=100000, MSE fitness and gradients"
   fi
   echo "pass: kernel trace"
