@@ -104,6 +104,8 @@ void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
 // Whether an evaluation of N programs stages derived input rows: computing
 // them costs about eight programs' work per case.
 inline bool use_derived(int64_t N) { return N >= 16; }
+// program-cases from which a population for the resident kernels does
+constexpr int64_t DERIVED_MIN_RESIDENT = int64_t(1) << 22;
 void zero_i32(int32_t* p, int64_t n, hipStream_t s);
 
 // Tile variant of class 0 for a problem (0 wide, 1 narrow).  Under
