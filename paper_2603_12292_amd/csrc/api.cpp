@@ -139,8 +139,12 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
                        bool with_grad = false) {
   // (a resident table of few program-cases: copying the derived rows into every
   // compute unit takes longer than they save.  7596 programs of 16 operators x
-  // 310 cases 98 against 94 us, 20 000 programs 211 against 227)
-  const bool short_table = P->n_programs >= bgl::RESIDENT_MIN_PROGRAMS && P->n_programs * d->M < DERIVED_MIN_RESIDENT;
+  // 310 cases 98 against 94 us, 20 000 programs 211 against 227.  From D = 7
+  // on one table fills a compute unit's LDS and leaves it half its waves:
+  // at D = 9 20 000 x 512 182 against 109 us, at D = 8 65 000 x 500 309 against
+  // 339)
+  const int64_t enough = d->D > 6 && d->M <= bgl::TILE ? 4 * DERIVED_MIN_RESIDENT : DERIVED_MIN_RESIDENT;
+  const bool short_table = P->n_programs >= bgl::RESIDENT_MIN_PROGRAMS && P->n_programs * d->M < enough;
   const bool derived = extras && !with_grad && use_derived(P->n_programs) && !short_table;
   EvalLayout L{};
   Carve c;
