@@ -129,6 +129,7 @@ struct EvalLayout {
   size_t f_tokens, f_len, f_consts, f_coff, f_cc, f_mapn, f_maps, f_mapd;  // folded programs (fold)
   int32_t fold;                   // constant subtrees folded
   int32_t derived, rows;          // derived input rows staged; rows per staged tile
+  int32_t work_shift, work_words;  // counters of a work list (counter_shift), words of all lists'
   int64_t Mp, chunk, gchunk;      // case chunks of the evaluation and of the adjoint
   int32_t n_chunks, gn_chunks, slice;
 };
@@ -165,14 +166,7 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   L.meta = c.take<bgl::ProgMeta>(N);
   L.class_count = c.take<int32_t>(64);  // [0..2] need classes, [8..9] length classes, [32..33] layout flags
   // right behind the counters (256 bytes): one clear covers both
-  L.work = c.take<unsigned long long>(8);  // evaluation: one per class; adjoint: one per list
-  L.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
-  L.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
-  L.long_list = c.take<int32_t>(size_t(N));
-  L.Mp = round_up(d->M, bgl::TILE);
-  L.Xt = c.take<float>(size_t(L.rows) * L.Mp);
-  L.stats = c.take<double>(4);
-  L.slice = slice;
+  // the evaluation's class lists, then (cleared again) the adjoint's lists;
   // the chunking depends on the whole population only, so that a sliced
   // evaluation sums every program's partials in the same order
   eval_chunks(d->M, N, &L.chunk, &L.n_chunks);
@@ -182,6 +176,16 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   L.gn_chunks = 0;
   if (with_grad) choose_chunks(d->M, N, &L.gchunk, &L.gn_chunks, bgl::GRAD_CHUNK_CASES, bgl::GRAD_TILE_CASES,
                                16384);
+  L.work_shift = bgl::counter_shift(N * std::max(L.n_chunks, L.gn_chunks));
+  L.work_words = (with_grad ? bgl::GRAD_LISTS : bgl::N_CLASSES) * bgl::counter_words(L.work_shift);
+  L.work = c.take<unsigned long long>(L.work_words);
+  L.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
+  L.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
+  L.long_list = c.take<int32_t>(size_t(N));
+  L.Mp = round_up(d->M, bgl::TILE);
+  L.Xt = c.take<float>(size_t(L.rows) * L.Mp);
+  L.stats = c.take<double>(4);
+  L.slice = slice;
   L.part = c.take<double>(std::max<size_t>(size_t(n_sums) * L.n_chunks * slice, size_t(L.gn_chunks) * N));
   L.gpart = with_grad ? c.take<double>(size_t(L.gn_chunks) * std::max<int64_t>(P->n_consts, 1)) : 0;
   L.coef = with_grad ? c.take<double>(size_t(3) * N) : 0;
@@ -210,7 +214,7 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
                       bool adjoint = false) {
   // the decoder's counters and flags, and the work counters of the first
   // interpreter launch
-  zero_i32(reinterpret_cast<int32_t*>(ws + L.class_count), int64_t(L.work - L.class_count) / 4 + 16, s);
+  zero_i32(reinterpret_cast<int32_t*>(ws + L.class_count), int64_t(L.work - L.class_count) / 4 + 2 * L.work_words, s);
   bgl::PrepareArgs pa;
   pa.tokens = P->tokens;
   pa.n_tokens = P->n_tokens;
@@ -394,6 +398,7 @@ bgl::EvalArgs eval_args(char* ws, const EvalLayout& L, const beagle_programs* P,
   ea.class_count = reinterpret_cast<const int32_t*>(ws + L.class_count);
   ea.class_list = reinterpret_cast<const int32_t*>(ws + L.class_list);
   ea.work = reinterpret_cast<unsigned long long*>(ws + L.work);
+  ea.work_shift = L.work_shift;
   ea.n_total = P->n_programs;
   ea.prog_begin = 0;
   ea.meta_shift = shift_in_kernel ? reinterpret_cast<bgl::ProgMeta*>(ws + L.meta) : nullptr;
@@ -1053,7 +1058,7 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
     if (st != BEAGLE_OK) return st;
   }
   unsigned long long* work = reinterpret_cast<unsigned long long*>(ws + L.work);
-  zero_i32(reinterpret_cast<int32_t*>(work), 2 * 8, s);
+  zero_i32(reinterpret_cast<int32_t*>(work), 2 * L.work_words, s);
   bgl::GradArgs ga;
   ga.code = reinterpret_cast<const uint32_t*>(ws + L.code);
   ga.aux = reinterpret_cast<const uint32_t*>(ws + L.aux);
@@ -1078,6 +1083,7 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   ga.list_count = reinterpret_cast<const int32_t*>(ws + L.class_count) + 8;
   ga.list = reinterpret_cast<const int32_t*>(ws + L.len_list);
   ga.work = work;
+  ga.work_shift = L.work_shift;
   hipError_t e = bgl::launch_grad(ga, s);
   if (e != hipSuccess) return hip_fail(e, "gradient launch");
   bgl::GradFinalizeArgs fa;

@@ -140,11 +140,18 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   };
   std::vector<Off> off(n);
   size_t at_table = 0, at_items = 0, at_work = 0, at_counts = 0;
+  int work_shift = 0;
   auto lay_out = [&](bool derived) {
     Carve c;
     at_table = c.take<bgl::BatchProblem>(n);
     at_items = c.take<int64_t>(size_t(bgl::N_LISTS) * (n + 1));
-    at_work = c.take<unsigned long long>(bgl::N_LISTS);
+    int64_t batch_items = 0;  // (of the longest list at most)
+    for (int i = 0; i < n; ++i) {
+      eval_chunks(data[active[i]].M, progs[active[i]].n_programs, &off[i].chunk, &off[i].n_chunks);
+      batch_items += int64_t(progs[active[i]].n_programs) * off[i].n_chunks;
+    }
+    work_shift = bgl::counter_shift(batch_items);
+    at_work = c.take<unsigned long long>(size_t(bgl::N_LISTS) * bgl::counter_words(work_shift));
     at_counts = c.take<int32_t>(size_t(64) * n);
     for (int i = 0; i < n; ++i) {
       const beagle_programs& P = progs[active[i]];
@@ -166,7 +173,6 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
       o.Mp = round_up(d.M, bgl::TILE);
       o.Xt = c.take<float>(size_t(bgl::stage_rows(d.D, o.derived)) * o.Mp);
       o.stats = c.take<double>(4);
-      eval_chunks(d.M, N, &o.chunk, &o.n_chunks);
       o.part = c.take<double>(size_t(n_sums) * o.n_chunks * N);
     }
     return c.used + 256;
@@ -258,6 +264,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   a.n_cases = b.n_cases;
   a.item_off = reinterpret_cast<int64_t*>(ws + at_items);
   a.work = reinterpret_cast<unsigned long long*>(ws + at_work);
+  a.work_shift = work_shift;
 
   // upload the table (outside the graph), then launch the graph for it
   const size_t table_bytes = sizeof(bgl::BatchProblem) * n;

@@ -689,9 +689,9 @@ k_eval_class(EvalArgs a) {
   // workgroups beyond the items leave at once
   if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;
   float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
-  WaveItems work(items, a.work + CLS, claim_least(a.chunk));
+  WaveItems work(items, a.work + CLS * counter_words(a.work_shift), a.work_shift);
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(CLS == 0 && a.chunk < 2 * TILE ? 2 : 1);
     if (it < 0) break;
     const int c = a.n_chunks == 1 ? 0 : int(it / count);
     const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count] - a.prog_begin);
@@ -710,9 +710,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) k
   const int64_t items = int64_t(count) * a.n_chunks;
   if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;
   float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
-  WaveItems work(items, a.work, 1);
+  WaveItems work(items, a.work, a.work_shift);
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(1);
     if (it < 0) break;
     const int c = int(it / count), i = int(it - int64_t(c) * count);
     const int cls = i < n0 ? 0 : i < n01 ? 1 : 2;
@@ -747,9 +747,9 @@ k_eval_resident(EvalArgs a) {
   for (int i = threadIdx.x; i < n4; i += blockDim.x)
     reinterpret_cast<float4*>(table)[i] = reinterpret_cast<const float4*>(a.Xt)[i];
   __syncthreads();
-  WaveItems work(count, a.work + CLS, claim_least(a.M));
+  WaveItems work(count, a.work + CLS * counter_words(a.work_shift), a.work_shift);
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(claim_least(a.M));
     if (it < 0) break;
     const int p = __builtin_amdgcn_readfirstlane(list[it] - a.prog_begin);
     if (p >= 0 && p < a.n_programs) eval_wave<KIND, K, class_stack(CLS), true>(a, p, 0, table);  // else another slice's
@@ -773,10 +773,10 @@ k_eval_batch(BatchArgs b, int vl) {
   const int64_t items = off[b.n_problems];
   if (int64_t(blockIdx.x) * EVAL_WAVES >= items) return;  // (as in k_eval_class)
   float* ring = rings[__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6))];
-  WaveItems work(items, b.work + vl, 2);
+  WaveItems work(items, b.work + vl * counter_words(b.work_shift), b.work_shift);
   int lo = 0;  // the problem of the previous item (a lower bound for the next)
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(2);
     if (it < 0) break;
     // the last problem q >= lo with off[q] <= it (problems without items in
     // this list have empty ranges and are stepped over)
@@ -817,6 +817,7 @@ k_eval_batch(BatchArgs b, int vl) {
     a.class_count = nullptr;
     a.class_list = nullptr;
     a.work = nullptr;
+    a.work_shift = 0;
     a.n_total = P.prep.n_programs;
     a.prog_begin = 0;
     a.meta_shift = P.n_chunks == 1 ? P.prep.meta : nullptr;
@@ -991,8 +992,7 @@ __global__ void k_batch_items(BatchArgs b) {
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int n) {
-  const int i = threadIdx.x;
-  if (i < n) p[i] = 0ull;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0ull;
 }
 
 static int cu_count() {
@@ -1071,7 +1071,8 @@ static hipError_t launch_resident(const EvalArgs& a, hipStream_t s, hipEvent_t e
 template <int KIND>
 static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                               bool counters_clear) {
-  if (!counters_clear) hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, a.work, N_CLASSES);
+  if (!counters_clear) 
+    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, a.work, N_CLASSES * counter_words(a.work_shift));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // (a chunk of half a tile: only the narrow tile starts inside a tile)
@@ -1151,7 +1152,7 @@ void prime_eval_batch(int kind) {
 
 template <int KIND>
 static hipError_t launch_batch_kind(const BatchArgs& b, const int* has, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, b.work, N_LISTS);
+  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, b.work, N_LISTS * counter_words(b.work_shift));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_list<KIND, 0, 0>(b, 0, has, s)) != hipSuccess) return e;

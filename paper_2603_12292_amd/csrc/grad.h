@@ -90,7 +90,8 @@ struct GradArgs {
   const double* stats;        // CORR: target statistics (mean, sum of w = y - mean, Syy)
   const int32_t* list_count;  // [GRAD_LISTS] program counts of the adjoint lists
   const int32_t* list;        // [GRAD_LISTS][n_programs]
-  unsigned long long* work;   // [GRAD_LISTS] work-item counters, zero at launch
+  unsigned long long* work;   // [GRAD_LISTS] lists' work counters, zero at launch
+  int32_t work_shift;         // ... 2^work_shift each (counter_shift)
 };
 
 struct GradFinalizeArgs {

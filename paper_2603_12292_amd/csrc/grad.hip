@@ -381,9 +381,9 @@ __global__ void __launch_bounds__(64) k_grad(GradArgs a) {
   const int32_t* list = a.list + (LONG ? int64_t(a.n_programs) : 0);
   // waves beyond the items leave at once (no atomic on a short list)
   if (int64_t(blockIdx.x) >= items) return;
-  WaveItems work(items, a.work + (LONG ? 1 : 0), 1);
+  WaveItems work(items, a.work + (LONG ? counter_words(a.work_shift) : 0), a.work_shift);
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(1);
     if (it < 0) break;
     const int c = int(it / count);
     const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count]);
@@ -898,9 +898,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIST ==
   const int64_t items = int64_t(count) * a.n_chunks;
   const int32_t* list = a.list + LIST * int64_t(a.n_programs);
   if (int64_t(blockIdx.x) >= items) return;  // (as in k_grad)
-  WaveItems work(items, a.work + LIST, 1);
+  WaveItems work(items, a.work + LIST * counter_words(a.work_shift), a.work_shift);
   for (;;) {
-    const int64_t it = work.next();
+    const int64_t it = work.next(1);
     if (it < 0) break;
     const int c = int(it / count);
     const int p = __builtin_amdgcn_readfirstlane(list[it - int64_t(c) * count]);

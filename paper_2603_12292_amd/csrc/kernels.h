@@ -138,7 +138,8 @@ struct EvalArgs {
   const double* stats;    // target statistics (correlation fitness)
   const int32_t* class_count;       // [N_CLASSES]
   const int32_t* class_list;        // [N_CLASSES][n_total] global program indices
-  unsigned long long* work;         // [N_CLASSES] work-item counters, zero at launch
+  unsigned long long* work;         // [N_CLASSES] lists' work counters, zero at launch
+  int32_t work_shift;               // ... 2^work_shift each (counter_shift)
   int32_t n_total;                  // programs in the whole population
   int32_t prog_begin;               // first program of this launch (slice-local index 0)
   double smax = 0.0;                // the paper's scores: maximum score S
@@ -204,7 +205,8 @@ struct BatchArgs {
   int64_t n_programs;          // over the whole table
   int64_t n_cases;             // padded cases over the whole table
   int64_t* item_off;           // [N_LISTS][n_problems + 1] first work item of each problem per list
-  unsigned long long* work;    // [N_LISTS] work-item counters, zero at launch
+  unsigned long long* work;    // [N_LISTS] lists' work counters, zero at launch
+  int32_t work_shift;          // ... 2^work_shift each (counter_shift)
 };
 
 // The problem holding batch-wide index x of a prefix field (prog_begin or
@@ -253,7 +255,14 @@ constexpr int64_t FOLD_MIN_CASES_ADJOINT = 512;
 constexpr int64_t MIXED_MAX_ITEMS = 4096;
 // (that launch has one tile width: nothing to tune)
 inline bool mixed_launch(int64_t n_programs, int64_t n_chunks) { return n_programs * n_chunks <= MIXED_MAX_ITEMS; }
-constexpr int64_t CLAIM_MAX = 16;  // work items of one claim at most
+constexpr int CLAIM_MAX = 16;  // work items of one claim at most
+// Work counters of a list (see WaveItems): 2^shift of them, a line apart; the
+// lists' counters follow one another.  One counter where every grid walks the
+// list without claims, or nearly so.
+constexpr int COUNTER_SHIFT = 4;
+constexpr int COUNTER_STRIDE = 16;  // 64-bit words: 128 bytes
+inline int counter_shift(int64_t items) { return items > 4096 ? COUNTER_SHIFT : 0; }
+__host__ __device__ constexpr int counter_words(int shift) { return shift ? COUNTER_STRIDE << shift : 1; }
 __host__ __device__ constexpr int class_k(int c, int kv) { return c == 0 ? (kv == 0 ? 8 : 4) : 4; }
 
 // decoding: programs of at most 64 tokens in k_prepare_wave (a wave per
