@@ -100,10 +100,14 @@ void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int6
 
 void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks) {
   // chunks of whole wide tiles, of half tiles where those leave under 4096
-  // work items; never more than 1024 chunks (the partial sums' memory)
+  // work items; at most 1024 chunks, or as many as make CHUNK_ITEMS items
   const int64_t most = std::max<int64_t>(bgl::CHUNK_CASES, round_up((M + 1023) / 1024, bgl::TILE));
   const int64_t unit = N * ((M + bgl::TILE - 1) / bgl::TILE) < 4096 ? bgl::CHUNK_UNIT : bgl::TILE;
-  choose_chunks(M, N, chunk, n_chunks, most, unit);
+  // Small case sets stay whole, for the resident kernels, where the programs
+  // fill the waves: 16 000 programs x 1000 cases 65 us (in two chunks 95,
+  // 3..12 tokens, D = 5); 4096 x 2048 139 us (in four 107, 5..64 tokens, D = 2).
+  const bool whole = N >= bgl::RESIDENT_MIN_PROGRAMS && M <= std::min<int64_t>(2048, N / 4);
+  choose_chunks(M, N, chunk, n_chunks, most, unit, whole ? 1 : bgl::CHUNK_ITEMS);
 }
 
 static __global__ void k_zero_i32(int32_t* p, int64_t n) {
@@ -579,7 +583,7 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
   // the work counters are clear for the first launch unless the tuner's
   // timed runs used them
   bool counters_clear = true;
-  if (ctx && !bgl::mixed_launch(progs->n_programs, L.n_chunks)) {
+  if (ctx && !bgl::mixed_launch(progs->n_programs, L.n_chunks, L.chunk)) {
     counters_clear = known_tile_variant(ctx, kind, data->D, data->M,
                                         double(progs->n_tokens) / progs->n_programs, &kv);
     TuneSlice ts{kind, slice_args(0, std::min(slice, progs->n_programs))};
@@ -609,7 +613,7 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
     fa.fitness = fitness + p0;
     fa.coef = nullptr;
     fa.smax = smax;
-    hipLaunchKernelGGL(bgl::k_finalize, dim3((np + 63) / 64), dim3(64), 0, s, fa);
+    bgl::launch_finalize(fa, s);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "finalize launch");
   }
@@ -998,7 +1002,7 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   const bgl::EvalArgs ea = eval_args(ws, L, progs, data, shift_in_kernel);
   int kv = 0;
   TuneSlice ts{BEAGLE_FIT_CORR, ea};
-  if (!bgl::mixed_launch(progs->n_programs, L.n_chunks))
+  if (!bgl::mixed_launch(progs->n_programs, L.n_chunks, L.chunk))
     st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s,
                       run_slice, &ts, &kv);
   if (st != BEAGLE_OK) return st;
@@ -1014,7 +1018,7 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   fa.kind = BEAGLE_FIT_CORR;
   fa.fitness = fitness;
   fa.coef = reinterpret_cast<double*>(ws + L.coef);
-  hipLaunchKernelGGL(bgl::k_finalize, dim3((progs->n_programs + 63) / 64), dim3(64), 0, s, fa);
+  bgl::launch_finalize(fa, s);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "finalize launch");
   return BEAGLE_OK;

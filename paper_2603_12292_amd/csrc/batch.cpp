@@ -73,7 +73,8 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   if (e != hipSuccess) return e;
   e = bgl::launch_eval_batch(b.args.kind, b.args, b.has, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bgl::k_finalize_batch, dim3(uint32_t((b.n_programs + 63) / 64)), dim3(64), 0, s, b.args);
+  const uint32_t fgrid = uint32_t(std::min<int64_t>((b.n_programs + 3) / 4, 1 << 20));
+  hipLaunchKernelGGL(bgl::k_finalize_batch, dim3(fgrid), dim3(256), 0, s, b.args);
   return hipGetLastError();
 }
 
@@ -113,7 +114,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
       int64_t chunk = 0;
       int32_t n_chunks = 0;
       eval_chunks(data[q].M, progs[q].n_programs, &chunk, &n_chunks);
-      if (bgl::mixed_launch(progs[q].n_programs, n_chunks)) {
+      if (bgl::mixed_launch(progs[q].n_programs, n_chunks, chunk)) {
         // too few work items alone to be measured: the wide tile, which is the
         // faster one wherever chunks hold whole tiles
         kv[q] = 0;

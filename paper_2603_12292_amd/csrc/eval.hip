@@ -868,12 +868,19 @@ __global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int64_t 
   for (int64_t i = threadIdx.x; i < M; i += 256) out[int64_t(blockIdx.x) * M + i] = __int_as_float(0x7FC00000);
 }
 
-// Fitness of every program from its chunk partials, summed in chunk order.
-// Eight chunks' partials are loaded ahead of their additions: one load after
-// the other, the 73 chunks of a problem took 55 us.
+// Fitness of every program from its chunk partials.  Up to
+// WIDE_FINALIZE_CHUNKS a thread adds them in chunk order, eight loaded ahead of
+// their additions; more (WIDE) a wave, lane l chunks l, l + 64, ... and then the
+// lanes' sums: one load after the other, the 73 chunks of a problem took 55 us.
+template <bool WIDE>
 __device__ static double chunk_sum(const FinalizeArgs& a, int j, int p) {
   const double* part = a.part + int64_t(j) * a.n_chunks * a.n_programs + p;
   double s = 0.0;
+  if constexpr (WIDE) {
+#pragma unroll 4
+    for (int c = threadIdx.x & 63; c < a.n_chunks; c += 64) s += part[int64_t(c) * a.n_programs];
+    return wave_sum(s);
+  }
   int c = 0;
   for (; c + 8 <= a.n_chunks; c += 8) {
     double v[8];
@@ -886,20 +893,23 @@ __device__ static double chunk_sum(const FinalizeArgs& a, int j, int p) {
   return s;
 }
 
+// (WIDE: every lane of the wave, with the same p)
+template <bool WIDE>
 __device__ static void finalize_program(const FinalizeArgs& a, int p) {
   const ProgMeta m = a.meta[p];
+  const bool one = !WIDE || (threadIdx.x & 63) == 0;
   const double nan = __longlong_as_double(0x7FF8000000000000LL);
   double F;
   if (m.status != BEAGLE_PROG_OK) {
     F = nan;
   } else if (a.kind == BEAGLE_FIT_MSE) {
-    F = chunk_sum(a, 0, p) / double(a.M);
+    F = chunk_sum<WIDE>(a, 0, p) / double(a.M);
   } else if (a.kind == BEAGLE_FIT_POINT) {
-    F = chunk_sum(a, 0, p);
+    F = chunk_sum<WIDE>(a, 0, p);
   } else if (a.kind == BEAGLE_FIT_R4) {
     double s[7];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) s[j] = chunk_sum(a, j, p);
+    for (int j = 0; j < 7; ++j) s[j] = chunk_sum<WIDE>(a, j, p);
     const double c1 = s[0], c2 = s[1], n = double(a.M) - c1 - c2;
     double r = 0.0;
     if (n >= 2.0) {
@@ -913,7 +923,7 @@ __device__ static void finalize_program(const FinalizeArgs& a, int p) {
   } else {
     double s[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) s[j] = chunk_sum(a, j, p);
+    for (int j = 0; j < 3; ++j) s[j] = chunk_sum<WIDE>(a, j, p);
     const double Md = double(a.M);
     const double syy = a.stats[2], sw = a.stats[1];
     // gradient seed (1 - r^2 differentiated, unclamped; zero for a constant
@@ -942,37 +952,53 @@ __device__ static void finalize_program(const FinalizeArgs& a, int p) {
         beta = 2.0 * r * r / sxx;
       }
     }
-    if (a.coef) {
+    if (a.coef && one) {
       a.coef[3 * int64_t(p)] = alpha;
       a.coef[3 * int64_t(p) + 1] = beta;
       a.coef[3 * int64_t(p) + 2] = mu;
     }
   }
-  a.fitness[p] = F;
+  if (one) a.fitness[p] = F;
 }
 
-__global__ void k_finalize(FinalizeArgs a) {
+__global__ void __launch_bounds__(64) k_finalize(FinalizeArgs a) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < a.n_programs) finalize_program(a, p);
+  if (p < a.n_programs) finalize_program<false>(a, p);
 }
 
-// One thread per program of every problem of the table.
-__global__ void k_finalize_batch(BatchArgs b) {
-  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= b.n_programs) return;
-  const int q = batch_find(b, g, [](const BatchProblem& t) { return t.prog_begin; });
-  const BatchProblem& P = b.table[q];
-  FinalizeArgs a;
-  a.meta = P.prep.meta;
-  a.part = P.part;
-  a.stats = P.stats;
-  a.M = P.M;
-  a.n_programs = P.prep.n_programs;
-  a.n_chunks = P.n_chunks;
-  a.kind = b.kind;
-  a.fitness = P.fitness;
-  a.coef = nullptr;
-  finalize_program(a, int(g - P.prog_begin));
+__global__ void __launch_bounds__(256) k_finalize_wide(FinalizeArgs a) {
+  for (int64_t p = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); p < a.n_programs; p += int64_t(gridDim.x) * 4)
+    finalize_program<true>(a, int(p));
+}
+
+void launch_finalize(const FinalizeArgs& a, hipStream_t s) {
+  if (a.n_chunks > WIDE_FINALIZE_CHUNKS)
+    hipLaunchKernelGGL(k_finalize_wide, dim3(std::min((a.n_programs + 3) / 4, 1 << 20)), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_finalize, dim3((a.n_programs + 63) / 64), dim3(64), 0, s, a);
+}
+
+// One wave per program of every problem of the table.
+__global__ void __launch_bounds__(256) k_finalize_batch(BatchArgs b) {
+  for (int64_t g = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); g < b.n_programs; g += int64_t(gridDim.x) * 4) {
+    const int q = batch_find(b, g, [](const BatchProblem& t) { return t.prog_begin; });
+    const BatchProblem& P = b.table[q];
+    FinalizeArgs a;
+    a.meta = P.prep.meta;
+    a.part = P.part;
+    a.stats = P.stats;
+    a.M = P.M;
+    a.n_programs = P.prep.n_programs;
+    a.n_chunks = P.n_chunks;
+    a.kind = b.kind;
+    a.fitness = P.fitness;
+    a.coef = nullptr;
+    const int p = int(g - P.prog_begin);
+    if (P.n_chunks > WIDE_FINALIZE_CHUNKS)
+      finalize_program<true>(a, p);
+    else if ((threadIdx.x & 63) == 0)
+      finalize_program<false>(a, p);
+  }
 }
 
 // First work item of every problem in each work list (exclusive prefix sums
@@ -1083,7 +1109,7 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
     if ((e = launch_resident<KIND, 4, 1>(a, s)) != hipSuccess) return e;
     return launch_class<KIND, 2, 0>(a, s);
   }
-  if (mixed_launch(a.n_total, a.n_chunks)) {
+  if (mixed_launch(a.n_total, a.n_chunks, a.chunk)) {
     const int grid = int((int64_t(a.n_total) * a.n_chunks + EVAL_WAVES - 1) / EVAL_WAVES);
     if (ev0 || ev1)
       hipExtLaunchKernelGGL(k_eval_mixed<KIND>, dim3(grid), dim3(256), 0, s, ev0, ev1, 0u, a);

@@ -99,7 +99,7 @@ int64_t round_up(int64_t v, int64_t m);
 // population alone gives too few work items.
 void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit,
                    int64_t target_blocks = 4096);
-// The evaluation's chunks (see CHUNK_CASES).
+// The evaluation's chunks (see CHUNK_CASES, CHUNK_ITEMS).
 void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
 // Whether an evaluation of N programs stages derived input rows: computing
 // them costs about eight programs' work per case.

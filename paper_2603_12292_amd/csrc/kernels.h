@@ -238,6 +238,17 @@ constexpr int RING = 2;
 // stay in an XCD's L2), a multiple of CHUNK_UNIT (a narrow tile).
 constexpr int64_t CHUNK_CASES = 4096;
 constexpr int64_t CHUNK_UNIT = 256;
+// Work items that a population of few programs is split into: four for each
+// of the 6144 waves of the 8-case kernel (six per SIMD), which walk them
+// without claims.  With 4096, less than a wave's worth each, the longest
+// programs decided the time: 4096 programs x 4096 cases 245 us (now 120), 1000
+// x 20 000 with the further operators 280 (190), 100 x 10^5 175 (94); with
+// 65 536 an item's start counts (2000 x 10^4: 140 -> 148 us).
+constexpr int64_t CHUNK_ITEMS = 24576;
+// Chunks whose partial sums a wave adds, 64 at a time, instead of a thread, one
+// after the other (10 programs x 10^5 cases in 391 chunks: correlation 112
+// us, now 75).
+constexpr int32_t WIDE_FINALIZE_CHUNKS = 16;
 // The resident-inputs evaluator (small case sets, register-need classes 0
 // and 1): staged rows of at most this many bytes, populations of at least this
 // many programs.
@@ -249,12 +260,16 @@ constexpr int32_t RESIDENT_MIN_PROGRAMS = 4096;
 constexpr int64_t FOLD_MIN_CASES = 2048;
 constexpr int64_t FOLD_MIN_WORK = int64_t(1) << 26;  // programs x cases that repay its launch
 constexpr int64_t FOLD_MIN_CASES_ADJOINT = 512;
-// Work items (programs x chunks) up to which one launch runs all register-need
-// classes (its registers allow fewer waves per SIMD): two launches fewer count
-// for more there than the waves (256 programs x 1000 cases: 32 -> 25 us).
+// Work items of one narrow tile up to which one launch runs all register-need
+// classes: two launches fewer count for more there than the three waves per
+// SIMD that its registers allow (400 items 32 -> 27 us, 3000 37 -> 33, 4000
+// within 1 us either way; 5..64 tokens).  Items of several tiles need the
+// class kernels' waves (100 programs x 10^5 cases in 40 chunks: 175 against 109
+// us).  It has one tile width: nothing to tune.
 constexpr int64_t MIXED_MAX_ITEMS = 4096;
-// (that launch has one tile width: nothing to tune)
-inline bool mixed_launch(int64_t n_programs, int64_t n_chunks) { return n_programs * n_chunks <= MIXED_MAX_ITEMS; }
+inline bool mixed_launch(int64_t n_programs, int64_t n_chunks, int64_t chunk) {
+  return n_programs * n_chunks <= MIXED_MAX_ITEMS && chunk <= CHUNK_UNIT;
+}
 constexpr int CLAIM_MAX = 16;  // work items of one claim at most
 // Work counters of a list (see WaveItems): 2^shift of them, a line apart; the
 // lists' counters follow one another.  One counter where every grid walks the
@@ -289,7 +304,8 @@ __global__ void k_shifts_batch(BatchArgs b);
 __global__ void k_batch_items(BatchArgs b);
 __global__ void k_finalize_batch(BatchArgs b);
 __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* __restrict__ stats);
-__global__ void k_finalize(FinalizeArgs a);
+// (more than WIDE_FINALIZE_CHUNKS chunks: a wave per program, else a thread)
+void launch_finalize(const FinalizeArgs& a, hipStream_t s);
 __global__ void k_shifts(ValuesArgs a);
 // NaN rows of the invalid programs of a prediction (a workgroup per program)
 __global__ void k_nan_rows(const ProgMeta* meta, int64_t M, float* out);

@@ -6,8 +6,10 @@
 namespace bgl {
 
 // Work items [0, items) of a persistent grid's waves.  A short list (at most
-// four items per wave) is walked statically (wave w takes items w, w + W, ...:
-// no atomics); a longer one through shared counters, in claims that shrink
+// four items per wave) is walked statically (of every W items a wave takes one,
+// in each round another place on, so that a wave does not meet the same program
+// in chunk after chunk where W is a multiple of the programs: 24 programs x 8
+// 10^6 cases took as long as the longest of them; no atomics); a longer one through shared counters, in claims that shrink
 // towards the list's end: long claims at the end leave waves idle.
 // Atomics on one address serialise (12 ns each, whatever the number of
 // waves): with one counter, the first claim of 6144 waves takes 75 us, the
@@ -27,7 +29,7 @@ struct WaveItems {
   int64_t item, items;  // the next item of this wave's claim; all items
   unsigned long long* work;
   int rest, stride;  // items left of the claim, and between them
-  int counter;  // (-1: a static walk)
+  int counter;       // -1: a static walk, `stride` items a round, `rest` the place in it
   __device__ __forceinline__ WaveItems(int64_t items_, unsigned long long* work_, int shift)
       : items(items_), work(work_) {
     const int per = int(blockDim.x >> 6), waves = int(gridDim.x) * per;
@@ -42,8 +44,8 @@ struct WaveItems {
       rest = 0;
     } else {
       counter = -1;
-      item = id;
-      rest = id < items ? int((items - id + waves - 1) / waves) : 0;
+      item = 0;
+      rest = id;
       stride = waves;
     }
   }
@@ -66,7 +68,14 @@ struct WaveItems {
   }
   // the next item, or -1; claims are of at least `least` items
   __device__ __forceinline__ int64_t next(int least) {
-    if (rest == 0 && (counter < 0 || !claim(least))) return -1;
+    if (counter < 0) {
+      const int64_t r = item + rest;
+      item += stride;
+      rest += int(0.38f * float(stride)) | 1;
+      if (rest >= stride) rest -= stride;
+      return r < items ? r : -1;
+    }
+    if (rest == 0 && !claim(least)) return -1;
     --rest;
     const int64_t r = item;
     item += stride;
