@@ -252,12 +252,13 @@ typedef enum { BEAGLE_TUNE_AUTO = 0, BEAGLE_TUNE_WIDE = 1, BEAGLE_TUNE_NARROW = 
 /* How many fitness cases each lane carries through the interpreter for the
  * common programs (stack of at most 4 values): 8 (BEAGLE_TUNE_WIDE; case
  * sets split into chunks of less than 512 cases take 4 all the same) or 4
- * (BEAGLE_TUNE_NARROW).  BEAGLE_TUNE_AUTO, the
- * default, times both the first time an evaluation meets a problem-shape
- * bucket (fitness kind, D, log2 M, log2 of the mean program length) -- that
- * call synchronises the device -- and keeps the faster in the context (calls
- * of few programs on few cases take one launch of one width and measure
- * nothing).  When
+ * (BEAGLE_TUNE_NARROW).  BEAGLE_TUNE_AUTO, the default, takes the width that
+ * is known to be the faster one for small case sets, few program-cases and
+ * D > 8; elsewhere it times both the first time beagle_eval,
+ * beagle_eval_score or beagle_eval_grad meets a problem-shape bucket (fitness
+ * kind, D, log2 M, log2 of the mean program length) -- that call synchronises
+ * the device -- and keeps the faster in the context.  beagle_eval_batched
+ * measures nothing: it takes what is kept, or 8.  When
  * the environment variable BEAGLE_AUTOTUNE_CACHE names a file, buckets are
  * read from it when a context is created and every new measurement is
  * written back to it.  The choice changes no result bit: with either width a

@@ -502,8 +502,12 @@ beagle_status beagle_ctx_tile_width(beagle_ctx* ctx, int kind, int32_t D, int64_
   if (D < 1 || D > BEAGLE_MAX_D || M < 1 || n_programs < 1 || n_tokens < 0)
     return fail(BEAGLE_E_INVALID_ARG, "bad problem shape");
   int kv = 0;
-  *cases_per_lane =
-      known_tile_variant(ctx, kind, D, M, double(n_tokens) / n_programs, &kv) ? bgl::class_k(0, kv) : 0;
+  const bool known = known_tile_variant(ctx, kind, D, M, n_programs, double(n_tokens) / n_programs, &kv);
+  int64_t chunk = 0;
+  int32_t n_chunks = 0;
+  eval_chunks(M, n_programs, &chunk, &n_chunks);
+  if (chunk % bgl::TILE != 0) kv = 1;
+  *cases_per_lane = known ? bgl::class_k(0, kv) : 0;
   return BEAGLE_OK;
 }
 
@@ -583,12 +587,12 @@ beagle_status evaluate_in(char* ws, const EvalLayout& L, int32_t slice, beagle_c
   // the work counters are clear for the first launch unless the tuner's
   // timed runs used them
   bool counters_clear = true;
-  if (ctx && !bgl::mixed_launch(progs->n_programs, L.n_chunks, L.chunk)) {
-    counters_clear = known_tile_variant(ctx, kind, data->D, data->M,
-                                        double(progs->n_tokens) / progs->n_programs, &kv);
+  if (ctx) {
+    const int64_t N = progs->n_programs;
+    const double mean_len = double(progs->n_tokens) / double(N);
+    counters_clear = known_tile_variant(ctx, kind, data->D, data->M, N, mean_len, &kv);
     TuneSlice ts{kind, slice_args(0, std::min(slice, progs->n_programs))};
-    st = tile_variant(ctx, kind, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s, run_slice, &ts,
-                      &kv);
+    st = tile_variant(ctx, kind, data->D, data->M, N, mean_len, s, run_slice, &ts, &kv);
     if (st != BEAGLE_OK) return st;
   }
   for (int32_t p0 = 0; p0 < progs->n_programs; p0 += slice) {
@@ -1002,9 +1006,8 @@ beagle_status corr_pass(beagle_ctx* ctx, const beagle_programs* progs, const bea
   const bgl::EvalArgs ea = eval_args(ws, L, progs, data, shift_in_kernel);
   int kv = 0;
   TuneSlice ts{BEAGLE_FIT_CORR, ea};
-  if (!bgl::mixed_launch(progs->n_programs, L.n_chunks, L.chunk))
-    st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, double(progs->n_tokens) / progs->n_programs, s,
-                      run_slice, &ts, &kv);
+  st = tile_variant(ctx, BEAGLE_FIT_CORR, data->D, data->M, progs->n_programs,
+                    double(progs->n_tokens) / progs->n_programs, s, run_slice, &ts, &kv);
   if (st != BEAGLE_OK) return st;
   hipError_t e = bgl::launch_eval(BEAGLE_FIT_CORR, kv, ea, s, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(e, "eval launch");

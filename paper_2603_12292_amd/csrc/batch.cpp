@@ -105,26 +105,13 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int n_sums = kind == BEAGLE_FIT_MSE ? 1 : 3;
 
-  // tile widths: a bucket met for the first time is measured by evaluating
-  // one of its problems alone (through beagle_eval, which tunes it)
-  std::vector<int> kv(n_problems, 1);
+  // tile widths: where a single call would measure its bucket first, the wide
+  // tile (a batch of 24 problems took 24 such measurements, twelve runs each
+  // and the workspace grown problem by problem, on its first meeting)
+  std::vector<int> kv(n_problems, 0);
   for (int q : active) {
     const double mean_len = double(progs[q].n_tokens) / progs[q].n_programs;
-    if (!known_tile_variant(ctx, kind, data[q].D, data[q].M, mean_len, &kv[q])) {
-      int64_t chunk = 0;
-      int32_t n_chunks = 0;
-      eval_chunks(data[q].M, progs[q].n_programs, &chunk, &n_chunks);
-      if (bgl::mixed_launch(progs[q].n_programs, n_chunks, chunk)) {
-        // too few work items alone to be measured: the wide tile, which is the
-        // faster one wherever chunks hold whole tiles
-        kv[q] = 0;
-        continue;
-      }
-      beagle_status st = beagle_eval(ctx, &progs[q], &data[q], kind, fitness[q], status ? status[q] : nullptr,
-                                     stream);
-      if (st != BEAGLE_OK) return st;
-      if (!known_tile_variant(ctx, kind, data[q].D, data[q].M, mean_len, &kv[q])) kv[q] = 0;
-    }
+    if (!known_tile_variant(ctx, kind, data[q].D, data[q].M, progs[q].n_programs, mean_len, &kv[q])) kv[q] = 0;
   }
 
   // table order: decreasing estimated work, ties by problem index

@@ -113,10 +113,11 @@ void zero_i32(int32_t* p, int64_t n, hipStream_t s);
 // must enqueue one evaluation of the problem with that variant on `s`
 // between the two events it is given.
 using TuneRun = hipError_t (*)(void* user, int kv, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
-beagle_status tile_variant(beagle_ctx* ctx, int kind, int D, int64_t M, double mean_len, hipStream_t s,
+beagle_status tile_variant(beagle_ctx* ctx, int kind, int D, int64_t M, int64_t N, double mean_len, hipStream_t s,
                            TuneRun run, void* user, int* kv);
-// The variant without measuring: false when AUTO has not yet met the bucket.
-bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, double mean_len, int* kv);
+// The variant without measuring: false when it is AUTO's to measure and the
+// bucket has not yet been met.
+bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, int64_t N, double mean_len, int* kv);
 void load_tune_file(beagle_ctx* ctx);
 void release_graphs(beagle_ctx* ctx);
 

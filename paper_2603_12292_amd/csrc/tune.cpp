@@ -14,6 +14,9 @@
 namespace bgl {
 namespace host {
 
+// program-cases from which AUTO measures (see ruled_tile)
+static constexpr int64_t TUNE_MIN_WORK = int64_t(1) << 24;
+
 static TuneKey bucket(int kind, int D, int64_t M, double mean_len) {
   const int mlog = int(std::lround(std::log2(double(std::max<int64_t>(M, 1)))));
   const int llog = int(std::lround(std::log2(std::max(mean_len, 1.0))));
@@ -48,7 +51,30 @@ static void save_tune_file(const beagle_ctx* ctx) {
   (void)std::rename(tmp.c_str(), ctx->tune_file.c_str());
 }
 
-bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, double mean_len, int* kv) {
+// The variant of the calls that AUTO does not measure, or -1.
+//  - A chunk of half tiles: the narrow one, whatever the policy (the wide tile
+//    starts at whole staged tiles only), so there is nothing to compare.
+//  - At most 256 cases: half of a wide tile would be empty (500 000 programs
+//    x 256 cases: 1010 us, wide 1420).
+//  - Other cases in one chunk, the resident kernels': the wide one, 3 to 35 %
+//    faster but for half-filled last tiles of few (600 cases: within 8 %).  A
+//    bucket has cases of both paths in it, and one path's measurement says
+//    nothing about the other.
+//  - D > 8: the wide one, 5 to 35 % faster (rows are streamed: D is no matter).
+//  - Few program-cases: the wide one.  Runs of under about 100 us measure the
+//    launches and the waves' ends, and the bucket would keep that for large
+//    populations as well.
+static int ruled_tile(int D, int64_t M, int64_t N) {
+  int64_t chunk = 0;
+  int32_t n_chunks = 0;
+  eval_chunks(M, N, &chunk, &n_chunks);
+  if (chunk % TILE != 0) return 1;
+  if (n_chunks == 1 && N >= RESIDENT_MIN_PROGRAMS) return M <= CHUNK_UNIT ? 1 : 0;
+  if (D > 8 || M * N < TUNE_MIN_WORK) return 0;
+  return -1;
+}
+
+bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, int64_t N, double mean_len, int* kv) {
   if (ctx->tuning == BEAGLE_TUNE_NARROW) {
     *kv = 1;
     return true;
@@ -57,15 +83,20 @@ bool known_tile_variant(const beagle_ctx* ctx, int kind, int D, int64_t M, doubl
     *kv = 0;
     return true;
   }
+  const int rule = ruled_tile(D, M, N);
+  if (rule >= 0) {
+    *kv = rule;
+    return true;
+  }
   const auto it = ctx->tuned.find(bucket(kind, D, M, mean_len));
   if (it == ctx->tuned.end()) return false;
   *kv = it->second;
   return true;
 }
 
-beagle_status tile_variant(beagle_ctx* ctx, int kind, int D, int64_t M, double mean_len, hipStream_t s,
+beagle_status tile_variant(beagle_ctx* ctx, int kind, int D, int64_t M, int64_t N, double mean_len, hipStream_t s,
                            TuneRun run, void* user, int* kv) {
-  if (known_tile_variant(ctx, kind, D, M, mean_len, kv)) return BEAGLE_OK;
+  if (known_tile_variant(ctx, kind, D, M, N, mean_len, kv)) return BEAGLE_OK;
   *kv = 0;
   // no measurement while the caller's stream is being captured into a graph
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
