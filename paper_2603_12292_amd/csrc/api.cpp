@@ -142,21 +142,28 @@ struct EvalLayout {
 // programs); false where it does not fit.
 EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, bool extras,
                        bool with_grad = false) {
-  // (a resident table of few program-cases: copying the derived rows into every
-  // compute unit takes longer than they save.  7596 programs of 16 operators x
-  // 310 cases 98 against 94 us, 20 000 programs 211 against 227.  From D = 7
-  // on one table fills a compute unit's LDS and leaves it half its waves:
-  // at D = 9 20 000 x 512 182 against 109 us, at D = 8 65 000 x 500 309 against
-  // 339)
-  const int64_t enough = d->D > 6 && d->M <= bgl::TILE ? 4 * DERIVED_MIN_RESIDENT : DERIVED_MIN_RESIDENT;
-  const bool short_table = P->n_programs >= bgl::RESIDENT_MIN_PROGRAMS && P->n_programs * d->M < enough;
-  const bool derived = extras && !with_grad && use_derived(P->n_programs) && !short_table;
   EvalLayout L{};
   Carve c;
-  L.derived = derived ? 1 : 0;
-  L.rows = bgl::stage_rows(d->D, L.derived);
   const int64_t nt = std::max<int64_t>(P->n_tokens, 1);
   const int64_t N = std::max<int32_t>(P->n_programs, 1);
+  // the chunking depends on the whole population only, so that a sliced
+  // evaluation sums every program's partials in the same order
+  eval_chunks(d->M, N, &L.chunk, &L.n_chunks);
+  bool derived = extras && !with_grad && use_derived(N, d->M, d->D);
+  if (derived && bgl::resident_call(N, L.n_chunks, d->M, bgl::stage_rows(d->D, 0))) {
+    const bool table = bgl::resident_call(N, L.n_chunks, d->M, bgl::stage_rows(d->D, 1));
+    // (at most half a tile of cases: the waves count for more than the rows, so
+    // the table must leave room for a second one.  10^6 programs x 256 cases,
+    // D = 9, 5..64 tokens: 1590 us, with the 110 KB of derived rows 1760)
+    if (d->M <= bgl::CHUNK_UNIT)
+      derived = 2 * bgl::resident_bytes(d->M, bgl::stage_rows(d->D, 1)) <= bgl::RESIDENT_MAX_BYTES &&
+                N * d->M >= DERIVED_MIN_RESIDENT;
+    else
+      derived = table ? N * d->M >= DERIVED_MIN_RESIDENT
+                      : d->M > 4 * bgl::TILE || P->n_tokens >= DERIVED_MIN_LENGTH * N;
+  }
+  L.derived = derived ? 1 : 0;
+  L.rows = bgl::stage_rows(d->D, L.derived);
   L.code = c.take<uint32_t>(nt);
   L.aux = c.take<uint32_t>(nt);
   // (the row lists, a byte per token: an evaluation writes no adjoint words)
@@ -170,10 +177,7 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   L.meta = c.take<bgl::ProgMeta>(N);
   L.class_count = c.take<int32_t>(64);  // [0..2] need classes, [8..9] length classes, [32..33] layout flags
   // right behind the counters (256 bytes): one clear covers both
-  // the evaluation's class lists, then (cleared again) the adjoint's lists;
-  // the chunking depends on the whole population only, so that a sliced
-  // evaluation sums every program's partials in the same order
-  eval_chunks(d->M, N, &L.chunk, &L.n_chunks);
+  // the evaluation's class lists, then (cleared again) the adjoint's lists
   // the adjoint's kernels each walk one list of programs: shorter chunks
   // keep a short list from leaving most of the chip idle
   L.gchunk = 0;

@@ -147,7 +147,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
       const int64_t nt = std::max<int64_t>(P.n_tokens, 1);
       const int64_t N = P.n_programs;
       Off& o = off[i];
-      o.derived = derived && use_derived(N) ? 1 : 0;
+      o.derived = derived && use_derived(N, d.M, d.D) ? 1 : 0;
       o.code = c.take<uint32_t>(nt);
       o.aux = c.take<uint32_t>(nt);
       o.cval = c.take<float>(nt);

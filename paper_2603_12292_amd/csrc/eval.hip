@@ -18,11 +18,11 @@
 
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <type_traits>
 
 #include "beagle_device.h"
 #include "kernels.h"
+#include "per_device.h"
 #include "trig.h"
 #include "wave_items.h"
 
@@ -1057,35 +1057,34 @@ static hipError_t launch_class(const EvalArgs& a, hipStream_t s, hipEvent_t ev0 
   return hipGetLastError();
 }
 
-// bytes of the staged case set
-static size_t resident_bytes(const EvalArgs& a) {
-  return size_t((a.M + TILE - 1) / TILE) * size_t(a.rows) * size_t(TILE) * sizeof(float);
-}
-
-// The resident kernels take the call when there is one chunk whose rows fit
-// and enough programs to repay the copies; both give the same bits (a wave
-// adds a program's cases in the same order).
-static bool resident_eligible(const EvalArgs& a) {
-  return a.n_chunks == 1 && a.n_total >= RESIDENT_MIN_PROGRAMS && resident_bytes(a) <= RESIDENT_MAX_BYTES;
-}
-
 template <int KIND, int K, int CLS>
 static hipError_t launch_resident(const EvalArgs& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-  const size_t lds = resident_bytes(a);
-  // workgroups per CU that fit, and waves of each: together the waves that the
-  // registers allow (RESIDENT_WAVES per SIMD, 4 for the deeper class), at most
-  // 16 in one workgroup
-  const int want = 4 * (CLS == 0 ? RESIDENT_WAVES : 4);
-  const int fit = std::max(1, std::min(want / 4, int(RESIDENT_MAX_BYTES / lds)));
-  // (a multiple of four: a wave of each workgroup more on one SIMD than on
-  // another would keep the next workgroup out)
-  const int waves = std::max(4, std::min(16, want / fit / 4 * 4));
-  const int grid = fit * cu_count();
-  static std::once_flag once;
-  std::call_once(once, [] {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_eval_resident<KIND, K, CLS>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, int(RESIDENT_MAX_BYTES));
+  // (the limit of a kernel's LDS is the current device's)
+  static PerDevice<hipError_t> limit_raised;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = limit_raised.get(dev, [] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_eval_resident<KIND, K, CLS>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, int(RESIDENT_MAX_BYTES));
   });
+  if (e != hipSuccess) return e;
+  const size_t lds = resident_bytes(a.M, a.rows);
+  // Workgroups per CU, of those that fit, and waves of each: together the
+  // waves that the registers allow (RESIDENT_WAVES per SIMD, 4 for the deeper
+  // class; the narrow tile's registers allow more, which took longer: 16 000
+  // programs x 256 cases 45 against 41 us), at most 16 in one workgroup and a
+  // multiple of four (a wave of each workgroup more on one SIMD than on another
+  // would keep the next workgroup out).  The most that fit are not always the
+  // most waves: four tables of 35 KB leave 16 waves, three 24 (20 000 programs of
+  // 3..12 tokens x 512 cases, D = 16: 100 and 60 us).
+  const int want = 4 * (CLS == 0 ? RESIDENT_WAVES : 4);
+  int fit = 1, waves = std::min(16, want);
+  for (int f = 2; f <= std::min(want / 4, int(RESIDENT_MAX_BYTES / lds)); ++f) {
+    const int w = std::min(16, want / f / 4 * 4);
+    if (f * w >= fit * waves) fit = f, waves = w;
+  }
+  const int grid = fit * cu_count();
   if (ev0 || ev1)
     hipExtLaunchKernelGGL((k_eval_resident<KIND, K, CLS>), dim3(grid), dim3(waves * 64), uint32_t(lds), s, ev0, ev1, 0u,
                           a);
@@ -1103,7 +1102,10 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
   if (e != hipSuccess) return e;
   // (a chunk of half a tile: only the narrow tile starts inside a tile)
   const bool wide = kv == 0 && a.chunk % TILE == 0;
-  if (resident_eligible(a)) {
+  // The resident kernels take the call when there is one chunk whose rows fit
+  // and enough programs to repay the copies; both give the same bits (a wave
+  // adds a program's cases in the same order).
+  if (resident_call(a.n_total, a.n_chunks, a.M, a.rows)) {
     e = wide ? launch_resident<KIND, 8, 0>(a, s, ev0, ev1) : launch_resident<KIND, 4, 0>(a, s, ev0, ev1);
     if (e != hipSuccess) return e;
     if ((e = launch_resident<KIND, 4, 1>(a, s)) != hipSuccess) return e;

@@ -101,11 +101,30 @@ void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int6
                    int64_t target_blocks = 4096);
 // The evaluation's chunks (see CHUNK_CASES, CHUNK_ITEMS).
 void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
-// Whether an evaluation of N programs stages derived input rows: computing
-// them costs about eight programs' work per case.
-inline bool use_derived(int64_t N) { return N >= 16; }
-// program-cases from which a population for the resident kernels does
+// Whether an evaluation of N programs on M cases stages derived input rows:
+// their computing and writing is 5 D rows' work per case, and every program
+// saves about a quarter of its own.  D = 5, 5..64 tokens: 16 programs x 10^5
+// cases 47 us (without 43), 40 x 10^5 63 (61), 64 x 10^5 72 (73), 200 x 10^5 146
+// (171).  Rows that don't stay in the caches are read from memory as well: 24
+// programs x 8 10^6 cases 1270 us (1060), 64 x 2 10^6 690 (710); D = 9, 100 x 10^6
+// 986 (857), 200 x 10^6 equal.
+inline bool use_derived(int64_t N, int64_t M, int32_t D) {
+  const bool cached = int64_t(bgl::stage_rows(D, 1)) * M * 4 <= int64_t(64) << 20;
+  return N >= 16 && N >= (cached ? 8 : 12) * int64_t(D);
+}
+// Program-cases from which a population for the resident kernels does: copying
+// the derived rows into every compute unit takes longer than they save.  7596
+// programs of 16 operators x 310 cases 98 against 94 us, 20 000 programs 211
+// against 227.
 constexpr int64_t DERIVED_MIN_RESIDENT = int64_t(1) << 22;
+// Mean program length (of the token array: slots count whole) from which a
+// population gives up the resident table, which the derived rows would not fit,
+// for them: a short program's start is not repaid by what they save.  65 000
+// programs x 1500 cases, D = 9, table against streamed rows with derived ones:
+// 3..12 tokens 210 and 250 us, 3..32 325 and 325, 5..64 555 and 515; x 2048, D = 5:
+// 240 and 260, 411 and 386, 750 and 650.  Over more tiles it is: x 4096, D = 5,
+// 3..12 tokens 440 and 390.
+constexpr int64_t DERIVED_MIN_LENGTH = 12;
 void zero_i32(int32_t* p, int64_t n, hipStream_t s);
 
 // Tile variant of class 0 for a problem (0 wide, 1 narrow).  Under

@@ -254,6 +254,12 @@ constexpr int32_t WIDE_FINALIZE_CHUNKS = 16;
 // many programs.
 constexpr size_t RESIDENT_MAX_BYTES = 158 * 1024;
 constexpr int32_t RESIDENT_MIN_PROGRAMS = 4096;
+inline size_t resident_bytes(int64_t M, int32_t rows) {
+  return size_t((M + TILE - 1) / TILE) * size_t(rows) * size_t(TILE) * sizeof(float);
+}
+inline bool resident_call(int64_t n_programs, int32_t n_chunks, int64_t M, int32_t rows) {
+  return n_chunks == 1 && n_programs >= RESIDENT_MIN_PROGRAMS && resident_bytes(M, rows) <= RESIDENT_MAX_BYTES;
+}
 // Cases from which constant subtrees are folded: the fold costs a program a
 // few hundred instructions, and saves about a hundred per 512 cases of an
 // evaluation, three times that of a gradient.
