@@ -235,6 +235,12 @@ struct TableRows {
   }
 };
 
+// Rows of one case per lane in LDS, 64 of a row together (k_outputs_small).
+struct LaneRows {
+  const float* x;
+  __device__ __forceinline__ void row(uint32_t r, float (&v)[1]) const { v[0] = x[r * 64u]; }
+};
+
 // Rows of case 0, read straight from global memory (the shifts).
 struct DirectRows {
   const float* x;
@@ -861,6 +867,34 @@ __global__ void __launch_bounds__(64) k_shifts_batch(BatchArgs b) {
   a.Xt = P.Xt;
   a.rows = P.rows;
   shift_program(a, int(g - P.prog_begin));
+}
+
+// Outputs of one program on 64 cases, a case per lane: four times the waves of
+// the narrow tile, which is what counts with few of them, and nothing computed
+// for cases that aren't there (100 000 programs x 64 cases: 190 us, with the
+// narrow tile 280; 5000 x 64 45 and 60; 300 x 3000 with the further operators 35 and
+// 40).  Invalid programs' rows are NaN.
+__global__ void __launch_bounds__(64) k_outputs_small(ValuesArgs a, int64_t M, int32_t D, float* out) {
+  __shared__ float x[MAX_D * 64];
+  const int p = blockIdx.x, lane = threadIdx.x;
+  const int64_t i = int64_t(blockIdx.y) * 64 + lane;
+  const ProgMeta m = a.meta[p];
+  float top[1] = {__int_as_float(0x7FC00000)};
+  if (m.status == BEAGLE_PROG_OK) {
+    const int64_t off = a.tok_offset[p];
+    const uint32_t* code = a.code + off;
+    const float* cval = a.cval + off;
+    const int L = m.len;
+    const uint32_t vc0 = lane < L ? code[lane] : 0u;
+    const float vv0 = lane < L ? cval[lane] : 0.0f;
+    const float* xt = a.Xt + case_offset(i, a.rows);
+    for (int d = 0; d < D; ++d)
+      if ((m.vmask >> d) & 1u) x[d * 64 + lane] = xt[d * TILE];
+    __syncthreads();
+    LaneRows rows{x + lane};
+    interpret<1, MAX_STACK>(vc0, vv0, code, cval, L, lane, rows, top);
+  }
+  if (i < M) out[int64_t(p) * M + i] = top[0];
 }
 
 __global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int64_t M, float* out) {

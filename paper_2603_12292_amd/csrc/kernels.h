@@ -173,6 +173,13 @@ struct ValuesArgs {
   int32_t rows;
 };
 
+// A prediction of few program-cases, or of few cases: a wave per program and 64
+// of them, one per lane, in one launch (see k_outputs_small).
+constexpr int64_t SMALL_OUTPUTS = int64_t(1) << 20;
+inline bool small_outputs(int64_t n_programs, int64_t M) {
+  return n_programs * M <= SMALL_OUTPUTS || (M <= 128 && n_programs < (int64_t(1) << 26));
+}
+
 // One problem of a batched evaluation: an entry of the device problem table.
 // Every pointer (the caller's arrays and this problem's share of the
 // workspace) is resolved on the host before the table is uploaded.
@@ -313,6 +320,7 @@ __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* _
 // (more than WIDE_FINALIZE_CHUNKS chunks: a wave per program, else a thread)
 void launch_finalize(const FinalizeArgs& a, hipStream_t s);
 __global__ void k_shifts(ValuesArgs a);
+__global__ void k_outputs_small(ValuesArgs a, int64_t M, int32_t D, float* out);
 // NaN rows of the invalid programs of a prediction (a workgroup per program)
 __global__ void k_nan_rows(const ProgMeta* meta, int64_t M, float* out);
 // host launchers of the templated evaluation kernels (eval.hip)

@@ -1,0 +1,75 @@
+"""Predictions: the kernel for few program-cases gives the outputs that the
+evaluator's kernels give, at the edges of both."""
+import numpy as np
+import pytest
+
+from paper_2603_12292_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _api():
+    from paper_2603_12292_amd import api
+    return api
+
+
+def _same(a, b):
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    ok = ~np.isnan(a)
+    assert np.array_equal(a.view(np.uint32)[ok], b.view(np.uint32)[ok])
+
+
+@pytest.mark.parametrize("D", [1, 5, 16])
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 511, 513, 2000])
+def test_small_predictions_match_large_ones(D, M):
+    # the same cases at the head of a set that is too large for the small kernel
+    api = _api()
+    ps = wl.random_population(3 + D, 40, 3, 90, D)
+    toks = ps.tokens.copy()
+    toks[ps.tok_offset[0]] = wl.tok(wl.VAR, D)          # invalid: a NaN row
+    ps = wl.ProgramSet(toks, ps.tok_offset, ps.tok_len, ps.consts, ps.const_offset, ps.const_count)
+    X = np.random.default_rng(M).uniform(-4, 4, size=(30000, D)).astype(np.float32)
+    X[:8, 0] = [0.0, -0.0, 1e-40, np.inf, -np.inf, np.nan, 3e38, 81.0]
+    P = api.DevicePrograms.from_programset(ps)
+    Xd = torch.from_numpy(X).cuda()
+    large, st = api.predict(P, Xd, with_status=True)
+    small, ss = api.predict(P, Xd[:M].contiguous(), with_status=True)
+    assert st[0] != 0 and torch.equal(st, ss) and bool(torch.isnan(small[0]).all())
+    _same(large[:, :M].contiguous().cpu().numpy(), small.cpu().numpy())
+
+
+@pytest.mark.parametrize("M", [64, 128, 129, 256, 257])
+def test_many_programs_on_few_cases(M):
+    api = _api()
+    base = wl.random_population(11, 100, 3, 40, 3)
+    X = np.random.default_rng(M).uniform(-4, 4, size=(M, 3)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    one = api.predict(api.DevicePrograms.from_programset(base), Xd).cpu().numpy()
+    many = api.predict(api.DevicePrograms.from_programset(wl.replicate(base, 200)), Xd).cpu().numpy()
+    for k in (0, 1, 99, 199):
+        _same(one, many[100 * k:100 * k + 100].copy())
+
+
+def _us(f, n=30):
+    f(), f(), f()
+    best = 1e9
+    for _ in range(5):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(n):
+            f()
+        t1.record()
+        torch.cuda.synchronize()
+        best = min(best, t0.elapsed_time(t1) / n * 1e3)
+    return best
+
+
+def test_few_cases_cost_less_than_more():
+    # 64 cases are a quarter of the narrow tile's 256
+    api = _api()
+    P = api.DevicePrograms.from_programset(wl.replicate(wl.random_population(12, 100, 5, 64, 5), 1000))
+    X = torch.rand((256, 5), device="cuda") + 0.5
+    a, b = (_us(lambda x=x: api.predict(P, x)) for x in (X[:64].contiguous(), X))
+    print(f"100000 programs x 64 cases {a:.0f} us, x 256 {b:.0f} us")
+    assert a < 0.85 * b
