@@ -254,7 +254,7 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   pa.long_count = reinterpret_cast<int32_t*>(ws + L.class_count) + 16;
   pa.long_list = reinterpret_cast<int32_t*>(ws + L.long_list);
   pa.layout = reinterpret_cast<int32_t*>(ws + L.class_count) + 32;
-  const bool owners = P->n_programs >= bgl::OWNER_MIN_PROGRAMS;
+  const bool owners = decoder == BEAGLE_DECODE_THREAD || P->n_programs >= bgl::OWNER_MIN_PROGRAMS;
   pa.owner = owners ? reinterpret_cast<int32_t*>(ws + L.owner) : nullptr;
   pa.cowner = owners && adjoint ? reinterpret_cast<int32_t*>(ws + L.cowner) : nullptr;
   pa.wave_programs = 64;

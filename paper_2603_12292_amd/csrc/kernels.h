@@ -53,8 +53,8 @@ struct PrepareArgs {
   // then owner / cowner hold, per token / constant slot, the lowest index of
   // a program whose range covers it, and a program finding another index in
   // its range gets BEAGLE_PROG_BAD_LAYOUT.
-  // On few programs (OWNER_MIN_PROGRAMS) owner and cowner are null and each
-  // program of a flagged layout looks through the lower-indexed ones itself.
+  // On few programs (OWNER_MIN_PROGRAMS) owner and cowner are null where a wave
+  // decodes or folds a program, and it looks through the lower-indexed ones itself.
   int32_t* layout;
   int32_t* owner;   // [n_tokens]
   int32_t* cowner;  // [n_consts] (adjoint only)
@@ -231,8 +231,10 @@ __device__ __forceinline__ int batch_find(const BatchArgs& b, int64_t x, F field
   return lo;
 }
 
-// programs from which the owner arrays are filled: two launches, for a check
-// that otherwise reads every lower-indexed header only where a layout is flagged
+// programs from which the owner arrays are filled: two launches, for a check that
+// otherwise reads every lower-indexed header only where a layout is flagged.  Below
+// it the waves of k_prepare_wave and k_fold read them (PrepareArgs::layout); the
+// decoders with a thread per program always have the arrays
 constexpr int32_t OWNER_MIN_PROGRAMS = 4097;
 constexpr int EVAL_WAVES = 4;
 // rows a wave keeps in flight: two are enough behind the other waves of a

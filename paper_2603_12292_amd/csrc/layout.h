@@ -28,4 +28,24 @@ __device__ __forceinline__ bool overlaps(const PrepareArgs& a, int q, int64_t of
   return a.adjoint && const_range(a, q, o, n) && n > 0 && cc > 0 && o < coff + cc && coff < o + n;
 }
 
+// Whether no lower-indexed program's range meets program p's: the whole wave
+// looks through them, four of its rounds at a time (a round is one latency:
+// 4000 programs in shuffled order, 62 rounds, ~10 us).  A thread by itself would
+// take 64 times as long, so the kernels that decode with one have the owner
+// arrays.
+__device__ __forceinline__ bool wave_alone(const PrepareArgs& a, int p, int64_t off, int32_t L, int64_t coff,
+                                           int32_t cc) {
+  const int lane = int(threadIdx.x & 63u);
+  for (int q0 = 0; q0 < p; q0 += 256) {
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = q0 + r * 64 + lane;
+      bad |= q < p && overlaps(a, q, off, L, coff, cc);
+    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) return false;
+  }
+  return true;
+}
+
 }  // namespace bgl

@@ -92,12 +92,8 @@ struct ListIds {
 // else when every slot of its ranges carries its own index as the lowest
 // covering one (see PrepareArgs::layout).
 __device__ static bool owns_ranges(const PrepareArgs& a, int p, int64_t off, int32_t L, int64_t coff, int32_t cc) {
-  if (!a.layout || !(a.layout[0] | a.layout[1])) return true;
-  if (!a.owner) {
-    for (int q = 0; q < p; ++q)
-      if (overlaps(a, q, off, L, coff, cc)) return false;
-    return true;
-  }
+  // (no owner arrays: k_prepare_wave has looked, before it listed the program)
+  if (!a.layout || !a.owner || !(a.layout[0] | a.layout[1])) return true;
   if (a.layout[0])
     for (int32_t i = 0; i < L; ++i)
       if (a.owner[off + i] != p) return false;
@@ -649,11 +645,8 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
   if (status == BEAGLE_PROG_OK && (lay_tok | lay_const)) {
     // ranges not sorted and disjoint: every slot must carry p as its owner
     bool mine = true;
-    if (!a.owner) {
-      for (int q0 = 0; q0 < p && mine; q0 += 64)
-        mine = __builtin_amdgcn_ballot_w64(q0 + lane < p && overlaps(a, q0 + lane, off, L, coff, cc)) == 0;
-    } else if (lay_tok) mine = __builtin_amdgcn_ballot_w64(lane < L && a.owner[off + lane] != p) == 0;
-    if (ADJ && mine && lay_const && a.owner)
+    if (lay_tok) mine = __builtin_amdgcn_ballot_w64(lane < L && a.owner[off + lane] != p) == 0;
+    if (ADJ && mine && lay_const)
       for (int32_t j0 = 0; j0 < cc && mine; j0 += 64)
         mine = __builtin_amdgcn_ballot_w64(j0 + lane < cc && a.cowner[coff + j0 + lane] != p) == 0;
     if (!mine) status = BEAGLE_PROG_BAD_LAYOUT;
@@ -1193,11 +1186,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
   const int nb = base < a.n_programs ? int(a.n_programs - base < ppw ? a.n_programs - base : ppw) : 0;
   // the header's own checks (lane j: program j): no tokens, or token or
   // constant range outside its array
-  const int hst = hL == 0 ? BEAGLE_PROG_EMPTY
-                  : hL < 0 || hoff < 0 || hoff + hL > a.n_tokens || hcc < 0 ||
-                            (hcc > 0 && (hcoff < 0 || hcoff + hcc > a.n_consts))
-                      ? BEAGLE_PROG_BAD_LAYOUT
-                      : BEAGLE_PROG_OK;
+  int hst = hL == 0 ? BEAGLE_PROG_EMPTY
+            : hL < 0 || hoff < 0 || hoff + hL > a.n_tokens || hcc < 0 ||
+                      (hcc > 0 && (hcoff < 0 || hcoff + hcc > a.n_consts))
+                ? BEAGLE_PROG_BAD_LAYOUT
+                : BEAGLE_PROG_OK;
+  // the disjoint-ranges flags (set before this kernel): with the owner arrays
+  // each program's slots are looked up as it is decoded, without them the wave
+  // looks here (longer programs too: k_prepare_long has no wave for each)
+  const int flag_tok = a.layout ? a.layout[0] : 0;
+  const int flag_const = a.layout && ADJ ? a.layout[1] : 0;
+  if (!a.owner && (flag_tok | flag_const))
+    for (int j = 0; j < nb; ++j) {
+      const int32_t L = __builtin_amdgcn_readlane(hL, j);
+      if (__builtin_amdgcn_readlane(hst, j) != BEAGLE_PROG_OK || L > MAX_LEN) continue;
+      if (!wave_alone(a, int(base + j), lane64(hoff, j), L, lane64(hcoff, j), __builtin_amdgcn_readlane(hcc, j)))
+        hst = wdec::sel(lane == j, int(BEAGLE_PROG_BAD_LAYOUT), hst);
+    }
+  const int lay_tok = a.owner ? flag_tok : 0;
+  const int lay_const = a.owner ? flag_const : 0;
   const uint64_t fetch_ok = __builtin_amdgcn_ballot_w64(hst == BEAGLE_PROG_OK && hL <= PREP_NARROW);
   // the lane's token of program j, where program j is decoded here and its
   // header passed (else 0: the decoder reports the header's status)
@@ -1206,9 +1213,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
     const bool ok = ((fetch_ok >> j) & 1u) && lane < L;
     return ok ? uint32_t(a.tokens[lane64(hoff, j) + lane]) : 0u;
   };
-  // the disjoint-ranges flags (set before this kernel)
-  const int lay_tok = a.layout ? a.layout[0] : 0;
-  const int lay_const = a.layout && ADJ ? a.layout[1] : 0;
   int cls = -1, lc = -1;
   // program j's header fields, held by lane j and stored together at the end
   int32_t head = 0;
@@ -1220,7 +1224,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
       const uint32_t t = t_next;
       if (j + 1 < nb) t_next = fetch(j + 1);
       const int32_t L = __builtin_amdgcn_readlane(hL, j);
-      if (L > PREP_NARROW) {
+      // (a bad header's length is still checked first by k_prepare_long)
+      if (L > PREP_NARROW && (L > MAX_LEN || __builtin_amdgcn_readlane(hst, j) == BEAGLE_PROG_OK)) {
         defer |= lane == j;
         continue;
       }
@@ -1289,7 +1294,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
       const int jn = rest ? take(rest) : -1;
       if (jn >= 0) t_next = fetch(jn);
       const int32_t L = __builtin_amdgcn_readlane(hL, j);
-      if (L > PREP_NARROW) {
+      // (a bad header's length is still checked first by k_prepare_long)
+      if (L > PREP_NARROW && (L > MAX_LEN || __builtin_amdgcn_readlane(hst, j) == BEAGLE_PROG_OK)) {
         defer |= lane == j;
       } else {
         const ListIds ids = decode_wave<false>(a, int(base + j), lane64(hoff, j), L, lane64(hcoff, j),
