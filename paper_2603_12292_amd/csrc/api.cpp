@@ -782,7 +782,8 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   const int kv = data->M <= bgl::CHUNK_UNIT ? 1 : 0;
   hipError_t e = bgl::launch_eval(bgl::KIND_OUTPUTS, kv, ea, s, nullptr, nullptr, true);
   if (e != hipSuccess) return hip_fail(e, "eval launch");
-  hipLaunchKernelGGL(bgl::k_nan_rows, dim3(progs->n_programs), dim3(256), 0, s, ea.meta, data->M, yhat);
+  hipLaunchKernelGGL(bgl::k_nan_rows, dim3(std::min(progs->n_programs, 1 << 22)), dim3(256), 0, s, ea.meta,
+                     progs->n_programs, data->M, yhat);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "nan rows launch");
   clear_error();

@@ -897,9 +897,12 @@ __global__ void __launch_bounds__(64) k_outputs_small(ValuesArgs a, int64_t M, i
   if (i < M) out[int64_t(p) * M + i] = top[0];
 }
 
-__global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int64_t M, float* out) {
-  if (meta[blockIdx.x].status == BEAGLE_PROG_OK) return;
-  for (int64_t i = threadIdx.x; i < M; i += 256) out[int64_t(blockIdx.x) * M + i] = __int_as_float(0x7FC00000);
+__global__ void __launch_bounds__(256) k_nan_rows(const ProgMeta* meta, int32_t n_programs, int64_t M,
+                                                  float* out) {
+  for (int64_t p = blockIdx.x; p < n_programs; p += gridDim.x) {
+    if (meta[p].status == BEAGLE_PROG_OK) continue;
+    for (int64_t i = threadIdx.x; i < M; i += 256) out[p * M + i] = __int_as_float(0x7FC00000);
+  }
 }
 
 // Fitness of every program from its chunk partials.  Up to

@@ -103,7 +103,7 @@ __global__ void __launch_bounds__(256) k_fold(FoldArgs f) {
   __shared__ unsigned long long lds_keep[4];
   const PrepareArgs& a = f.in;
   const int lane = int(threadIdx.x & 63u), w = int(threadIdx.x >> 6);
-  const int p = __builtin_amdgcn_readfirstlane(int(blockIdx.x) * 4 + w);
+  const int p = __builtin_amdgcn_readfirstlane(f.first + int(blockIdx.x) * 4 + w);
   if (p >= a.n_programs) return;  // (no barrier below)
   uint32_t* st = lds_t[w];
   float* sv = lds_v[w];
@@ -290,11 +290,17 @@ __global__ void __launch_bounds__(256) k_fold(FoldArgs f) {
 }
 
 void launch_fold(const FoldArgs& f, hipStream_t s) {
-  const uint32_t grid = uint32_t((f.in.n_programs + 3) / 4);
-  if (f.in.adjoint)
-    hipLaunchKernelGGL(k_fold<true>, dim3(grid), dim3(256), 0, s, f);
-  else
-    hipLaunchKernelGGL(k_fold<false>, dim3(grid), dim3(256), 0, s, f);
+  // (a grid has fewer than 2^32 threads, and a program takes 64)
+  constexpr int32_t LAUNCH = 1 << 24;
+  FoldArgs g = f;
+  for (int64_t first = 0; first < f.in.n_programs; first += LAUNCH) {
+    g.first = int32_t(first);
+    const uint32_t grid = uint32_t((std::min<int64_t>(f.in.n_programs - first, LAUNCH) + 3) / 4);
+    if (f.in.adjoint)
+      hipLaunchKernelGGL(k_fold<true>, dim3(grid), dim3(256), 0, s, g);
+    else
+      hipLaunchKernelGGL(k_fold<false>, dim3(grid), dim3(256), 0, s, g);
+  }
 }
 
 }  // namespace bgl

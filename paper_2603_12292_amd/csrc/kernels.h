@@ -67,6 +67,7 @@ struct PrepareArgs {
 // for the programs that are kept as they are).
 struct FoldArgs {
   PrepareArgs in;         // the caller's programs and the ranges check's results
+  int32_t first;          // (set by launch_fold) the launch's first program
   uint16_t* tokens;       // [n_tokens]
   int32_t* tok_len;       // [n_programs]; -1: the ranges check failed
   float* consts;          // [n_consts + n_tokens]
@@ -323,8 +324,9 @@ __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* _
 void launch_finalize(const FinalizeArgs& a, hipStream_t s);
 __global__ void k_shifts(ValuesArgs a);
 __global__ void k_outputs_small(ValuesArgs a, int64_t M, int32_t D, float* out);
-// NaN rows of the invalid programs of a prediction (a workgroup per program)
-__global__ void k_nan_rows(const ProgMeta* meta, int64_t M, float* out);
+// NaN rows of the invalid programs of a prediction (a workgroup per program, and
+// the programs a grid apart)
+__global__ void k_nan_rows(const ProgMeta* meta, int32_t n_programs, int64_t M, float* out);
 // host launchers of the templated evaluation kernels (eval.hip)
 // ev0/ev1 (may be null) are recorded on `s` right before and after the
 // fast-path kernel.
