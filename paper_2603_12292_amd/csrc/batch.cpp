@@ -48,6 +48,7 @@ constexpr size_t MAX_GRAPHS = 8;
 struct Batch {
   bgl::BatchArgs args;
   int has[bgl::N_LISTS];
+  bool owners = false;  // some problem's ranges check uses the owner arrays
   int64_t n_programs = 0, n_cases = 0;
   int n = 0;
 };
@@ -57,8 +58,10 @@ hipError_t enqueue(const Batch& b, int32_t* counts, hipStream_t s) {
   zero_i32(counts, int64_t(64) * b.n, s);
   const uint32_t pgrid = uint32_t((b.n_programs + 255) / 256);
   hipLaunchKernelGGL(bgl::k_layout_check_batch, dim3(pgrid), dim3(256), 0, s, b.args);
-  hipLaunchKernelGGL(bgl::k_layout_fill_batch, dim3(64, uint32_t(b.n)), dim3(256), 0, s, b.args);
-  hipLaunchKernelGGL(bgl::k_layout_mark_batch, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, b.args);
+  if (b.owners) {
+    hipLaunchKernelGGL(bgl::k_layout_fill_batch, dim3(64, uint32_t(b.n)), dim3(256), 0, s, b.args);
+    hipLaunchKernelGGL(bgl::k_layout_mark_batch, dim3(std::min<uint32_t>(pgrid, 1024)), dim3(256), 0, s, b.args);
+  }
   hipLaunchKernelGGL(bgl::k_prepare_batch, dim3(uint32_t((b.n_programs + 63) / 64)), dim3(64), 0, s, b.args);
   hipLaunchKernelGGL(bgl::k_stage_batch, dim3(uint32_t((b.n_cases + 255) / 256)), dim3(256), 0, s, b.args);
   if (b.args.kind == BEAGLE_FIT_CORR) {
@@ -217,7 +220,8 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     pa.long_count = nullptr;  // k_prepare_batch decodes every program itself
     pa.long_list = nullptr;
     pa.layout = counts + int64_t(64) * i + 32;
-    pa.owner = reinterpret_cast<int32_t*>(ws + o.owner);
+    pa.owner = P.n_programs >= bgl::OWNER_MIN_BATCH ? reinterpret_cast<int32_t*>(ws + o.owner) : nullptr;
+    b.owners |= pa.owner != nullptr;
     pa.cowner = nullptr;
     pa.wave_programs = 64;
     t.X = d.X;

@@ -234,9 +234,12 @@ __device__ __forceinline__ int batch_find(const BatchArgs& b, int64_t x, F field
 
 // programs from which the owner arrays are filled: two launches, for a check that
 // otherwise reads every lower-indexed header only where a layout is flagged.  Below
-// it the waves of k_prepare_wave and k_fold read them (PrepareArgs::layout); the
-// decoders with a thread per program always have the arrays
+// it the waves of k_prepare_wave and k_fold read them (PrepareArgs::layout).  A
+// decoder with a thread per program has the arrays, in a batch from
+// OWNER_MIN_BATCH programs of a problem on: 64 headers take a thread about as
+// long as the launches (16 problems of 32 programs in order 156 -> 151 us)
 constexpr int32_t OWNER_MIN_PROGRAMS = 4097;
+constexpr int32_t OWNER_MIN_BATCH = 65;
 constexpr int EVAL_WAVES = 4;
 // rows a wave keeps in flight: two are enough behind the other waves of a
 // SIMD, and four cost the fifth of them (the workgroup's 32 KB leave room for

@@ -92,8 +92,13 @@ struct ListIds {
 // else when every slot of its ranges carries its own index as the lowest
 // covering one (see PrepareArgs::layout).
 __device__ static bool owns_ranges(const PrepareArgs& a, int p, int64_t off, int32_t L, int64_t coff, int32_t cc) {
-  // (no owner arrays: k_prepare_wave has looked, before it listed the program)
-  if (!a.layout || !a.owner || !(a.layout[0] | a.layout[1])) return true;
+  if (!a.layout || !(a.layout[0] | a.layout[1])) return true;
+  if (!a.owner) {
+    if (a.long_list) return true;  // (k_prepare_wave has looked, before it listed the program)
+    for (int q = 0; q < p; ++q)    // (a batch of few programs a problem)
+      if (overlaps(a, q, off, L, coff, cc)) return false;
+    return true;
+  }
   if (a.layout[0])
     for (int32_t i = 0; i < L; ++i)
       if (a.owner[off + i] != p) return false;

@@ -45,7 +45,7 @@ def _shared(off, n):
     return out
 
 
-@pytest.mark.parametrize("N,len_hi", [(70, 12), (300, 90), (4096, 60), (4097, 90), (5000, 16)])
+@pytest.mark.parametrize("N,len_hi", [(64, 70), (70, 12), (300, 90), (4096, 60), (4097, 90), (5000, 16)])
 @pytest.mark.parametrize("M", [40, 520])
 def test_shared_ranges_are_bad_layout(N, len_hi, M):
     api = _api()
