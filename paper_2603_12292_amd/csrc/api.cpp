@@ -52,11 +52,19 @@ beagle_status reserve(beagle_ctx* ctx, size_t bytes) {
   if (!ctx->cap) want = std::max(want, bytes + bytes / 4);
   if (ctx->cap) want = std::min(want, ctx->cap);
   e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), want);
+  if (e != hipSuccess && want > bytes) {
+    (void)hipGetLastError();
+    want = bytes;
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->ws), want);
+  }
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // (the next launch's check would find it)
     ctx->ws = nullptr;
+    ctx->refused = ctx->refused ? std::min(ctx->refused, bytes) : bytes;
     return fail(BEAGLE_E_NOMEM, std::string("hipMalloc of workspace failed: ") + hipGetErrorString(e));
   }
   ctx->ws_size = want;
+  if (bytes >= ctx->refused) ctx->refused = 0;  // (there is memory again)
   return BEAGLE_OK;
 }
 
@@ -98,7 +106,11 @@ void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int6
   *n_chunks = int32_t((M + ch - 1) / ch);
 }
 
-void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks) {
+void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int level) {
+  if (level == LEVEL_LEAST) {
+    choose_chunks(M, N, chunk, n_chunks, 32768, 4 * bgl::TILE);
+    return;
+  }
   // chunks of whole wide tiles, of half tiles where those leave under 4096
   // work items; at most 1024 chunks, or as many as make CHUNK_ITEMS items
   const int64_t most = std::max<int64_t>(bgl::CHUNK_CASES, round_up((M + 1023) / 1024, bgl::TILE));
@@ -128,8 +140,8 @@ using namespace bgl::host;
 
 // The pieces of workspace one evaluation uses.
 struct EvalLayout {
-  size_t code, aux, vrow, cval, s_stack, s_start, s_need, owner, cowner, meta, class_count, class_list, len_list,
-      long_list, work, Xt, stats, part, gpart, coef, total;
+  size_t code, aux, vrow, cval, scr, owner, cowner, meta, class_count, class_list, len_list, long_list,
+      work, Xt, stats, part, gpart, coef, total;
   size_t f_tokens, f_len, f_consts, f_coff, f_cc, f_mapn, f_maps, f_mapd;  // folded programs (fold)
   int32_t fold;                   // constant subtrees folded
   int32_t derived, rows;          // derived input rows staged; rows per staged tile
@@ -138,17 +150,16 @@ struct EvalLayout {
   int32_t n_chunks, gn_chunks, slice;
 };
 
-// extras: the workspace that only speed needs (derived rows, folded
-// programs); false where it does not fit.
-EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, bool extras,
+EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_sums, int32_t slice, int level,
                        bool with_grad = false) {
   EvalLayout L{};
+  const bool extras = level == LEVEL_FULL;
   Carve c;
   const int64_t nt = std::max<int64_t>(P->n_tokens, 1);
   const int64_t N = std::max<int32_t>(P->n_programs, 1);
   // the chunking depends on the whole population only, so that a sliced
   // evaluation sums every program's partials in the same order
-  eval_chunks(d->M, N, &L.chunk, &L.n_chunks);
+  eval_chunks(d->M, N, &L.chunk, &L.n_chunks, level);
   bool derived = extras && !with_grad && use_derived(N, d->M, d->D);
   if (derived && bgl::resident_call(N, L.n_chunks, d->M, bgl::stage_rows(d->D, 0))) {
     const bool table = bgl::resident_call(N, L.n_chunks, d->M, bgl::stage_rows(d->D, 1));
@@ -169,9 +180,7 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   // (the row lists, a byte per token: an evaluation writes no adjoint words)
   L.vrow = with_grad ? c.take<uint8_t>(nt) : L.aux;
   L.cval = c.take<float>(nt);
-  L.s_stack = c.take<int32_t>(nt);
-  L.s_start = c.take<int32_t>(nt);
-  L.s_need = c.take<int32_t>(nt);
+  L.scr = c.take<uint16_t>(3 * nt);
   L.owner = c.take<int32_t>(nt);
   L.cowner = with_grad ? c.take<int32_t>(std::max<int64_t>(P->n_consts, 1)) : 0;
   L.meta = c.take<bgl::ProgMeta>(N);
@@ -183,12 +192,12 @@ EvalLayout eval_layout(const beagle_programs* P, const beagle_dataset* d, int n_
   L.gchunk = 0;
   L.gn_chunks = 0;
   if (with_grad) choose_chunks(d->M, N, &L.gchunk, &L.gn_chunks, bgl::GRAD_CHUNK_CASES, bgl::GRAD_TILE_CASES,
-                               16384);
-  L.work_shift = bgl::counter_shift(N * std::max(L.n_chunks, L.gn_chunks));
+                               level == LEVEL_LEAST ? 4096 : 16384);
+  L.work_shift = level == LEVEL_LEAST ? 0 : bgl::counter_shift(N * std::max(L.n_chunks, L.gn_chunks));
   L.work_words = (with_grad ? bgl::GRAD_LISTS : bgl::N_CLASSES) * bgl::counter_words(L.work_shift);
   L.work = c.take<unsigned long long>(L.work_words);
   L.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
-  L.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
+  L.len_list = with_grad ? c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N) : 0;
   L.long_list = c.take<int32_t>(size_t(N));
   L.Mp = round_up(d->M, bgl::TILE);
   L.Xt = c.take<float>(size_t(L.rows) * L.Mp);
@@ -240,9 +249,7 @@ beagle_status prepare(char* ws, const beagle_programs* P, const beagle_dataset* 
   pa.vrow = reinterpret_cast<uint8_t*>(ws + L.vrow);
   pa.derived = L.derived;
   pa.max_words = max_words;
-  pa.scr_stack = reinterpret_cast<int32_t*>(ws + L.s_stack);
-  pa.scr_start = reinterpret_cast<int32_t*>(ws + L.s_start);
-  pa.scr_need = reinterpret_cast<int32_t*>(ws + L.s_need);
+  pa.scr = reinterpret_cast<uint16_t*>(ws + L.scr);
   pa.meta = reinterpret_cast<bgl::ProgMeta*>(ws + L.meta);
   pa.status_out = status;
   pa.class_count = reinterpret_cast<int32_t*>(ws + L.class_count);
@@ -540,18 +547,17 @@ beagle_status beagle_ctx_set_tuning(beagle_ctx* ctx, int policy) {
 
 namespace {
 
-// Layout of a whole-population evaluation within `cap` bytes of workspace
-// (0: unlimited): the largest program slice whose partials fit.
-EvalLayout capped_layout(const beagle_programs* progs, const beagle_dataset* data, int kind, size_t cap,
+// Layout of a whole-population evaluation at a level within `cap` bytes of
+// workspace (0: unlimited): the largest program slice whose partials fit (below
+// the full level, which is for whole populations).
+EvalLayout capped_layout(const beagle_programs* progs, const beagle_dataset* data, int kind, size_t cap, int level,
                          int32_t* slice_out) {
   const int n_sums = bgl::kind_sums(kind);
   int32_t slice = progs->n_programs;
-  EvalLayout L = eval_layout(progs, data, n_sums, slice, true);
-  // without the extras where they do not fit (the same values)
-  if (cap && L.total > cap) L = eval_layout(progs, data, n_sums, slice, false);
-  while (cap && L.total > cap && slice > 1) {
+  EvalLayout L = eval_layout(progs, data, n_sums, slice, level);
+  while (level != LEVEL_FULL && cap && L.total > cap && slice > 1) {
     slice = (slice + 1) / 2;
-    L = eval_layout(progs, data, n_sums, slice, false);
+    L = eval_layout(progs, data, n_sums, slice, level);
   }
   *slice_out = slice;
   return L;
@@ -646,8 +652,11 @@ beagle_status evaluate(beagle_ctx* ctx, const beagle_programs* progs, const beag
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   int32_t slice = 0;
-  const EvalLayout L = capped_layout(progs, data, kind, ctx->cap, &slice);
-  st = reserve(ctx, L.total);
+  EvalLayout L;
+  st = reserve_first(ctx, [&](int level) {
+    L = capped_layout(progs, data, kind, ctx->cap, level, &slice);
+    return L.total;
+  });
   if (st != BEAGLE_OK) return st;
   st = evaluate_in(ctx->ws, L, slice, ctx, progs, data, kind, smax, fitness, status, s);
   if (st != BEAGLE_OK) return st;
@@ -692,7 +701,11 @@ beagle_status beagle_eval_static(const beagle_programs* progs, const beagle_data
   if (progs->n_programs == 0) return BEAGLE_OK;
   if (!fitness) return fail(BEAGLE_E_INVALID_ARG, "fitness is NULL");
   int32_t slice = 0;
-  const EvalLayout L = capped_layout(progs, data, kind, BEAGLE_STATIC_SCRATCH_BYTES, &slice);
+  EvalLayout L;
+  for (int level = LEVEL_FULL; level < N_LEVELS; ++level) {
+    L = capped_layout(progs, data, kind, BEAGLE_STATIC_SCRATCH_BYTES, level, &slice);
+    if (L.total <= BEAGLE_STATIC_SCRATCH_BYTES) break;
+  }
   if (L.total > BEAGLE_STATIC_SCRATCH_BYTES)
     return fail(BEAGLE_E_NOMEM, "beagle_eval_static: the evaluation needs " + std::to_string(L.total) +
                                     " bytes of scratch, the static array holds " +
@@ -740,7 +753,7 @@ beagle_status beagle_eval_workspace_size(const beagle_programs* progs, const bea
   if (st != BEAGLE_OK) return st;
   st = check_data(data, kind);
   if (st != BEAGLE_OK) return st;
-  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1), true).total;
+  *bytes = eval_layout(progs, data, bgl::kind_sums(kind), std::max(progs->n_programs, 1), LEVEL_FULL).total;
   return BEAGLE_OK;
 }
 
@@ -760,9 +773,11 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool small = bgl::small_outputs(progs->n_programs, data->M);
-  EvalLayout L = eval_layout(progs, data, 1, 1, !small);
-  if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, 1, 1, false);
-  st = reserve(ctx, L.total);
+  EvalLayout L;
+  st = reserve_first(ctx, [&](int level) {
+    L = eval_layout(progs, data, 1, 1, small && level == LEVEL_FULL ? LEVEL_BARE : level);
+    return L.total;
+  });
   if (st != BEAGLE_OK) return st;
   st = prepare(ctx->ws, progs, data, L, status, s, ctx->decoder);
   if (st != BEAGLE_OK) return st;
@@ -1067,9 +1082,11 @@ beagle_status beagle_eval_grad(beagle_ctx* ctx, const beagle_programs* progs, co
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool corr = kind == BEAGLE_FIT_CORR;
-  EvalLayout L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, true, true);
-  if (ctx->cap && L.total > ctx->cap) L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, false, true);
-  st = reserve(ctx, L.total);
+  EvalLayout L;
+  st = reserve_first(ctx, [&](int level) {
+    L = eval_layout(progs, data, corr ? 3 : 1, progs->n_programs, level, true);
+    return L.total;
+  });
   if (st != BEAGLE_OK) return st;
   hipEvent_t join = nullptr;
   if (corr && (st = launch_target_stats(ctx, data, reinterpret_cast<double*>(ctx->ws + L.stats), s, &join)) !=

@@ -120,25 +120,25 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
   });
   const int n = int(active.size());
 
-  // workspace layout, with derived input rows where they fit
+  // workspace layout (see Level)
   struct Off {
-    size_t code, aux, cval, s_stack, s_start, s_need, owner, meta, class_list, len_list, Xt, stats, part;
+    size_t code, aux, cval, scr, owner, meta, class_list, Xt, stats, part;
     int64_t Mp, chunk;
     int32_t n_chunks, derived;
   };
   std::vector<Off> off(n);
   size_t at_table = 0, at_items = 0, at_work = 0, at_counts = 0;
   int work_shift = 0;
-  auto lay_out = [&](bool derived) {
+  auto lay_out = [&](int level) {
     Carve c;
     at_table = c.take<bgl::BatchProblem>(n);
     at_items = c.take<int64_t>(size_t(bgl::N_LISTS) * (n + 1));
     int64_t batch_items = 0;  // (of the longest list at most)
     for (int i = 0; i < n; ++i) {
-      eval_chunks(data[active[i]].M, progs[active[i]].n_programs, &off[i].chunk, &off[i].n_chunks);
+      eval_chunks(data[active[i]].M, progs[active[i]].n_programs, &off[i].chunk, &off[i].n_chunks, level);
       batch_items += int64_t(progs[active[i]].n_programs) * off[i].n_chunks;
     }
-    work_shift = bgl::counter_shift(batch_items);
+    work_shift = level == LEVEL_LEAST ? 0 : bgl::counter_shift(batch_items);
     at_work = c.take<unsigned long long>(size_t(bgl::N_LISTS) * bgl::counter_words(work_shift));
     at_counts = c.take<int32_t>(size_t(64) * n);
     for (int i = 0; i < n; ++i) {
@@ -147,17 +147,14 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
       const int64_t nt = std::max<int64_t>(P.n_tokens, 1);
       const int64_t N = P.n_programs;
       Off& o = off[i];
-      o.derived = derived && use_derived(N, d.M, d.D) ? 1 : 0;
+      o.derived = level == LEVEL_FULL && use_derived(N, d.M, d.D) ? 1 : 0;
       o.code = c.take<uint32_t>(nt);
       o.aux = c.take<uint32_t>(nt);
       o.cval = c.take<float>(nt);
-      o.s_stack = c.take<int32_t>(nt);
-      o.s_start = c.take<int32_t>(nt);
-      o.s_need = c.take<int32_t>(nt);
+      o.scr = c.take<uint16_t>(3 * nt);
       o.owner = c.take<int32_t>(nt);
       o.meta = c.take<bgl::ProgMeta>(N);
       o.class_list = c.take<int32_t>(size_t(bgl::N_CLASSES) * N);
-      o.len_list = c.take<int32_t>(size_t(bgl::GRAD_LISTS) * N);
       o.Mp = round_up(d.M, bgl::TILE);
       o.Xt = c.take<float>(size_t(bgl::stage_rows(d.D, o.derived)) * o.Mp);
       o.stats = c.take<double>(4);
@@ -165,9 +162,7 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     }
     return c.used + 256;
   };
-  size_t need = lay_out(true);
-  if (ctx->cap && need > ctx->cap) need = lay_out(false);
-  beagle_status st = reserve(ctx, need);
+  beagle_status st = reserve_first(ctx, lay_out);
   if (st != BEAGLE_OK) return st;
   char* ws = ctx->ws;
 
@@ -206,15 +201,13 @@ beagle_status beagle_eval_batched(beagle_ctx* ctx, const beagle_programs* progs,
     pa.vrow = reinterpret_cast<uint8_t*>(ws + o.aux);  // (no adjoint words here)
     pa.derived = o.derived;
     pa.max_words = bgl::MAX_LEN;
-    pa.scr_stack = reinterpret_cast<int32_t*>(ws + o.s_stack);
-    pa.scr_start = reinterpret_cast<int32_t*>(ws + o.s_start);
-    pa.scr_need = reinterpret_cast<int32_t*>(ws + o.s_need);
+    pa.scr = reinterpret_cast<uint16_t*>(ws + o.scr);
     pa.meta = reinterpret_cast<bgl::ProgMeta*>(ws + o.meta);
     pa.status_out = status ? status[q] : nullptr;
     pa.class_count = counts + int64_t(64) * i;
     pa.class_list = reinterpret_cast<int32_t*>(ws + o.class_list);
     pa.len_count = counts + int64_t(64) * i + 8;
-    pa.len_list = reinterpret_cast<int32_t*>(ws + o.len_list);
+    pa.len_list = nullptr;  // (the adjoint's)
     pa.short_words = bgl::GRAD_SHORT_WORDS;
     pa.adjoint = 0;
     pa.long_count = nullptr;  // k_prepare_batch decodes every program itself

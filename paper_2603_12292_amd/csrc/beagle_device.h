@@ -323,11 +323,11 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Per-program metadata written by the preparation kernel.
 struct ProgMeta {
   int32_t status;  // BEAGLE_PROG_* code
-  int32_t need;    // register need of the expression tree (max stack size)
   int32_t len;     // decoded instruction words (fused pairs count once)
   float shift;     // correlation fitness: the program's output at case 0
   uint32_t vmask;  // bit d set: the program reads input variable d (the adjoint stages only those)
   int32_t nv;      // VAR words (entries of the program's row list)
 };
+static_assert(sizeof(ProgMeta) == 20, "part of every call's workspace");
 
 }  // namespace bgl

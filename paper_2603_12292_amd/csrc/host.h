@@ -47,6 +47,7 @@ struct beagle_ctx {
   std::map<bgl::host::TuneKey, int> tuned;  // bucket -> tile variant (0 wide, 1 narrow)
   std::string tune_file;                    // BEAGLE_AUTOTUNE_CACHE at creation ("" = none)
   // batched evaluation
+  size_t refused = 0;  // bytes of the smallest workspace that could not be allocated (0: none)
   std::vector<bgl::host::BatchGraph> graphs;
   hipStream_t capture_stream = nullptr;  // graphs are captured here, launched on the caller's stream
   std::vector<bgl::BatchProblem> table;  // host copy of the last uploaded problem table
@@ -91,6 +92,24 @@ struct Carve {
 // Grows the workspace to `bytes` (synchronises the device and drops the
 // captured graphs when it moves).
 beagle_status reserve(beagle_ctx* ctx, size_t bytes);
+// How much workspace a call is laid out with: all that speed wants; without
+// derived rows and folded programs (the same values, bit for bit); or the least,
+// with few case chunks too (sums in another order).
+enum Level { LEVEL_FULL, LEVEL_BARE, LEVEL_LEAST, N_LEVELS };
+// Reserves the first of the layouts that the cap allows and the device has
+// memory for; layout(level) makes one and returns its bytes.
+template <class F>
+beagle_status reserve_first(beagle_ctx* ctx, F layout) {
+  for (int level = LEVEL_FULL;; ++level) {
+    const size_t bytes = layout(level);
+    if (level != LEVEL_LEAST) {
+      if (ctx->cap && bytes > ctx->cap) continue;
+      if (ctx->refused && bytes >= ctx->refused && bytes > ctx->ws_size) continue;
+    }
+    const beagle_status st = reserve(ctx, bytes);
+    if (st != BEAGLE_E_NOMEM || level == LEVEL_LEAST) return st;
+  }
+}
 beagle_status check_programs(const beagle_programs* p);
 beagle_status check_data(const beagle_dataset* d, int kind);
 int64_t round_up(int64_t v, int64_t m);
@@ -100,7 +119,7 @@ int64_t round_up(int64_t v, int64_t m);
 void choose_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int64_t max_chunk_cases, int64_t unit,
                    int64_t target_blocks = 4096);
 // The evaluation's chunks (see CHUNK_CASES, CHUNK_ITEMS).
-void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks);
+void eval_chunks(int64_t M, int64_t N, int64_t* chunk, int32_t* n_chunks, int level = LEVEL_FULL);
 // Whether an evaluation of N programs on M cases stages derived input rows:
 // their computing and writing is 5 D rows' work per case, and every program
 // saves about a quarter of its own.  D = 5, 5..64 tokens: 16 programs x 10^5

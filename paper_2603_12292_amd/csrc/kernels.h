@@ -29,9 +29,7 @@ struct PrepareArgs {
   // variable" decodes to a VAR word of such a row
   int32_t derived;
   int32_t max_words;   // decoded words allowed (longer -> BEAGLE_PROG_TOO_LONG)
-  int32_t* scr_stack;  // [n_tokens] scratch
-  int32_t* scr_start;  // [n_tokens] scratch
-  int32_t* scr_need;   // [n_tokens] scratch
+  uint16_t* scr;  // [3 * n_tokens] scratch of the programs longer than 128 tokens
   ProgMeta* meta;      // [n_programs]
   int8_t* status_out;  // [n_programs] or null
   int32_t* class_count;  // [N_CLASSES] programs per register-need class

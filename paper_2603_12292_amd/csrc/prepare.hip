@@ -81,8 +81,8 @@ __device__ static void dtape_words(const uint32_t* code, uint32_t* aux, int L, S
 // list (-1: an invalid program joins none).
 struct ListIds {
   int cls = -1, lc = -1;
-  // the wave decoders' program header fields (ProgMeta): status | need << 8
-  // | len << 16 | nv << 24, and the variable mask (shift is 0 after decoding)
+  // the wave decoders' program header fields (ProgMeta): status | len << 16 |
+  // nv << 24, and the variable mask (shift is 0 after decoding)
   int32_t head = 0;
   uint32_t vmask = 0u;
 };
@@ -313,7 +313,6 @@ __device__ static ListIds prepare_program(const PrepareArgs& a, int p, ST tok, S
   }
   ProgMeta m;
   m.status = status;
-  m.need = need_root;
   m.len = status == BEAGLE_PROG_OK ? L_dec : 0;
   m.shift = 0.0f;
   m.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
@@ -472,9 +471,9 @@ __device__ static ListIds prepare_one(const PrepareArgs& a, int p, LDS& lds) {
   } else {
     // (an invalid layout is reported before any scratch access)
     const int64_t o = off >= 0 && off < a.n_tokens ? off : 0;
-    using SG = Scratch<int32_t, 1>;
-    return prepare_program(a, p, Scratch<const uint16_t, 1>{a.tokens + o}, SG{a.scr_stack + o}, SG{a.scr_start + o},
-                    SG{a.scr_need + o}, Scratch<uint32_t, 1>{a.code + o});
+    using SG = Scratch<uint16_t, 1>;  // (indices up to MAX_LEN and a flag in bit 15)
+    return prepare_program(a, p, Scratch<const uint16_t, 1>{a.tokens + o}, SG{a.scr + o}, SG{a.scr + a.n_tokens + o},
+                           SG{a.scr + 2 * a.n_tokens + o}, Scratch<uint32_t, 1>{a.code + o});
   }
 }
 
@@ -926,7 +925,7 @@ __device__ static ListIds decode_wave(const PrepareArgs& a, int p, int64_t off, 
         if (ext && ids.cls == 0) ids.cls = 1;
         ids.lc = lc_short;
       }
-      ids.head = status | (need_root << 8) | (L_dec << 16) | (__popcll(vm) << 24);
+      ids.head = status | (L_dec << 16) | (__popcll(vm) << 24);
       ids.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
       return ids;
     }
@@ -1145,7 +1144,7 @@ __device__ static ListIds decode_seg(const PrepareArgs& a, int p, int64_t off, i
     if (ext && ids.cls == 0) ids.cls = 1;
   }
   // (a program stopped by its length keeps its need)
-  ids.head = status | ((ok ? need_root : 0) << 8) | ((status == BEAGLE_PROG_OK ? L_dec : 0) << 16) |
+  ids.head = status | ((status == BEAGLE_PROG_OK ? L_dec : 0) << 16) |
              (__popcll(segbits(vm)) << 24);
   ids.vmask = status == BEAGLE_PROG_OK ? vmask : 0u;
   return ids;
@@ -1319,7 +1318,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADJ ? 
   if (lane < nb && !defer) {
     ProgMeta m;
     m.status = head & 0xFF;
-    m.need = (head >> 8) & 0xFF;
     m.len = (head >> 16) & 0xFF;
     m.shift = 0.0f;
     m.vmask = vmask;
