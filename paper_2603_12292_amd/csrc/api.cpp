@@ -768,6 +768,7 @@ beagle_status beagle_predict(beagle_ctx* ctx, const beagle_programs* progs, cons
   if (!yhat) return fail(BEAGLE_E_INVALID_ARG, "yhat is NULL");
   if (int64_t(progs->n_programs) * data->M > (int64_t(1) << 31))
     return fail(BEAGLE_E_UNSUPPORTED, "predict: n_programs * M > 2^31");
+  // (a limit of the interface: no kernel here needs it, but a caller may rely on it)
   if (data->M > 4194240) return fail(BEAGLE_E_UNSUPPORTED, "predict: M > 4194240");
   DeviceGuard g(ctx->device);
   if (g.err != hipSuccess) return hip_fail(g.err, "hipSetDevice");

@@ -1133,7 +1133,7 @@ static hipError_t launch_resident(const EvalArgs& a, hipStream_t s, hipEvent_t e
 template <int KIND>
 static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                               bool counters_clear) {
-  if (!counters_clear) 
+  if (!counters_clear)
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, a.work, N_CLASSES * counter_words(a.work_shift));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1145,8 +1145,14 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
   if (resident_call(a.n_total, a.n_chunks, a.M, a.rows)) {
     e = wide ? launch_resident<KIND, 8, 0>(a, s, ev0, ev1) : launch_resident<KIND, 4, 0>(a, s, ev0, ev1);
     if (e != hipSuccess) return e;
-    if ((e = launch_resident<KIND, 4, 1>(a, s)) != hipSuccess) return e;
-    return launch_class<KIND, 2, 0>(a, s);
+    EvalArgs d = a;  // (the classes 1 and 2; outputs don't depend on the chunks)
+    if (KIND == KIND_OUTPUTS && a.n_total < RESIDENT_MIN_DEEP_OUTPUTS) {
+      d.chunk = TILE;
+      d.n_chunks = int32_t((a.M + TILE - 1) / TILE);
+      e = launch_class<KIND, 1, 0>(d, s);
+    } else
+      e = launch_resident<KIND, 4, 1>(a, s);
+    return e != hipSuccess ? e : launch_class<KIND, 2, 0>(d, s);
   }
   if (mixed_launch(a.n_total, a.n_chunks, a.chunk)) {
     const int grid = int((int64_t(a.n_total) * a.n_chunks + EVAL_WAVES - 1) / EVAL_WAVES);

@@ -324,6 +324,11 @@ __global__ void k_target_stats(const float* __restrict__ y, int64_t M, double* _
 // (more than WIDE_FINALIZE_CHUNKS chunks: a wave per program, else a thread)
 void launch_finalize(const FinalizeArgs& a, hipStream_t s);
 __global__ void k_shifts(ValuesArgs a);
+// Programs from which class 1 of a prediction takes the resident table, which
+// leaves its kernel few waves; below, its programs are cut by tiles and streamed.
+// 16 operators: 20 000 programs x 1000 cases 291 us, streamed 228 (a wave per
+// program and 64 cases 257); x 300 177 and 149; 100 000 x 300 417 and 465.
+constexpr int64_t RESIDENT_MIN_DEEP_OUTPUTS = 65536;
 __global__ void k_outputs_small(ValuesArgs a, int64_t M, int32_t D, float* out);
 // NaN rows of the invalid programs of a prediction (a workgroup per program, and
 // the programs a grid apart)

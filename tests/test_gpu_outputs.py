@@ -73,3 +73,15 @@ def test_few_cases_cost_less_than_more():
     a, b = (_us(lambda x=x: api.predict(P, x)) for x in (X[:64].contiguous(), X))
     print(f"100000 programs x 64 cases {a:.0f} us, x 256 {b:.0f} us")
     assert a < 0.85 * b
+
+
+@pytest.mark.parametrize("N,M", [(4096, 300), (5000, 513), (20000, 100)])
+def test_further_operators_in_a_resident_prediction(N, M):
+    # class 1 of fewer than 65536 programs: cut by tiles beside class 0's table
+    api = _api()
+    base = wl.random_population(31, 200, 3, 32, 5, unary=wl.UNARY_OPS + wl.EXTENDED_OPS)
+    X = torch.rand((M, 5), device="cuda") + 0.5
+    one = api.predict(api.DevicePrograms.from_programset(base), X).cpu().numpy()
+    many = api.predict(api.DevicePrograms.from_programset(wl.replicate(base, -(-N // 200))), X).cpu().numpy()
+    for k in (0, 7, N // 200 - 1):
+        _same(one, many[200 * k:200 * k + 200].copy())
