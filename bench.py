@@ -63,7 +63,7 @@ def committed_counters(kernel: str) -> dict:
 
 def job_cores() -> int:
     """Host cores this job may use: its affinity mask, limited by the thread
-    allotment it runs under (OMP_NUM_THREADS, which a shared GPU machine sets to
+    allotment it runs under (OMP_NUM_THREADS, which a shared machine sets to
     the job's CPU share)."""
     n = len(os.sched_getaffinity(0))
     env = os.environ.get("OMP_NUM_THREADS", "")

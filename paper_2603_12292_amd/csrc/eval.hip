@@ -1142,16 +1142,20 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
   // The resident kernels take the call when there is one chunk whose rows fit
   // and enough programs to repay the copies; both give the same bits (a wave
   // adds a program's cases in the same order).
-  if (resident_call(a.n_total, a.n_chunks, a.M, a.rows)) {
+  const bool resident = resident_call(a.n_total, a.n_chunks, a.M, a.rows);
+  // the classes 1 and 2 of a prediction, whose outputs don't depend on the chunks
+  EvalArgs d = a;
+  const int64_t tiles = (a.M + TILE - 1) / TILE;
+  const bool halves = a.n_total * tiles < HALF_TILE_DEEP_OUTPUTS;
+  const bool cut = KIND == KIND_OUTPUTS && (resident ? a.n_total < RESIDENT_MIN_DEEP_OUTPUTS : halves);
+  if (cut) {
+    d.chunk = halves ? CHUNK_UNIT : TILE;
+    d.n_chunks = int32_t((a.M + d.chunk - 1) / d.chunk);
+  }
+  if (resident) {
     e = wide ? launch_resident<KIND, 8, 0>(a, s, ev0, ev1) : launch_resident<KIND, 4, 0>(a, s, ev0, ev1);
     if (e != hipSuccess) return e;
-    EvalArgs d = a;  // (the classes 1 and 2; outputs don't depend on the chunks)
-    if (KIND == KIND_OUTPUTS && a.n_total < RESIDENT_MIN_DEEP_OUTPUTS) {
-      d.chunk = TILE;
-      d.n_chunks = int32_t((a.M + TILE - 1) / TILE);
-      e = launch_class<KIND, 1, 0>(d, s);
-    } else
-      e = launch_resident<KIND, 4, 1>(a, s);
+    e = cut ? launch_class<KIND, 1, 0>(d, s) : launch_resident<KIND, 4, 1>(a, s);
     return e != hipSuccess ? e : launch_class<KIND, 2, 0>(d, s);
   }
   if (mixed_launch(a.n_total, a.n_chunks, a.chunk)) {
@@ -1164,9 +1168,9 @@ static hipError_t launch_kind(int kv, const EvalArgs& a, hipStream_t s, hipEvent
   }
   e = wide ? launch_class<KIND, 0, 0>(a, s, ev0, ev1) : launch_class<KIND, 0, 1>(a, s, ev0, ev1);
   if (e != hipSuccess) return e;
-  e = launch_class<KIND, 1, 0>(a, s);
+  e = launch_class<KIND, 1, 0>(d, s);
   if (e != hipSuccess) return e;
-  return launch_class<KIND, 2, 0>(a, s);
+  return launch_class<KIND, 2, 0>(d, s);
 }
 
 hipError_t launch_eval(int kind, int kv, const EvalArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,

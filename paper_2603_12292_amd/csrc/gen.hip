@@ -332,8 +332,8 @@ __global__ void __launch_bounds__(256) k_generation(GenStepArgs a) {
   }
 }
 
-// Children per wave: 32 (64 left the second phase's last waves alone: 243
-// against 228 us for 10^6 children), fewer (not below the GEN_GROUPS that the second
+// Children per wave: 32 (64 left the second phase's last waves alone: 6 % longer
+// for 10^6 children, 250 us), fewer (not below the GEN_GROUPS that the second
 // phase writes at a time) where that would leave under 8192 waves, eight per
 // SIMD: the phases are chains of dependent reads, which only other waves hide.
 void launch_generation(GenStepArgs a, hipStream_t s) {

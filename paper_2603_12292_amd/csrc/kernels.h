@@ -329,6 +329,11 @@ __global__ void k_shifts(ValuesArgs a);
 // 16 operators: 20 000 programs x 1000 cases 291 us, streamed 228 (a wave per
 // program and 64 cases 257); x 300 177 and 149; 100 000 x 300 417 and 465.
 constexpr int64_t RESIDENT_MIN_DEEP_OUTPUTS = 65536;
+// Tiles of a prediction below which its classes 1 and 2 are cut by half tiles: their
+// kernels hold 4096 waves, and little more than that in whole tiles ends in a round
+// that is nearly empty.  1000 programs x 3000 cases 71 us, in half tiles 65; 5000 x
+// 500 83 and 76; 1000 x 10 000 (20 000 tiles) 127 and 145.
+constexpr int64_t HALF_TILE_DEEP_OUTPUTS = 12288;
 __global__ void k_outputs_small(ValuesArgs a, int64_t M, int32_t D, float* out);
 // NaN rows of the invalid programs of a prediction (a workgroup per program, and
 // the programs a grid apart)

@@ -1,5 +1,5 @@
 #!/bin/bash
-# rocprofv3 passes over the evaluator and their summaries (run on a GPU machine).
+# rocprofv3 passes over the evaluator and their summaries (run where the GPU is).
 #
 #   paper_2603_12292_amd/profile.sh main OUTDIR PREFIX
 #       kernel trace of the benchmark's main line, then one counter pass each
