@@ -235,7 +235,7 @@ __device__ __forceinline__ int batch_find(const BatchArgs& b, int64_t x, F field
 // it the waves of k_prepare_wave and k_fold read them (PrepareArgs::layout).  A
 // decoder with a thread per program has the arrays, in a batch from
 // OWNER_MIN_BATCH programs of a problem on: 64 headers take a thread about as
-// long as the launches (16 problems of 32 programs in order 156 -> 151 us)
+// long as the launches (two problems of 32 programs in order 155 -> 151 us)
 constexpr int32_t OWNER_MIN_PROGRAMS = 4097;
 constexpr int32_t OWNER_MIN_BATCH = 65;
 constexpr int EVAL_WAVES = 4;

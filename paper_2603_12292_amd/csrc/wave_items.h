@@ -9,8 +9,9 @@ namespace bgl {
 // four items per wave) is walked statically (of every W items a wave takes one,
 // in each round another place on, so that a wave does not meet the same program
 // in chunk after chunk where W is a multiple of the programs: 24 programs x 8
-// 10^6 cases took as long as the longest of them; no atomics); a longer one through shared counters, in claims that shrink
-// towards the list's end: long claims at the end leave waves idle.
+// 10^6 cases took as long as the longest of them; no atomics); a longer one
+// through shared counters, in claims that shrink towards the list's end: long
+// claims at the end leave waves idle.
 // Atomics on one address serialise (12 ns each, whatever the number of
 // waves): with one counter, the first claim of 6144 waves takes 75 us, the
 // last, which finds nothing, as much again, and 300 000 one-tile items of
